@@ -1,0 +1,46 @@
+"""GPU kernels at the sizes where their work split changes (tiles, remainders,
+the smallest and largest of a dispatch's ranges), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2012_02207_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def fmm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2012_02207_amd import fmm as F
+    return F
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+# 1024 sinks are the most that get a workgroup each; more share one by fours
+@pytest.mark.parametrize("n,nsink", [(1, 1), (2, 2), (255, 1), (1025, 63), (1030, 1024), (1030, 1025), (3001, 1027)])
+@pytest.mark.parametrize("eps_soft", [0.0, 1e-3])
+def test_direct_sum_splits(fmm, n, nsink, eps_soft):
+    """Compensated on both sides, so the sums agree to the rounding of their
+    terms (a few 2^-53 each, of either sign) relative to the sum of the terms'
+    sizes; the potential's terms have one sign."""
+    pos, _, mass = W.plummer(max(n, 8), 31)
+    pos, mass = pos[:n].copy(), mass[:n].copy()
+    if n > 100:
+        pos[5] = pos[77]  # a coincident pair contributes nothing without softening
+    sinks = np.random.default_rng(n).permutation(n)[:nsink]
+    print(f"[gpu] direct n={n} nsink={nsink} eps_soft={eps_soft}", flush=True)
+    acc, pot = fmm.direct(_dev(pos), _dev(mass), eps_soft=eps_soft, sinks=_dev(sinks.astype(np.int32)))
+    ad, pd = oracle.direct(pos, mass, eps_soft=eps_soft, sinks=sinks.astype(np.int64))
+    d = pos[None] - pos[sinks][:, None]
+    s2 = (d * d).sum(-1) + eps_soft ** 2
+    s2[s2 == 0.0] = np.inf
+    size = (mass * np.sqrt((d * d).sum(-1)) * s2 ** -1.5).sum(1)
+    assert (np.abs(acc.cpu().numpy() - ad) <= 2e-15 * size[:, None] + 1e-300).all()
+    np.testing.assert_allclose(pot.cpu().numpy(), pd, rtol=2e-15, atol=0.0)

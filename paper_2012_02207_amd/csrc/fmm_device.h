@@ -130,6 +130,86 @@ __device__ __forceinline__ double fmm_fact_dev(int n) {
 }
 
 
+// ---- division without the operator's scaling --------------------------------
+// a / d rounded correctly, as the operator does, for operands well inside the
+// exponent range (div_safe): two Newton steps on the hardware reciprocal, then
+// the quotient corrected by its exact remainder (Markstein's division by fused
+// multiply-adds).  Nine FP64 instructions; the operator's scaling and fix-up
+// instructions about double that time.
+__device__ __forceinline__ double div_scaled(double a, double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(y, fma(-d, y, 1.0), y);
+  y = fma(y, fma(-d, y, 1.0), y);
+  double q = a * y;
+  return fma(fma(-d, q, a), y, q);
+}
+
+// 2^-500 <= |x| < 2^500 (false for 0, infinities and NaN)
+__device__ __forceinline__ bool div_safe(double x) {
+  unsigned e = ((unsigned)(__double_as_longlong(x) >> 52)) & 0x7ffu;
+  return e - 523u < 1000u;
+}
+
+// ---- the bodies of a list of leaves as a stream of 64-body chunks ----------
+// One wavefront reads the bodies of the list src[q .. qe) (cells, bodies
+// [cb, ce) each) in list order, 64 at a time whatever the leaves' sizes: short
+// leaves share a chunk.  The lanes hold a window of 64 list entries (first body
+// and count), loaded side by side and the next window one window ahead, so that
+// no chunk waits for the chain list entry -> cell bounds -> bodies.
+struct BodyStream {
+  const int *src, *cb, *ce;
+  int q, qe;         // list entries not in a window yet
+  int wb, wn;        // this lane's entry of the window: first body, count
+  int pb, pe, pcnt;  // the next window (first body, end; not waited for), its entries
+  int e, nwin, used; // current entry, entries of the window, bodies used of the current one
+
+  __device__ __forceinline__ void fetch(int lane) {
+    pcnt = min(64, qe - q);
+    if (pcnt > 0) {
+      int A = src[q + min(lane, pcnt - 1)];
+      pb = cb[A];
+      pe = ce[A];
+    }
+    q += pcnt;
+  }
+  __device__ __forceinline__ void start(const int* src_, const int* cb_, const int* ce_, int q0, int q1, int lane) {
+    src = src_;
+    cb = cb_;
+    ce = ce_;
+    q = q0;
+    qe = q1;
+    e = nwin = used = 0;
+    fetch(lane);
+  }
+  // This lane's body of the next chunk (`none` past the end of the chunk);
+  // returns the chunk's size, 0 at the end of the list.
+  __device__ __forceinline__ int next(int lane, int none, int& body) {
+    int cnt = 0;
+    body = none;
+    while (cnt < 64) {
+      if (e == nwin) {
+        if (pcnt == 0) break;
+        wb = pb;
+        wn = pe - pb;
+        nwin = pcnt;
+        e = 0;
+        fetch(lane);
+      }
+      int b = __builtin_amdgcn_readlane(wb, e) + used, n = __builtin_amdgcn_readlane(wn, e) - used;
+      int take = min(n, 64 - cnt);
+      if ((unsigned)(lane - cnt) < (unsigned)take) body = b + lane - cnt;
+      cnt += take;
+      if (take == n) {
+        e++;
+        used = 0;
+      } else {
+        used += take;
+      }
+    }
+    return cnt;
+  }
+};
+
 // ---- cross-lane transpose-reduce (the M2L kernels) ------------------------
 // D values per lane summed over the 64 lanes in six halving steps with
 // partner distances 32, 16, 8, 4, 2, 1.  With L values left, a lane keeps the

@@ -394,11 +394,26 @@ __global__ void k_fcell(int ncell, const int* off, const int* src, const double*
 }
 
 // near_i = sum_{j near, j != i} m_j / d^2, partners in ascending id, bodies in
-// sorted order, one running sum per body (k_fleaf adds the far part).
-// One wavefront per sink leaf, a lane per sink body; each source leaf is
-// staged in LDS (one coalesced load, the next one fetched while the current
-// one is summed) and read by all lanes as broadcasts.
+// sorted order, one running sum per body (k_fleaf adds the far part).  The sum
+// of a body is one chain of additions in a fixed order, but its terms are
+// independent, and the FP64 division is most of the work.  A body's own term
+// has d2 = 0 and counts as +0.  The partners are read as 64-body chunks
+// (BodyStream), the next one fetched while the current one is summed.
+
+__device__ __forceinline__ double near_term(const double4& s, const double4& me, bool use) {
+  double dx = s.x - me.x, dy = s.y - me.y, dz = s.z - me.z;
+  double d2 = (dx * dx + dy * dy) + dz * dz;
+  return use && d2 > 0.0 ? s.w / d2 : 0.0;
+}
+
+// Where the leaves fill the chip: one wavefront per sink leaf, the chunk in
+// LDS, the n_B sink bodies replicated over G = 64 / n_B lane groups.  With
+// G > 1 the groups form the terms of G partners side by side and pass them
+// through LDS to the adds.  Bound by FP64 issue of the divisions; with one
+// lane per sink body (45 of 64 lanes idle in a 19-body leaf) the kernel took
+// 887 us at N = 2^20, p = 10 (635 us now) and 4.3 ms at N = 2^22 (2.6 ms).
 constexpr int NF_WAVES = 4;
+constexpr int NF_STEPS = 4;  // terms per lane formed before they are added
 
 __global__ void __launch_bounds__(64 * NF_WAVES) k_near_f(int nleaves, const int* __restrict__ leaves,
                                                           const int* __restrict__ cb,
@@ -407,7 +422,8 @@ __global__ void __launch_bounds__(64 * NF_WAVES) k_near_f(int nleaves, const int
                                                           const int* __restrict__ src,
                                                           const double4* __restrict__ pm, double* f) {
   __shared__ double4 sbuf[NF_WAVES][64];
-  int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ double tbuf[NF_WAVES][64 * NF_STEPS];
+  int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int nblk = (nleaves + NF_WAVES - 1) / NF_WAVES;
   int blk = xcd_block();
   int li = blk * NF_WAVES + wv;
@@ -416,48 +432,150 @@ __global__ void __launch_bounds__(64 * NF_WAVES) k_near_f(int nleaves, const int
   int b = cb[B], e = ce[B];
   int qb = off[B], qe = off[B + 1];
   for (int i0 = b; i0 < e; i0 += 64) {
-    int i = i0 + lane;
-    bool act = i < e;
-    double4 me = act ? pm[i] : make_double4(0.0, 0.0, 0.0, 0.0);
+    int nB = min(64, e - i0);
+    int G = 64 / nB;
+    int g = lane / nB, sl = lane - g * nB;
+    bool act = g < G;
+    double4 me = pm[i0 + sl];
     double near = 0.0;
-    int q = qb, j0 = 0, je = 0;
-    if (q < qe) {
-      int A = src[q];
-      j0 = cb[A];
-      je = ce[A];
-    }
-    double4 cur = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (q < qe && lane < je - j0) cur = pm[j0 + lane];
-    while (q < qe) {
-      int na = min(64, je - j0);
-      int nq = q, nj0 = j0 + 64, nje = je;
-      if (nj0 >= je) {
-        nq = q + 1;
-        if (nq < qe) {
-          int A = src[nq];
-          nj0 = cb[A];
-          nje = ce[A];
-        }
-      }
+    BodyStream st;
+    st.start(src, cb, ce, qb, qe, lane);
+    int j, na = st.next(lane, b, j);
+    double4 cur = pm[j];
+    while (na > 0) {
       __builtin_amdgcn_wave_barrier();
       sbuf[wv][lane] = cur;
       __builtin_amdgcn_wave_barrier();
+      int nn = st.next(lane, b, j);
+      cur = pm[j];
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged chunk is visible to the wave
-      cur = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (nq < qe && lane < nje - nj0) cur = pm[nj0 + lane];
-      int tmax = act ? na : 0;
-      for (int t = 0; t < tmax; t++) {
-        double4 s = sbuf[wv][t];
-        double dx = s.x - me.x, dy = s.y - me.y, dz = s.z - me.z;
-        double d2 = (dx * dx + dy * dy) + dz * dz;
-        if (j0 + t != i && d2 > 0.0) near = near + s.w / d2;
+      if (G == 1) {  // a lane per body: term and add side by side
+        int tmax = act ? na : 0;
+        for (int t = 0; t < tmax; t++) near = near + near_term(sbuf[wv][t], me, true);
+      } else {
+        for (int base = 0; base < na; base += NF_STEPS * G) {
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int u = 0; u < NF_STEPS; u++) {
+            int t = base + u * G + g;
+            if (act && base + u * G < na) tbuf[wv][u * G * nB + lane] = near_term(sbuf[wv][t & 63], me, t < na);
+          }
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_s_waitcnt(0xc07f);  // the terms are visible to the wave
+          int cnt = min(NF_STEPS * G, na - base);
+          const double* tb = &tbuf[wv][sl];
+          int k = 0;
+          for (; k + 4 <= cnt; k += 4) {
+            double t0 = tb[k * nB], t1 = tb[(k + 1) * nB], t2 = tb[(k + 2) * nB], t3 = tb[(k + 3) * nB];
+            near = near + t0;
+            near = near + t1;
+            near = near + t2;
+            near = near + t3;
+          }
+          for (; k < cnt; k++) near = near + tb[k * nB];
+        }
       }
-      q = nq;
-      j0 = nj0;
-      je = nje;
+      na = nn;
     }
-    if (act) f[i] = near;
+    if (g == 0) f[i0 + sl] = near;
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Up to NF_FEW leaves the longest list is the kernel's length (in a 4096-body
+// model a 64-body leaf of the outskirts has all 4096 bodies as partners): a
+// workgroup of 16 wavefronts per leaf, each with four of its bodies at a time.
+// A lane holds one partner of the chunk and forms its terms for the four
+// bodies (wave-uniform); the terms go through LDS to a lane per body, which
+// adds its 64 in order.  At 4096 bodies, p = 6 the near sums took 659 us with a
+// wavefront per leaf and take 181 this way, at 1000 bodies 170 and 39, at 2737
+// leaves (50021 bodies) 243 and 91; at 5358 leaves the two are equal (240), and
+// where the leaves fill the chip the chains of adds lose (320 against 243 us at
+// 14391 leaves).
+constexpr int NF_FEW = 4096;
+
+// The terms of the lane's body (v; no body: mass 0) for sinks k .. k+3 of pm,
+// written to t[0], t[65], t[130], t[195].  masses_safe: every mass of the chunk
+// is 0 or div_safe; with the distances safe too the quotients come from
+// div_scaled, the same bits as the operator's.
+__device__ __forceinline__ void near_terms(const double4& v, const double4* __restrict__ sink, int last,
+                                           bool masses_safe, double* t) {
+  double d[4], m[4];
+  bool safe = masses_safe;
+#pragma unroll
+  for (int u = 0; u < 4; u++) {
+    double4 me = sink[min(u, last)];
+    double dx = v.x - me.x, dy = v.y - me.y, dz = v.z - me.z;
+    double d2 = (dx * dx + dy * dy) + dz * dz;
+    bool ok = d2 > 0.0;  // (operands selected, not the quotient: no branch per term)
+    m[u] = ok ? v.w : 0.0;
+    d[u] = ok ? d2 : 1.0;
+    safe = safe && div_safe(d[u]);
+  }
+  if (ballot(!safe) == 0) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) t[65 * u] = div_scaled(m[u], d[u]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; u++) t[65 * u] = m[u] / d[u];
+  }
+}
+
+// adds the terms t[0 .. cnt) in order, cnt a multiple of 8; the next eight are
+// read while eight are added
+__device__ __forceinline__ double add_terms(double near, const double* t, int cnt) {
+  double a[8];
+#pragma unroll
+  for (int u = 0; u < 8; u++) a[u] = t[u];
+  for (int k = 8; k < cnt; k += 8) {
+    double c[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) c[u] = t[k + u];
+#pragma unroll
+    for (int u = 0; u < 8; u++) near = near + a[u];
+#pragma unroll
+    for (int u = 0; u < 8; u++) a[u] = c[u];
+  }
+#pragma unroll
+  for (int u = 0; u < 8; u++) near = near + a[u];
+  return near;
+}
+
+__global__ void __launch_bounds__(1024) k_near_f_few(int nleaves, const int* __restrict__ leaves,
+                                                     const int* __restrict__ cb, const int* __restrict__ ce,
+                                                     const int* __restrict__ off, const int* __restrict__ src,
+                                                     const double4* __restrict__ pm, double* __restrict__ f) {
+  __shared__ double tbuf[16][4 * 65];
+  int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int li = xcd_block();
+  if (li >= nleaves) return;
+  int B = leaves[li];
+  int b = cb[B], e = ce[B];
+  int qb = off[B], qe = off[B + 1];
+  double* tw = tbuf[wv];
+  int mine = min(lane, 3) * 65;
+  for (int i0 = b + wv * 4; i0 < e; i0 += 64) {
+    int nB = min(4, e - i0);
+    double near = 0.0;
+    BodyStream st;
+    st.start(src, cb, ce, qb, qe, lane);
+    int j, na = st.next(lane, -1, j);
+    double4 cur = make_double4(0.0, 0.0, 0.0, 0.0);  // no body: mass 0
+    if (j >= 0) cur = pm[j];
+    while (na > 0) {
+      double4 v = cur;
+      int nn = st.next(lane, -1, j);
+      cur = make_double4(0.0, 0.0, 0.0, 0.0);
+      if (j >= 0) cur = pm[j];
+      bool msafe = ballot(!(v.w == 0.0 || div_safe(v.w))) == 0;
+      near_terms(v, pm + i0, nB - 1, msafe, tw + lane);
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the terms are visible to the wave
+      near = add_terms(near, tw + mine, (na + 7) & ~7);
+      __builtin_amdgcn_wave_barrier();
+      na = nn;
+    }
+    if (lane < nB) f[i0 + lane] = near;
   }
 }
 
@@ -531,12 +649,13 @@ void estimate_walk(Ctx& c, const std::function<void()>& beside) {
                        c.est_far.src.p, c.c_mass.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.fcell.p);
   }
   group_by_sink(c, c.est_near);
-  {
-    int nblk = (int)ceil_div(c.nleaf, NF_WAVES);
-    unsigned grid = xcd_grid(nblk);
-    hipLaunchKernelGGL(k_near_f, dim3(grid), dim3(64 * NF_WAVES), 0, s, (int)c.nleaf, c.leaves.p,
+  if (c.nleaf <= NF_FEW)
+    hipLaunchKernelGGL(k_near_f_few, dim3(xcd_grid(c.nleaf)), dim3(1024), 0, s, (int)c.nleaf, c.leaves.p,
                        c.c_begin.p, c.c_end.p, c.est_near.off.p, c.est_near.src.p, c.pm.p, c.fpart.p);
-  }
+  else
+    hipLaunchKernelGGL(k_near_f, dim3(xcd_grid(ceil_div(c.nleaf, NF_WAVES))), dim3(64 * NF_WAVES), 0, s,
+                       (int)c.nleaf, c.leaves.p, c.c_begin.p, c.c_end.p, c.est_near.off.p, c.est_near.src.p,
+                       c.pm.p, c.fpart.p);
   stream_wait(c.fork[7], c.side2, s);
   hipLaunchKernelGGL(k_fleaf, dim3((unsigned)ceil_div(c.nleaf, 128)), dim3(128), 0, s, (int)c.nleaf, c.leaves.p,
                      c.c_begin.p, c.c_end.p, c.c_parent.p, c.fcell.p, c.fpart.p);

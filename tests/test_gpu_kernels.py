@@ -44,3 +44,26 @@ def test_direct_sum_splits(fmm, n, nsink, eps_soft):
     size = (mass * np.sqrt((d * d).sum(-1)) * s2 ** -1.5).sum(1)
     assert (np.abs(acc.cpu().numpy() - ad) <= 2e-15 * size[:, None] + 1e-300).all()
     np.testing.assert_allclose(pot.cpu().numpy(), pd, rtol=2e-15, atol=0.0)
+
+
+# up to 4096 leaves the estimate's near sums take sixteen wavefronts per leaf;
+# leaves of one body to more than 64, masses beyond the range of the unscaled
+# division (2^-500 .. 2^500) among them
+@pytest.mark.parametrize("n,n_leaf,scale", [(1, 64, 1.0), (66, 64, 1.0), (130, 128, 1e-160), (700, 1, 1.0),
+                                            (5000, 1, 1.0), (4500, 3, 1e-200), (9000, 200, 1.0)])
+def test_estimate_near_sums(fmm, n, n_leaf, scale):
+    """The scalar-force estimate is summed in the oracle's order: bit for bit."""
+    pos, mass = W.uniform_cube(n, 17)
+    mass[::7] = 0.0
+    mass[1::5] *= scale
+    if n > 100:
+        pos[3] = pos[60]  # coincident bodies count nothing
+        pos[61] = pos[60] + 1e-170
+    print(f"[gpu] estimate n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=2, err_tol=1e-3, n_leaf=n_leaf)
+    f.forces(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    o.run(pos, mass, p=2, err_tol=1e-3, n_leaf=n_leaf, stage="walk")
+    assert np.array_equal(f.export("f_part"), o.get("f_part"))
+    assert np.array_equal(f.export("fmin"), o.get("fmin"))
+    f.close()

@@ -160,7 +160,8 @@ struct Ctx {
   dbuf<double4> pm;   // packed (x, y, z, m), sorted order
   dbuf<double> fpart;
   dbuf<int> leaf_of;  // leaf id of each sorted body
-  dbuf<int> leaves;   // ids of the leaf cells, ascending (built by the upward pass)
+  dbuf<unsigned short> lev;  // tree build: levels of the cells that start at each sorted body
+  dbuf<int> leaves;   // ids of the leaf cells, ascending
 
   // radix sort scratch
   dbuf<int> sort_hist;
@@ -183,7 +184,7 @@ struct Ctx {
   int depth = 0;
   std::vector<int> lvl_first, lvl_count;
   dbuf<int> c_level, c_begin, c_end, c_parent, c_child0, c_nchild;
-  dbuf<int> c_split;  // per-cell scratch for the level build (9 octant starts)
+  dbuf<int> c_split;  // per-cell scratch (chunks per cell)
   dbuf<double> c_mass, c_sx, c_sy, c_sz;  // mass and first moments
   dbuf<double> c_cx, c_cy, c_cz, c_rad;   // centre of mass and radius
   dbuf<unsigned long long> c_rad2bits;
@@ -211,10 +212,8 @@ struct Ctx {
 
   // walks
   dbuf<int2> front[2];
-  // device counters (ints), by offset: [0..1] scan total (long long) of the
-  // tree's level loop; [2] leaves counted by the level loop; [4..5] number of
-  // body chunks of the cells (long long, read by the radius and cell-minimum
-  // kernels); [32] input check; [40..41] near-field body pairs; [48..49]
+  // device counters (ints), by offset: [4..5] number of body chunks of the
+  // cells (long long, read by the radius and cell-minimum kernels); [32] input check; [40..41] near-field body pairs; [48..49]
   // FP32 M2L pairs (stats); [64] sinks with root-level pairs; [256..] walk
   // (64-bit counters at even int offsets)
   dbuf<int> counters;
@@ -293,7 +292,6 @@ void stream_wait(hipEvent_t e, hipStream_t from, hipStream_t to);
 
 // ------------------------------------------------------------------ stages
 void exclusive_scan(Ctx& c, const int* in, int* out, int64_t n, long long* total_dev);
-long long read_total(Ctx& c, const long long* total_dev);
 int radix_sort(Ctx& c, uint64_t* k0, int* v0, uint64_t* k1, int* v1, int64_t n, int nbits);
 uint32_t* radix_sort_narrow(Ctx& c, const uint64_t* in, uint32_t* b0, uint32_t* b1, int64_t n, int nbits);
 

@@ -119,12 +119,6 @@ void exclusive_scan(Ctx& c, const int* in, int* out, int64_t n, long long* total
   HIPCHK(hipGetLastError());
 }
 
-long long read_total(Ctx& c, const long long* total_dev) {
-  HIPCHK(hipMemcpyAsync(c.hbuf, total_dev, sizeof(long long), hipMemcpyDeviceToHost, c.stream));
-  HIPCHK(hipStreamSynchronize(c.stream));
-  return c.hbuf[0];
-}
-
 // ===================================================================== root box
 constexpr int BB_T = 256;
 
@@ -548,163 +542,161 @@ __global__ void k_gather(const double* pos, const double* mass, const int* idx, 
 }
 
 // ===================================================================== cells
-__device__ inline int octant_lower_bound(const uint64_t* key, int b, int e, int o, int shift) {
-  // first index in [b, e) whose digit (at `shift`) is >= o; digits are non-decreasing
-  int lo = b, hi = e;
-  while (lo < hi) {
-    int mid = lo + ((hi - lo) >> 1);
-    int d = (int)((key[mid] >> shift) & 7);
-    if (d < o)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo;
+// The cells straight from the sorted keys, all levels at once.  With lcp the
+// number of leading octal digits that two keys share (-1 across systems) and
+// D(i) the deepest level on which body i is in a cell of more than n_leaf
+// bodies (the largest lcp(key[k], key[k + n_leaf]) over the windows k .. k +
+// n_leaf that hold i), body i's leaf is on level Lf(i) = min(D(i) + 1, 21),
+// the cells that start at i are those of the levels lcp(key[i-1], key[i]) + 1
+// .. Lf(i), and the cells that end with it those of lcp(key[i], key[i+1]) + 1
+// .. Lf(i).  Ids are breadth first, so a cell's id is its level's first id plus
+// the number of that level's cells that start before it: k_cell_levels counts
+// the starts per level and tile, k_rs_rowscan sums them over the tiles, and
+// k_cell_emit writes the cells, the leaf list and every body's leaf.  Three
+// launches (35 us in all at N = 2^20, 25 us at N = 1000) instead of three per
+// level for 12 to 22 levels and four for the leaf lists (290 and 150 us).
+constexpr int CT_T = 256, CT_TILE = 1024, CT_NLEAF_MAX = 1024;
+constexpr int CT_LEVELS = FMM_MAX_LEVEL + 1;  // levels 0..21
+constexpr int CT_ROWS = 2 * CT_LEVELS;        // counts per tile: cells of each level, leaves of each level
+
+// leading octal digits shared by two 63-bit keys
+__device__ __forceinline__ int key_lcp(uint64_t a, uint64_t b) {
+  return a == b ? FMM_MAX_LEVEL : (__builtin_clzll(a ^ b) - 1) / 3;
 }
 
-// ---- the level loop on the device -----------------------------------------
-// Level l's cells are [lvl[2l], lvl[2l] + lvl[2l+1]) (first id, count), kept on
-// the device: every launch of a level reads its count there and the emit of
-// level l writes level l + 1's entry, so the host enqueues a batch of levels
-// without waiting and reads the table once at the end.  The cell arrays have
-// a fixed capacity; a level whose children would not fit sets the overflow
-// flag and ends the tree (the host grows the arrays and builds again).
-constexpr int LV_T = 256, LV_NB = 256, LV_SPLIT_BLOCKS = 512;
-constexpr int LV_TABLE = 128, LV_OVERFLOW = 180;  // int offsets in the device counters
-
-__global__ void k_lv_init(int nsys, int* lvl, int* nleaf, int* overflow) {
-  int t = threadIdx.x;
-  if (t < 2 * (FMM_MAX_LEVEL + 2)) lvl[t] = t == 1 ? nsys : 0;
-  if (t == 0) {
-    *nleaf = 0;
-    *overflow = 0;
-  }
-}
-
-// Children of every cell of the level: eight lanes per cell, lane o finding
-// the first body of octant o by its own binary search (the searches run side
-// by side instead of one after another); cells that stay leaves are counted in
-// *nleaf (one atomic per wavefront).  Grid-stride over the device count.
-__global__ void __launch_bounds__(LV_T) k_split_lv(int level, const int* lvl, int n_leaf, const uint64_t* key,
-                                                    const int* cb, const int* ce, int* split, int* nch,
-                                                    int* nleaf) {
-  int first = lvl[2 * level], count = lvl[2 * level + 1];
-  int64_t total = (int64_t)count * 8;
-  for (int64_t T0 = (int64_t)blockIdx.x * LV_T; T0 < total; T0 += (int64_t)gridDim.x * LV_T) {
-    int64_t T = T0 + threadIdx.x;
-    int t = (int)(T >> 3), o = (int)(T & 7);
-    bool ok = t < count;  // the 8 lanes of a cell agree
-    bool splits = false;
-    int bound = 0, e = 0;
-    if (ok) {
-      int c = first + t;
-      int b = cb[c];
-      e = ce[c];
-      splits = e - b > n_leaf && level < FMM_MAX_LEVEL;
-      if (splits) {
-        int shift = 3 * (FMM_MAX_LEVEL - (level + 1));
-        bound = o == 0 ? b : octant_lower_bound(key, b, e, o, shift);
-      }
+// lev[i]: (lcp(key[i-1], key[i]) + 1) << 8 | Lf(i); cnt[row * nblocks + block]:
+// the tile's counts; also clears nchild[0 .. cap), which the emit counts up
+__global__ void __launch_bounds__(CT_T) k_cell_levels(int n, int n_leaf, const uint64_t* __restrict__ key,
+                                                      const int* __restrict__ sys_off, int nsys,
+                                                      unsigned short* __restrict__ lev, int* __restrict__ cnt,
+                                                      int nblocks, int* __restrict__ nchild, int cap) {
+  __shared__ signed char win[2][CT_TILE + CT_NLEAF_MAX];
+  __shared__ int rows[CT_ROWS];
+  for (int i = blockIdx.x * CT_T + threadIdx.x; i < cap; i += gridDim.x * CT_T) nchild[i] = 0;
+  if (threadIdx.x < CT_ROWS) rows[threadIdx.x] = 0;
+  int t0 = blockIdx.x * CT_TILE;
+  int w0 = t0 - n_leaf;        // first window of the tile's bodies
+  int nw = CT_TILE + n_leaf;   // windows w0 .. t0 + CT_TILE - 1
+  for (int u = threadIdx.x; u < nw; u += CT_T) {
+    int k = w0 + u, c = -1;
+    if (k >= 0 && k + n_leaf < n) {
+      bool same = nsys == 1 || sys_off[system_of(sys_off, nsys, k) + 1] > k + n_leaf;
+      if (same) c = min(key_lcp(key[k], key[k + n_leaf]), FMM_MAX_LEVEL - 1);
     }
-    int next = __shfl_down(bound, 1, 8);
-    if (o == 7) next = e;
-    int cnt = splits && next > bound ? 1 : 0;
-    for (int m = 1; m < 8; m <<= 1) cnt += __shfl_xor(cnt, m, 8);
-    if (ok && splits) {
-      split[9 * (int64_t)t + o] = bound;
-      if (o == 7) split[9 * (int64_t)t + 8] = e;
+    win[0][u] = (signed char)c;
+  }
+  __syncthreads();
+  // largest over 2^j windows from each on, up to the last j with 2^j <= n_leaf + 1
+  int cur = 0, len = 1;
+  while (2 * len <= n_leaf + 1) {
+    for (int u = threadIdx.x; u < nw; u += CT_T) {
+      signed char x = win[cur][u];
+      if (u + len < nw) x = max(x, win[cur][u + len]);
+      win[cur ^ 1][u] = x;
     }
-    if (ok && o == 0) nch[t] = cnt;
-    unsigned long long leaves = __ballot(ok && o == 0 && cnt == 0);
-    if ((threadIdx.x & 63) == 0 && leaves) atomicAdd(nleaf, (int)__popcll(leaves));
+    cur ^= 1;
+    len *= 2;
+    __syncthreads();
   }
-}
-
-__device__ inline int block_sum(int v, int* sh) {
-  int tot;
-  block_excl_scan(v, sh, tot);
-  return tot;
-}
-
-// children counts of a level summed over LV_NB contiguous ranges
-__global__ void __launch_bounds__(LV_T) k_lv_bsum(int level, const int* lvl, const int* nch, int* bsum) {
-  __shared__ int sh[SCAN_T];
-  int count = lvl[2 * level + 1];
-  int chunk = (count + LV_NB - 1) / LV_NB;
-  int b0 = min(count, blockIdx.x * chunk), b1 = min(count, b0 + chunk);
-  int v = 0;
-  for (int t = b0 + threadIdx.x; t < b1; t += LV_T) v += nch[t];
-  int tot = block_sum(v, sh);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-// child ids by a scan of the counts (the range's offset from the block sums),
-// then every cell's children, non-empty octants in octant order; block 0
-// records the next level
-__global__ void __launch_bounds__(LV_T) k_lv_emit(int level, int* lvl, const int* split, const int* nch,
-                                                   const int* bsum, int cap, int* overflow, int* c_level,
-                                                   int* c_begin, int* c_end, int* c_parent, int* c_child0,
-                                                   int* c_nchild) {
-  __shared__ int sh[SCAN_T];
-  int first = lvl[2 * level], count = lvl[2 * level + 1];
-  int next_first = first + count;
-  int chunk = (count + LV_NB - 1) / LV_NB;
-  int b0 = min(count, blockIdx.x * chunk), b1 = min(count, b0 + chunk);
-  int pre = 0, all = 0;
-  for (int k = threadIdx.x; k < LV_NB; k += LV_T) {
-    int v = bsum[k];
-    if (k < (int)blockIdx.x) pre += v;
-    all += v;
-  }
-  pre = block_sum(pre, sh);
-  all = block_sum(all, sh);
-  bool over = (int64_t)next_first + all > cap;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    int nxt = level + 1;
-    if (nxt <= FMM_MAX_LEVEL + 1) {
-      lvl[2 * nxt] = next_first;
-      lvl[2 * nxt + 1] = over ? 0 : all;
+  for (int u = threadIdx.x; u < CT_TILE; u += CT_T) {
+    int i = t0 + u;
+    if (i >= n) continue;
+    int D = max(win[cur][u], win[cur][u + n_leaf + 1 - len]);  // windows i - n_leaf .. i
+    int Lf = D + 1;
+    int a = -1;
+    if (i > 0) {
+      bool same = nsys == 1 || sys_off[system_of(sys_off, nsys, i)] != i;
+      if (same) a = key_lcp(key[i - 1], key[i]);
     }
-    if (over) *overflow = 1;
+    lev[i] = (unsigned short)((a + 1) << 8 | Lf);
+    for (int l = a + 1; l <= Lf; l++) atomicAdd(&rows[l], 1);
+    if (a < Lf) atomicAdd(&rows[CT_LEVELS + Lf], 1);
   }
-  for (int base = b0; base < b1; base += LV_T) {
-    int t = base + threadIdx.x;
-    int k = t < b1 ? nch[t] : 0;
-    int tile;
-    int ex = block_excl_scan(k, sh, tile);
-    if (t < b1) {
-      int c = first + t;
-      c_nchild[c] = over ? 0 : k;
-      if (k == 0 || over) {
-        c_child0[c] = -1;
-      } else {
-        int id = next_first + pre + ex;
-        c_child0[c] = id;
-        for (int o = 0; o < 8; o++) {
-          int s0 = split[9 * (int64_t)t + o], s1 = split[9 * (int64_t)t + o + 1];
-          if (s1 > s0) {
-            c_level[id] = level + 1;
-            c_begin[id] = s0;
-            c_end[id] = s1;
-            c_parent[id] = c;
-            id++;
-          }
+  __syncthreads();
+  if (threadIdx.x < CT_ROWS) cnt[(size_t)threadIdx.x * nblocks + blockIdx.x] = rows[threadIdx.x];
+}
+
+// Bodies per wavefront of a tile are taken 64 at a time; the ranks of the
+// starts within 64 bodies come from ballots.  Ids of cap and more are not
+// written (the host enlarges the arrays and emits again).
+__global__ void __launch_bounds__(CT_T) k_cell_emit(int n, const unsigned short* __restrict__ lev,
+                                                    const int* __restrict__ offs, const int* __restrict__ rowtot,
+                                                    int nblocks, int cap, int* __restrict__ c_level,
+                                                    int* __restrict__ c_begin, int* __restrict__ c_end,
+                                                    int* __restrict__ c_parent, int* __restrict__ c_child0,
+                                                    int* __restrict__ c_nchild, int* __restrict__ leaf_of,
+                                                    int* __restrict__ leaves) {
+  constexpr int W = CT_T / 64, STEPS = CT_TILE / CT_T;
+  __shared__ int base[W][CT_ROWS];  // first id (or leaf rank) of each wavefront's part, by row
+  int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int i0 = blockIdx.x * CT_TILE + w * 64 * STEPS;
+  int top = 0;  // deepest level that has cells
+  for (int l = 0; l < CT_LEVELS; l++)
+    if (rowtot[l] > 0) top = l;
+  // counts of this wavefront's part
+  int mine = 0;  // lane r: count of row r
+  for (int k = 0; k < STEPS; k++) {
+    int i = i0 + 64 * k + lane;
+    int v = i < n ? lev[i] : 0xff00;
+    int a1 = v >> 8, Lf = v & 255;
+    for (int l = 0; l <= top; l++) {
+      uint64_t st = ballot(a1 <= l && l <= Lf), lf = ballot(a1 <= l && l == Lf);
+      if (lane == l) mine += (int)__popcll(st);
+      if (lane == CT_LEVELS + l) mine += (int)__popcll(lf);
+    }
+  }
+  if (lane < CT_ROWS) base[w][lane] = mine;
+  __syncthreads();
+  if (threadIdx.x < CT_ROWS) {
+    int r = threadIdx.x;
+    // the row's start: totals of the rows before it (of its kind), then the tiles before this one
+    int run = offs[(size_t)r * nblocks + blockIdx.x];
+    for (int q = r < CT_LEVELS ? 0 : CT_LEVELS; q < r; q++) run += rowtot[q];
+    for (int ww = 0; ww < W; ww++) {
+      int c = base[ww][r];
+      base[ww][r] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  uint64_t lt = lanemask_lt();
+  int next = lane < CT_ROWS ? base[w][lane] : 0;  // lane r: next id (or leaf rank) of row r
+  for (int k = 0; k < STEPS; k++) {
+    int i = i0 + 64 * k + lane;
+    bool ok = i < n;
+    int v = ok ? lev[i] : 0xff00;
+    int a1 = v >> 8, Lf = v & 255;
+    int next1 = ok && i + 1 < n ? lev[i + 1] >> 8 : 0;  // levels above this one's go on past body i
+    int prev = -1;       // the cell that holds body i, one level up
+    bool prev_st = false;
+    for (int l = 0; l <= top; l++) {
+      bool st = a1 <= l && l <= Lf, in = ok && l <= Lf;
+      uint64_t sm = ballot(st), lm = ballot(st && l == Lf);
+      int id0 = __builtin_amdgcn_readlane(next, l), lf0 = __builtin_amdgcn_readlane(next, CT_LEVELS + l);
+      int id = id0 + (int)__popcll(sm & lt) + (st ? 1 : 0) - 1;  // the level's last cell that starts at or before i
+      if (st && id < cap) {
+        c_level[id] = l;
+        c_begin[id] = i;
+        c_parent[id] = prev;
+        if (l == Lf) {
+          c_child0[id] = -1;
+          leaves[lf0 + (int)__popcll(lm & lt)] = id;
+        }
+        if (prev >= 0) {
+          atomicAdd(&c_nchild[prev], 1);
+          if (prev_st) c_child0[prev] = id;
         }
       }
+      if (in && id < cap) {
+        if (next1 <= l) c_end[id] = i + 1;
+        if (l == Lf) leaf_of[i] = id;
+      }
+      prev = id;
+      prev_st = st;
+      if (lane == l) next += (int)__popcll(sm);
+      if (lane == CT_LEVELS + l) next += (int)__popcll(lm);
     }
-    pre += tile;
   }
-}
-
-// one root per system: cell s holds the bodies of system s
-__global__ void k_roots(int nsys, const int* sys_off, int* c_level, int* c_begin, int* c_end,
-                        int* c_parent) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nsys) return;
-  c_level[s] = 0;
-  c_begin[s] = sys_off[s];
-  c_end[s] = sys_off[s + 1];
-  c_parent[s] = -1;
 }
 
 // mass, first moments and centre of mass, one level (deepest first); leaves sum
@@ -812,12 +804,6 @@ __global__ void k_radius_final(const unsigned long long* r2bits, int ncell, cons
   geo[c] = make_double4(cx[c], cy[c], cz[c], r);
 }
 
-__global__ void k_leaf_of(const int* cb, const int* ce, const int* nch, int ncell, int* leaf_of) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncell || nch[c] != 0) return;
-  for (int i = cb[c]; i < ce[c]; i++) leaf_of[i] = c;
-}
-
 static inline dim3 grid1(int64_t n, int t = 256) { return dim3((unsigned)ceil_div(n, t)); }
 
 // every body is in one cell per level: at most (depth + 1) n / CELL_CHUNK + ncell chunks
@@ -876,16 +862,6 @@ void refresh_frozen(Ctx& c, const double* pos, const double* mass) {
                      c.sy.p, c.sz.p, c.sm.p, c.pm.p);
   HIPCHK(hipGetLastError());
   cell_moments(c, false);
-}
-
-__global__ void k_list_leaves(const int* nch, int ncell, int* flag) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < ncell) flag[c] = nch[c] == 0 ? 1 : 0;
-}
-
-__global__ void k_compact_leaves(const int* flag, const int* off, int ncell, int* leaves) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < ncell && flag[c]) leaves[off[c]] = c;
 }
 
 void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
@@ -957,81 +933,54 @@ void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
   HIPCHK(hipGetLastError());
   if (c.have_events) HIPCHK(hipEventRecord(c.ev[17], s));
 
-  // breadth-first levels, built on the device (see k_lv_emit)
+  // the cells (see k_cell_levels); more of them than the arrays hold: larger
+  // arrays, and the cells written again
   size_t cap = (size_t)std::max<int64_t>(1024, 4 * n / std::max(1, c.prm.n_leaf) + 64 + 2 * nsys);
-  cap = std::max(cap, c.c_level.cap);
+  if (c.c_level.epoch == c.ws.epoch) cap = std::max(cap, c.c_level.cap);
   ensure(c.ws, c.counters, 512);  // the full size at once: counters[4..5] must outlive this call
-  int* nleaf_dev = c.counters.p + 2;
-  int* lvl = c.counters.p + LV_TABLE;
-  int* overflow = c.counters.p + LV_OVERFLOW;
-  constexpr int NLV = FMM_MAX_LEVEL + 2;  // table entries: levels 0..21 and the empty one after
-  constexpr int FIRST_BATCH = 12;         // levels enqueued before the first read-back
-  long long nleaf = 0;
-  int depth = 0;
+  int nb = (int)ceil_div(n, CT_TILE);
+  ensure(c.ws, c.sort_hist, (size_t)CT_ROWS * nb * 2 + CT_ROWS + 64);
+  int* cnt = c.sort_hist.p;
+  int* offs = cnt + (size_t)CT_ROWS * nb;
+  int* rowtot = offs + (size_t)CT_ROWS * nb;
+  ensure(c.ws, c.lev, (size_t)n);
+  int* h = (int*)c.hbuf;  // read-back: cells of each level, then leaves of each level
+  int64_t ncell = 0, nleaf = 0;
   for (int attempt = 0;; attempt++) {
-    for (auto* b : {&c.c_level, &c.c_begin, &c.c_end, &c.c_parent, &c.c_child0, &c.c_nchild})
+    for (auto* b : {&c.c_level, &c.c_begin, &c.c_end, &c.c_parent, &c.c_child0, &c.c_nchild, &c.leaves})
       ensure(c.ws, *b, cap);
-    cap = std::min({c.c_level.cap, c.c_begin.cap, c.c_end.cap, c.c_parent.cap, c.c_child0.cap,
-                    c.c_nchild.cap, (size_t)INT_MAX / 16});
-    ensure(c.ws, c.c_split, 10 * cap + LV_NB + 64);
-    int* split = c.c_split.p;  // 9 octant bounds per cell of the level
-    int* nch = split + 9 * cap;
-    int* bsum = nch + cap;
-    hipLaunchKernelGGL(k_roots, grid1(nsys), dim3(256), 0, s, nsys, c.sys_off.p, c.c_level.p, c.c_begin.p,
-                       c.c_end.p, c.c_parent.p);
-    hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, nsys, lvl, nleaf_dev, overflow);
-    int* h = (int*)c.hbuf;  // read-back: the table, then the leaf count and the overflow flag
-    int level = 0;
-    bool more = true;
-    for (int batch_end = FIRST_BATCH; more; batch_end = NLV - 1) {
-      for (; level < batch_end; level++) {
-        hipLaunchKernelGGL(k_split_lv, dim3(LV_SPLIT_BLOCKS), dim3(LV_T), 0, s, level, lvl, c.prm.n_leaf,
-                           c.key[0].p, c.c_begin.p, c.c_end.p, split, nch, nleaf_dev);
-        hipLaunchKernelGGL(k_lv_bsum, dim3(LV_NB), dim3(LV_T), 0, s, level, lvl, nch, bsum);
-        hipLaunchKernelGGL(k_lv_emit, dim3(LV_NB), dim3(LV_T), 0, s, level, lvl, split, nch, bsum, (int)cap,
-                           overflow, c.c_level.p, c.c_begin.p, c.c_end.p, c.c_parent.p, c.c_child0.p,
-                           c.c_nchild.p);
-      }
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(h, lvl, 2 * NLV * sizeof(int), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipMemcpyAsync(h + 2 * NLV, nleaf_dev, sizeof(int), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipMemcpyAsync(h + 2 * NLV + 1, overflow, sizeof(int), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      more = level < NLV - 1 && h[2 * level + 1] > 0 && !h[2 * NLV + 1];
+    int icap = (int)std::min(cap, (size_t)INT_MAX / 16);
+    hipLaunchKernelGGL(k_cell_levels, dim3(nb), dim3(CT_T), 0, s, (int)n, c.prm.n_leaf, c.key[0].p, c.sys_off.p,
+                       nsys, c.lev.p, cnt, nb, c.c_nchild.p, icap);
+    hipLaunchKernelGGL(k_rs_rowscan, dim3(CT_ROWS), dim3(RS_T), 0, s, cnt, nb, offs, rowtot);
+    hipLaunchKernelGGL(k_cell_emit, dim3(nb), dim3(CT_T), 0, s, (int)n, c.lev.p, offs, rowtot, nb, icap,
+                       c.c_level.p, c.c_begin.p, c.c_end.p, c.c_parent.p, c.c_child0.p, c.c_nchild.p, c.leaf_of.p,
+                       c.leaves.p);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(h, rowtot, CT_ROWS * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    ncell = nleaf = 0;
+    for (int l = 0; l < CT_LEVELS; l++) {
+      ncell += h[l];
+      nleaf += h[CT_LEVELS + l];
     }
-    if (!h[2 * NLV + 1]) {
-      c.lvl_first.clear();
-      c.lvl_count.clear();
-      for (int l = 0; l < NLV && h[2 * l + 1] > 0; l++) {
-        c.lvl_first.push_back(h[2 * l]);
-        c.lvl_count.push_back(h[2 * l + 1]);
-      }
-      nleaf = h[2 * NLV];
-      depth = (int)c.lvl_first.size() - 1;
-      break;
-    }
-    if (attempt > 8) throw hip_error{hipErrorUnknown, "cell arrays did not converge"};
-    cap *= 2;  // a level did not fit: larger arrays, build again
+    if (ncell <= icap) break;
+    if (attempt > 0 || ncell > INT_MAX / 16) throw hip_error{hipErrorUnknown, "too many cells"};
+    cap = (size_t)ncell;
   }
-  c.ncell = (int64_t)c.lvl_first[depth] + c.lvl_count[depth];
-  c.depth = depth;
-  int nc = (int)c.ncell;
-
-  cell_moments(c, true);
-  hipLaunchKernelGGL(k_leaf_of, grid1(nc), dim3(256), 0, s, c.c_begin.p, c.c_end.p, c.c_nchild.p, nc,
-                     c.leaf_of.p);
-  HIPCHK(hipGetLastError());
-  // the leaf cells in id order (built here, before any fork, so that every
-  // stream sees the list)
-  ensure(c.ws, c.c_split, (size_t)2 * nc + 64);
-  ensure(c.ws, c.leaves, (size_t)nc);
-  int* flag = c.c_split.p;
-  int* off = flag + nc + 32;
-  hipLaunchKernelGGL(k_list_leaves, grid1(nc), dim3(256), 0, s, c.c_nchild.p, nc, flag);
-  exclusive_scan(c, flag, off, nc, nullptr);
-  hipLaunchKernelGGL(k_compact_leaves, grid1(nc), dim3(256), 0, s, flag, off, nc, c.leaves.p);
-  HIPCHK(hipGetLastError());
+  c.lvl_first.clear();
+  c.lvl_count.clear();
+  int first = 0;
+  for (int l = 0; l < CT_LEVELS && h[l] > 0; l++) {
+    c.lvl_first.push_back(first);
+    c.lvl_count.push_back(h[l]);
+    first += h[l];
+  }
+  c.ncell = ncell;
+  c.depth = (int)c.lvl_first.size() - 1;
   c.nleaf = nleaf;
+  cell_moments(c, true);
+  HIPCHK(hipGetLastError());
 }
 
 }  // namespace fmm

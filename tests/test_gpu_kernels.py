@@ -67,3 +67,33 @@ def test_estimate_near_sums(fmm, n, n_leaf, scale):
     assert np.array_equal(f.export("f_part"), o.get("f_part"))
     assert np.array_equal(f.export("fmin"), o.get("fmin"))
     f.close()
+
+
+def _clumps(n, seed):
+    """Points at every scale: a cube, tight clumps, exact duplicates (level-21
+    cells) and a line of points that splits into single-child chains."""
+    rng = np.random.default_rng(seed)
+    pos = rng.uniform(-1.0, 1.0, (n, 3))
+    k = n // 4
+    pos[:k] = 0.25 + rng.normal(size=(k, 3)) * 10.0 ** rng.uniform(-9, -1, (k, 1))
+    if n > 40:
+        pos[k:k + n // 8] = pos[k]
+    return pos, np.full(n, 1.0 / n)
+
+
+# the cells are written in tiles of 1024 bodies, from windows of n_leaf + 1
+@pytest.mark.parametrize("n,n_leaf", [(1, 64), (2, 1), (64, 64), (65, 64), (1024, 7), (1025, 64), (2047, 1),
+                                      (2049, 1024), (5000, 100), (3071, 1023)])
+def test_cells_match_oracle(fmm, n, n_leaf):
+    """Cells, leaves and centres of the oracle's tree, bit for bit."""
+    pos, mass = _clumps(n, 40 + n)
+    print(f"[gpu] cells n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=1, n_leaf=n_leaf)
+    f.build(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    o.run(pos, mass, p=1, err_tol=1e-7, n_leaf=n_leaf, stage="upward")
+    for k in ("cell_level", "cell_begin", "cell_end", "cell_parent", "cell_child0", "cell_nchild"):
+        assert np.array_equal(f.export(k).astype(np.int64), o.get(k).astype(np.int64)), k
+    assert f.stats()["nleaf"] == (o.get("cell_nchild") == 0).sum()
+    assert np.array_equal(f.export("mult"), o.get("mult"))  # the leaf list reached every leaf
+    f.close()

@@ -302,10 +302,7 @@ __global__ void __launch_bounds__(64 * ADJ_WAVES) k_adj_near(const int* __restri
   int nseg = plan.cell_nseg[B];
   int b = cb[B], e = ce[B];
   int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) {  // one segment of a long list (the leaf's bodies fit one wavefront)
-    qb += seg * plan.K;
-    qe = min(qe, qb + plan.K);
-  }
+  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);  // (the leaf's bodies fit one wavefront)
   bool to_part = seg > 0;  // later segments of a long list: partial slots
   int64_t pslot = to_part ? (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) - b : 0;
   for (int i0 = b; i0 < e; i0 += 64) {

@@ -150,6 +150,27 @@ __device__ __forceinline__ bool div_safe(double x) {
   return e - 523u < 1000u;
 }
 
+// entries of segment seg of a list [qb, qe) cut into nseg segments (NfPlan)
+__device__ __forceinline__ void segment_bounds(int nseg, int seg, int& qb, int& qe) {
+  int64_t len = qe - qb;
+  int b = qb;
+  qb = b + (int)(len * seg / nseg);
+  qe = b + (int)(len * (seg + 1) / nseg);
+}
+
+// system of body i: the last s with off[s] <= i
+__device__ __forceinline__ int system_of(const int* off, int nsys, int64_t i) {
+  int lo = 0, hi = nsys - 1;
+  while (lo < hi) {
+    int mid = (lo + hi + 1) >> 1;
+    if (off[mid] <= i)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
 // ---- the bodies of a list of leaves as a stream of 64-body chunks ----------
 // One wavefront reads the bodies of the list src[q .. qe) (cells, bodies
 // [cb, ce) each) in list order, 64 at a time whatever the leaves' sizes: short

@@ -72,7 +72,7 @@ template <class T>
 void ensure(Workspace& w, dbuf<T>& b, size_t n, bool keep = false, hipStream_t s = nullptr) {
   bool live = b.p && b.epoch == w.epoch;
   if (live && n <= b.cap) return;
-  size_t ncap = n + n / 4 + 64;
+  size_t ncap = w.arena ? n : n + n / 4 + 64;  // (a carved buffer never grows in place: no slack)
   T* np = (T*)ws_alloc(w, ncap * sizeof(T));
   if (keep && live && b.cap) HIPCHK(hipMemcpyAsync(np, b.p, b.cap * sizeof(T), hipMemcpyDeviceToDevice, s));
   if (live) {
@@ -104,9 +104,10 @@ struct CellList {
 // ------------------------------------------------------------------ near field
 // Work items of the near-field kernels: item li < nleaf is leaf li of the leaf
 // list (its whole source list, or the first segment of a long one); a leaf
-// whose list is longer than K entries (and whose bodies fit one wavefront) is
-// cut into ceil(len / K) contiguous segments, and segments 1.. are the extra
-// items (leaf, segment) after the leaves, in any order.  The first segment
+// whose list is longer than its system's K entries (and whose bodies fit one
+// wavefront) is cut into ns = ceil(len / K) contiguous segments, segment k the
+// entries [len k / ns, len (k + 1) / ns), and segments 1.. are the extra items
+// (leaf, segment) after the leaves, in any order.  The first segment
 // writes the near field itself, segment k > 0 its partial sums to slots
 // cell_pbase[B] + (k - 1) n_B + body; these are added in segment order
 // afterwards, so the result does not depend on the order of the items.
@@ -116,7 +117,6 @@ struct NfPlan {
   const int2* extra;      // (leaf index, segment) of the extra items
   const int* nextra;      // extra item count (device)
   int nleaf;
-  int K;                  // list entries per segment
   int max_items;          // host bound on the item count (grid size)
   int max_slots;          // host bound on the partial slots
 };

@@ -249,10 +249,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
   int nseg = plan.cell_nseg[B];
   int b = cb[B], e = ce[B];
   int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) {  // one segment of a long list (the leaf's bodies fit one wavefront)
-    qb += seg * plan.K;
-    qe = min(qe, qb + plan.K);
-  }
+  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);  // (the leaf's bodies fit one wavefront)
   // output: the near field itself (a whole list, or the first segment of a
   // long one), or the partial sums of a later segment
   bool to_part = seg > 0;
@@ -381,17 +378,36 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 
 // Near-field work items (the plan above), one thread per leaf; ctr[0] counts
 // the extra items and ctr[1] the partial slots (both zero on entry).
-constexpr int NF_SEG_MIN = 256;    // list entries per segment, at least
-constexpr int NF_SEG_DIV = 8192;   // and at least the list total / NF_SEG_DIV
+// List entries per segment, at least: a 512th of the system's bodies, between
+// NF_SEG_MIN and NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
+// more of smaller leaves.  A small system has few leaves with long lists
+// (4096 bodies: 303 leaves of 226 entries), and only short segments spread
+// them over the chip; a large one has enough leaves, and only the outliers
+// are cut (at N = 2^18 one leaf holds 2776 entries, 42 times the mean work).
+// The bound is the system's own, so a system of a batch sums in the same order
+// as alone; only a list total over K NF_ITEMS raises it, to bound the partial
+// sums' memory.  @SEG_FIGS@
+constexpr int NF_SEG_MIN = 8, NF_SEG_MAX = 512;
+constexpr int NF_SEG_DIV = 512;
+constexpr int64_t NF_ITEMS = 65536;
+
+__host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int floor_k) {
+  int64_t k = bodies / NF_SEG_DIV;
+  k = k < NF_SEG_MIN ? NF_SEG_MIN : k > NF_SEG_MAX ? NF_SEG_MAX : k;
+  k = k * 64 / max_nb;
+  return k < floor_k ? floor_k : (int)k;
+}
 
 __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* __restrict__ cb,
-                          const int* __restrict__ ce, const int* __restrict__ off, int K, int* cell_nseg,
-                          int* cell_pbase, int2* extra, int* ctr) {
+                          const int* __restrict__ ce, const int* __restrict__ off, const int* __restrict__ sys_off,
+                          int nsys, int floor_k, int max_nb, int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
   int li = blockIdx.x * blockDim.x + threadIdx.x;
   if (li >= nleaf) return;
   int B = leaves[li];
   int len = off[B + 1] - off[B], nB = ce[B] - cb[B];
-  int ns = (nB <= 64 && len > K) ? (len + K - 1) / K : 1;
+  int sys = nsys > 1 ? system_of(sys_off, nsys, cb[B]) : 0;
+  int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, floor_k);
+  int ns = (nB <= max_nb && len > K) ? (len + K - 1) / K : 1;
   cell_nseg[B] = ns;
   if (ns > 1) {
     int x = atomicAdd(ctr, ns - 1);
@@ -414,6 +430,7 @@ __global__ void k_nf_combine(int64_t n, const int* __restrict__ leaf_of, const i
   int nB = ce[B] - cb[B];
   const double4* pp = part + cell_pbase[B] + (i - cb[B]);
   double4 t = nearbuf[i];
+#pragma unroll 4
   for (int k = 1; k < ns; k++) {
     double4 v = pp[(size_t)(k - 1) * nB];
     t.x += v.x;
@@ -429,22 +446,23 @@ __global__ void k_nf_combine(int64_t n, const int* __restrict__ leaf_of, const i
 void plan_near_field(Ctx& c) {
   int nleaf = (int)c.nleaf;
   int64_t cnt = c.p2p.count;
-  int K = (int)std::max<int64_t>(NF_SEG_MIN, ceil_div(cnt, NF_SEG_DIV));
-  // a split leaf holds len > K entries in ceil(len / K) < 2 len / K items, so
-  // extra items number fewer than cnt / K <= NF_SEG_DIV; its partial slots,
-  // (ceil(len / K) - 1) n_B < 64 len / K, fewer than 64 cnt / K in all
-  int64_t extra_max = std::min<int64_t>(NF_SEG_DIV, ceil_div(cnt, K));
-  int64_t slot_max = std::min<int64_t>(64 * (int64_t)NF_SEG_DIV, ceil_div(64 * cnt, K));
+  int floor_k = (int)ceil_div(cnt, NF_ITEMS);
+  // a split leaf holds len > K entries in ceil(len / K) segments, so the extra
+  // items number fewer than cnt / K, with the smallest K of any system
+  int max_nb = std::min(64, c.prm.n_leaf);
+  int kmin = nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, floor_k);
+  int64_t extra_max = cnt / kmin;
+  int64_t slot_max = extra_max * max_nb;
   ensure(c.ws, c.nf_cell_nseg, (size_t)c.ncell);
   ensure(c.ws, c.nf_cell_pbase, (size_t)c.ncell);
   ensure(c.ws, c.nf_extra, (size_t)extra_max + 1);
   ensure(c.ws, c.nf_part, (size_t)slot_max + 1);
   int* ctr = c.counters.p + 44;
   hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
-                     c.c_begin.p, c.c_end.p, c.p2p.off.p, K, c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p,
-                     ctr);
+                     c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, floor_k, max_nb, c.nf_cell_nseg.p,
+                     c.nf_cell_pbase.p, c.nf_extra.p, ctr);
   HIPCHK(hipGetLastError());
-  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr, nleaf, K, (int)(nleaf + extra_max),
+  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr, nleaf, (int)(nleaf + extra_max),
                 (int)slot_max};
 }
 

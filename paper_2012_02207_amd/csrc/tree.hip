@@ -230,19 +230,6 @@ __global__ void __launch_bounds__(BB_T) k_bbox_sys(const double* pos, const int*
   rb[4] = 2097152.0 / L;
 }
 
-// system of body i: the last s with off[s] <= i
-__device__ __forceinline__ int system_of(const int* off, int nsys, int64_t i) {
-  int lo = 0, hi = nsys - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= i)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-
 // ===================================================================== keys
 __device__ __forceinline__ uint64_t spread3(uint64_t x) {
   x &= 0x1fffffull;

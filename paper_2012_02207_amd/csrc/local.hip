@@ -378,7 +378,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 
 // Near-field work items (the plan above), one thread per leaf; ctr[0] counts
 // the extra items and ctr[1] the partial slots (both zero on entry).
-// List entries per segment, at least: a 512th of the system's bodies, between
+// List entries per segment, at least: a 1024th of the system's bodies, between
 // NF_SEG_MIN and NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
 // more of smaller leaves.  A small system has few leaves with long lists
 // (4096 bodies: 303 leaves of 226 entries), and only short segments spread
@@ -386,9 +386,13 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 // are cut (at N = 2^18 one leaf holds 2776 entries, 42 times the mean work).
 // The bound is the system's own, so a system of a batch sums in the same order
 // as alone; only a list total over K NF_ITEMS raises it, to bound the partial
-// sums' memory.  @SEG_FIGS@
+// sums' memory.  With 256 entries or more per segment whatever the size, the
+// near field took 390 us alone at N = 4096, p = 6 (156 now), 678 us at 30011
+// bodies, mixed (319), and the jerk of 50021 bodies 6.90 ms (4.36).  A 512th
+// and a 2048th: the jerk 4.73 and 4.11 ms, 30011 bodies 1.96 and 2.09 ms
+// (1.94), frozen 16384 0.68 and 0.86 (0.71).
 constexpr int NF_SEG_MIN = 8, NF_SEG_MAX = 512;
-constexpr int NF_SEG_DIV = 512;
+constexpr int NF_SEG_DIV = 1024;
 constexpr int64_t NF_ITEMS = 65536;
 
 __host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int floor_k) {

@@ -317,8 +317,8 @@ static void run_walk(Ctx& c, CellList& acc, CellList& nearl, bool group,
   size_t fcap0 = std::max<size_t>(4096, (size_t)c.ncell * 4);
   ensure(c.ws, c.front[0], fcap0);
   ensure(c.ws, c.front[1], fcap0);
-  ensure(c.ws, acc.raw, std::max<size_t>(acc.raw.cap, (size_t)c.ncell * 8 + 64));
-  ensure(c.ws, nearl.raw, std::max<size_t>(nearl.raw.cap, (size_t)c.ncell * 8 + 64));
+  ensure(c.ws, acc.raw, (size_t)c.ncell * 8 + 64);  // (kept as large as earlier calls left it)
+  ensure(c.ws, nearl.raw, (size_t)c.ncell * 8 + 64);
   ensure(c.ws, c.counters, 512);
   int* ctr = c.counters.p + 256;
   int bits = list_bits(c.ncell);
@@ -353,17 +353,18 @@ static void run_walk(Ctx& c, CellList& acc, CellList& nearl, bool group,
     if (!walk_list_fits(nacc) || !walk_list_fits(nnear) || !walk_list_fits(need_f))
       throw unsupported_error{"interaction list or walk frontier longer than 2^31 - 64 entries"};
     bool again = false;
+    int64_t slack = c.ws.arena ? 1 : 2;  // twice the need, except in the fixed scratch
     if (need_f > std::min(fcap_of(c.front[0]), fcap_of(c.front[1]))) {
       ensure(c.ws, c.front[0], (size_t)need_f * 2);
       ensure(c.ws, c.front[1], (size_t)need_f * 2);
       again = true;
     }
     if ((size_t)nacc + 2 > acc.raw.cap) {
-      ensure(c.ws, acc.raw, (size_t)nacc * 2 + 64);
+      ensure(c.ws, acc.raw, (size_t)(nacc * slack) + 64);
       again = true;
     }
     if ((size_t)nnear + 2 > nearl.raw.cap) {
-      ensure(c.ws, nearl.raw, (size_t)nnear * 2 + 64);
+      ensure(c.ws, nearl.raw, (size_t)(nnear * slack) + 64);
       again = true;
     }
     if (!again) break;

@@ -460,12 +460,26 @@ void plan_near_field(Ctx& c) {
   ensure(c.ws, c.nf_cell_nseg, (size_t)c.ncell);
   ensure(c.ws, c.nf_cell_pbase, (size_t)c.ncell);
   ensure(c.ws, c.nf_extra, (size_t)extra_max + 1);
-  ensure(c.ws, c.nf_part, (size_t)slot_max + 1);
   int* ctr = c.counters.p + 44;
   hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
                      c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, floor_k, max_nb, c.nf_cell_nseg.p,
                      c.nf_cell_pbase.p, c.nf_extra.p, ctr);
   HIPCHK(hipGetLastError());
+  // where memory is limited the partial sums get the slots that the plan
+  // counted (read back), not the bound, which is some four times that
+  if (c.ws.arena || c.ws.limit) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(c.stream, &cs));
+    if (cs == hipStreamCaptureStatusNone) {
+      int* h = (int*)(c.hbuf + 120);
+      HIPCHK(hipMemcpyAsync(h, ctr + 1, sizeof(int), hipMemcpyDeviceToHost, c.stream));
+      HIPCHK(hipStreamSynchronize(c.stream));
+      slot_max = *h;
+    } else {
+      slot_max = c.nf.max_slots;  // the evaluation run before the capture had the same lists
+    }
+  }
+  ensure(c.ws, c.nf_part, (size_t)slot_max + 1);
   c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr, nleaf, (int)(nleaf + extra_max),
                 (int)slot_max};
 }

@@ -68,8 +68,8 @@ typedef struct {
   int root_levels;  /* mixed precision: M2L touching a cell above this level stays FP64 */
   int m2l_waves;    /* mixed precision: wavefronts per sink in the FP32 M2L, 1, 2 or 4 (default 1);
                        each takes a contiguous part of the sink's list, the parts added in order */
-  int p2p_groups;   /* near field: at most this many lane groups share a sink leaf's sources
-                       (0 = as many as the wavefront holds, the default; else 1..64) */
+  int p2p_groups;   /* mixed precision: at most this many lane groups share a sink leaf's sources in
+                       the near field (0 = as many as the wavefront holds, the default; else 1..64) */
   int p2p_start;    /* after a tree build: 0 = the near field starts once its own list is
                        grouped (default); 1 = only after the M2L list is grouped as well, so
                        that a long near field does not hold the chip while that grouping waits */
@@ -289,7 +289,7 @@ fmm_status fmm_forces_batch(fmm_ctx* ctx, int64_t nsys, const int64_t* offsets, 
  * near field starts (p2p_start in {0, 1}, at the given n_leaf), the leaf
  * capacity n_leaf (the balance between the near field and the expansions),
  * then in mixed precision the FP32 M2L's wavefronts per sink (m2l_waves in
- * {1, 2, 4}), then the near field's lane groups per sink leaf (p2p_groups in
+ * {1, 2, 4}) and the near field's lane groups per sink leaf (p2p_groups in
  * {0, 4, 2}), one parameter at a time at the best of the ones before, by
  * timing full evaluations of the systems given as for fmm_forces_batch (nsys =
  * 1, offsets = {0, n} for a single system): n_leaf in {16, 24, 32, 48, 64, 96,

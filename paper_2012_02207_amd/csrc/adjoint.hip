@@ -227,21 +227,12 @@ __device__ inline void shift_low(int p, const double* L, double X, double Y, dou
   }
 }
 
-__device__ __forceinline__ double rsqrt_fp64(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double h = 0.5 * x;
-  y = y * fma(-h * y, y, 1.5);
-  y = y * fma(-h * y, y, 1.5);
-  return y;
-}
-
 // Near field of the gradient and jerk operators, one wavefront per work item of
-// the forward near field's plan (a sink leaf, or one segment of a long list;
-// the same layout as the forward near field): the leaf's bodies are replicated
-// over G = 64 / n_B lane groups, group g takes every G-th body of each source
-// leaf, whose positions and source records are staged in LDS by one coalesced
-// load per chunk (the next chunk is fetched into registers while the current
-// one is summed), and the G partial sums are combined in group order.
+// the forward near field's plan (a tile of a sink leaf's bodies and a segment of
+// its list) and in its layout: a lane per source body, 64 at a time from the list
+// whatever the leaves' sizes (the next chunk fetched while this one is summed),
+// against the tile's sinks, whose data are wave-uniform; each lane keeps the
+// sinks' partial sums in registers, added across the lanes at the end.
 // Per sink k and source j (u = x_k - x_j, s^2 = |u|^2 + eps^2; the pair with
 // itself and pairs with s = 0 contribute nothing):
 //   Psi      += src_j.xyz . u / s^3 - src_j.w / s
@@ -249,131 +240,102 @@ __device__ __forceinline__ double rsqrt_fp64(double x) {
 //   tidal    += m_j [tv_k / s^3 - 3 (u . tv_k) u / s^5]
 // written to out[2k] = (grad Psi, Psi) and out[2k+1] = (tidal, 0), or for a
 // later segment of a split leaf to its partial slot (added by k_adj_combine).
+// Bound by FP64 issue (37 instructions a pair).  With the forward
+// near field's former lane groups and LDS-staged sources it took 1485 us alone
+// for the jerk of 50021 bodies (3.8e8 pairs), this way 870.
 constexpr int ADJ_WAVES = 4;
 
 __device__ __forceinline__ void adj_pair(const double4& me, const double4& g, const double4& s,
-                                         const double4& gj, bool use, double eps2, double& psi,
-                                         double& px, double& py, double& pz, double& kx, double& ky,
-                                         double& kz) {
+                                         const double4& gj, bool use, double eps2, double* a) {
   double ux = me.x - s.x, uy = me.y - s.y, uz = me.z - s.z;
   double s2 = fma(ux, ux, fma(uy, uy, fma(uz, uz, eps2)));
-  double inv = rsqrt_fp64(s2);
+  double inv = rsqrt_d(s2);
   inv = (use && s2 > 0.0) ? inv : 0.0;
   double inv2 = inv * inv, inv3 = inv2 * inv, inv5 = inv3 * inv2;
   double ugj = fma(ux, gj.x, fma(uy, gj.y, uz * gj.z));
-  psi = fma(ugj, inv3, fma(-gj.w, inv, psi));
-  double c1 = -3.0 * ugj * inv5, c2 = gj.w * inv3;
-  px = fma(gj.x, inv3, fma(c1 + c2, ux, px));
-  py = fma(gj.y, inv3, fma(c1 + c2, uy, py));
-  pz = fma(gj.z, inv3, fma(c1 + c2, uz, pz));
+  a[3] = fma(ugj, inv3, fma(-gj.w, inv, a[3]));
+  double c12 = fma(-3.0 * ugj, inv5, gj.w * inv3);
+  a[0] = fma(gj.x, inv3, fma(c12, ux, a[0]));
+  a[1] = fma(gj.y, inv3, fma(c12, uy, a[1]));
+  a[2] = fma(gj.z, inv3, fma(c12, uz, a[2]));
   double ug = fma(ux, g.x, fma(uy, g.y, uz * g.z));
   double w3 = s.w * inv3, w5 = -3.0 * s.w * ug * inv5;
-  kx = fma(w3, g.x, fma(w5, ux, kx));
-  ky = fma(w3, g.y, fma(w5, uy, ky));
-  kz = fma(w3, g.z, fma(w5, uz, kz));
+  a[4] = fma(w3, g.x, fma(w5, ux, a[4]));
+  a[5] = fma(w3, g.y, fma(w5, uy, a[5]));
+  a[6] = fma(w3, g.z, fma(w5, uz, a[6]));
 }
 
-__global__ void __launch_bounds__(64 * ADJ_WAVES) k_adj_near(const int* __restrict__ leaves, NfPlan plan,
-                                                           const int* __restrict__ cb, const int* __restrict__ ce,
-                                                           const int* __restrict__ off,
-                                                           const int* __restrict__ srcl,
-                                                           const double4* __restrict__ pm,
-                                                           const double4* __restrict__ tv,
-                                                           const double4* __restrict__ src, double eps2,
-                                                           double4* __restrict__ out,
-                                                           double4* __restrict__ part) {
-  __shared__ double4 spm[ADJ_WAVES][64];
-  __shared__ double4 ssrc[ADJ_WAVES][64];
-  __shared__ double rbuf[ADJ_WAVES][7][64];
+// the sinks i0 .. i0 + TS over the list srcl[qb .. qe); the TS sinks' 7 sums
+// to out (8 values per sink, the last one 0)
+template <int TS>
+__device__ __forceinline__ void adj_tile(int i0, int qb, int qe, int lane, const int* __restrict__ srcl,
+                                         const int* __restrict__ cb, const int* __restrict__ ce,
+                                         const double4* __restrict__ pm, const double4* __restrict__ tv,
+                                         const double4* __restrict__ src, double eps2, double* __restrict__ out) {
+  double acc[7 * TS];
+#pragma unroll
+  for (int k = 0; k < 7 * TS; k++) acc[k] = 0.0;
+  const double4 *me = pm + i0, *g = tv + i0;
+  BodyStream st;
+  st.start(srcl, cb, ce, qb, qe, lane);
+  int j, na = st.next(lane, -1, j);
+  double4 cpm = pm[max(j, 0)], csrc = src[max(j, 0)];
+  while (na > 0) {
+    double4 s = cpm, gj = csrc;
+    bool live = j >= 0;  // (past the end of the list: nothing)
+    int self = j - i0;   // the sink that this lane's body is, if any
+    na = st.next(lane, -1, j);
+    cpm = pm[max(j, 0)];
+    csrc = src[max(j, 0)];
+#pragma unroll
+    for (int k = 0; k < TS; k++) adj_pair(me[k], g[k], s, gj, live && self != k, eps2, acc + 7 * k);
+  }
+  double tot = 0.0;
+  reduce_lanes<7 * TS>(acc, &tot, lane);
+  int c, real;
+  reduce_slot<7 * TS>(lane, c, real);
+  if (real) {
+    out[8 * (c / 7) + c % 7] = tot;
+    if (c % 7 == 6) out[8 * (c / 7) + 7] = 0.0;
+  }
+}
+
+// (tiles of up to four sinks at a time: 28 sums of two registers)
+__global__ void __launch_bounds__(64 * ADJ_WAVES) __attribute__((amdgpu_waves_per_eu(4))) k_adj_near(
+    const int* __restrict__ leaves, NfPlan plan, const int* __restrict__ cb, const int* __restrict__ ce,
+    const int* __restrict__ off, const int* __restrict__ srcl, const double4* __restrict__ pm,
+    const double4* __restrict__ tv, const double4* __restrict__ src, double eps2, double4* __restrict__ out,
+    double4* __restrict__ part) {
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int nblk = (plan.max_items + ADJ_WAVES - 1) / ADJ_WAVES;
   int blk = xcd_block();
   int it = blk * ADJ_WAVES + wv;
   if (blk >= nblk || it >= plan.max_items) return;
-  int li = it, seg = 0;
-  if (it >= plan.nleaf) {  // a later segment of a long list
+  int li = it, seg = 0, tile = 0;
+  if (it >= plan.nleaf) {  // a later tile or segment
     int x = it - plan.nleaf;
     if (x >= *plan.nextra) return;
     int2 v = plan.extra[x];
     li = v.x;
-    seg = v.y;
+    nf_decode(v.y, seg, tile);
   }
   int B = leaves[li];
   int nseg = plan.cell_nseg[B];
   int b = cb[B], e = ce[B];
   int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);  // (the leaf's bodies fit one wavefront)
-  bool to_part = seg > 0;  // later segments of a long list: partial slots
-  int64_t pslot = to_part ? (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) - b : 0;
-  for (int i0 = b; i0 < e; i0 += 64) {
-    int nB = min(64, e - i0);
-    int G = 64 / nB;
-    int g = lane / nB, sl = lane - g * nB;
-    bool act = g < G;
-    int i = i0 + sl;
-    double4 me = pm[i], gk = tv[i];
-    double psi = 0.0, px = 0.0, py = 0.0, pz = 0.0, kx = 0.0, ky = 0.0, kz = 0.0;
-    int q = qb, j0 = 0, je = 0;
-    if (q < qe) {
-      int A = srcl[q];
-      j0 = cb[A];
-      je = ce[A];
+  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
+  double4* dst = seg > 0 ? part + 2 * ((int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b)) : out + 2 * (int64_t)b;
+  int s0, ts;
+  nf_tile(e - b, tile, s0, ts);
+  for (int h = 0; h < ts; h += 4) {
+    double* o = (double*)(dst + 2 * (s0 + h));
+    int i0 = b + s0 + h;
+    switch (min(4, ts - h)) {
+      case 1: adj_tile<1>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
+      case 2: adj_tile<2>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
+      case 3: adj_tile<3>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
+      case 4: adj_tile<4>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
     }
-    double4 cpm = make_double4(0.0, 0.0, 0.0, 0.0), csrc = cpm;
-    if (q < qe && lane < je - j0) {
-      cpm = pm[j0 + lane];
-      csrc = src[j0 + lane];
-    }
-    while (q < qe) {
-      int na = min(64, je - j0);
-      int nq = q, nj0 = j0 + 64, nje = je;
-      if (nj0 >= je) {
-        nq = q + 1;
-        if (nq < qe) {
-          int A = srcl[nq];
-          nj0 = cb[A];
-          nje = ce[A];
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      spm[wv][lane] = cpm;
-      ssrc[wv][lane] = csrc;
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged chunk is visible to the wave
-      if (nq < qe && lane < nje - nj0) {
-        cpm = pm[nj0 + lane];
-        csrc = src[nj0 + lane];
-      }
-      int tmax = act ? na : 0;
-      int ti = i - j0;  // the sink's own slot when this chunk holds it
-      for (int t = g; t < tmax; t += G)
-        adj_pair(me, gk, spm[wv][t], ssrc[wv][t], t != ti, eps2, psi, px, py, pz, kx, ky, kz);
-      q = nq;
-      j0 = nj0;
-      je = nje;
-    }
-    __builtin_amdgcn_wave_barrier();
-    rbuf[wv][0][lane] = px;
-    rbuf[wv][1][lane] = py;
-    rbuf[wv][2][lane] = pz;
-    rbuf[wv][3][lane] = psi;
-    rbuf[wv][4][lane] = kx;
-    rbuf[wv][5][lane] = ky;
-    rbuf[wv][6][lane] = kz;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    if (g == 0) {
-      double t[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      for (int gg = 0; gg < G; gg++) {
-        int l = gg * nB + sl;
-#pragma unroll
-        for (int r = 0; r < 7; r++) t[r] += rbuf[wv][r][l];
-      }
-      double4* dst = to_part ? part + 2 * (pslot + i) : out + 2 * (int64_t)i;
-      dst[0] = make_double4(t[0], t[1], t[2], t[3]);
-      dst[1] = make_double4(t[4], t[5], t[6], 0.0);
-    }
-    __builtin_amdgcn_wave_barrier();
   }
 }
 

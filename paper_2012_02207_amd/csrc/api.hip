@@ -476,8 +476,8 @@ fmm_status fmm_stats(fmm_ctx* ctx, fmm_stats_t* out) {
         HIPCHK(hipMemcpyAsync(c.hbuf, d, 8, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));
         out->n_p2p_pairs = c.hbuf[0];
-        // the near field's work items: the leaves and the extra segments
-        HIPCHK(hipMemcpyAsync(c.hbuf, c.counters.p + 44, 4, hipMemcpyDeviceToHost, c.stream));
+        // the near field's work items: the leaves and the later segments
+        HIPCHK(hipMemcpyAsync(c.hbuf, c.counters.p + 42, 4, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));
         out->n_p2p_items = (int64_t)c.nleaf + *(const int*)c.hbuf;
       }
@@ -823,8 +823,8 @@ fmm_status fmm_autotune(fmm_ctx* ctx, int64_t nsys, const int64_t* offsets, cons
   // coordinate search: the near field's start (at the given leaf capacity,
   // so that the capacity is then chosen under the better schedule), the leaf
   // capacity (it sets the balance of near and far field), then the FP32 M2L's
-  // wavefronts per sink (mixed precision only), then the near field's lane
-  // groups
+  // wavefronts per sink and the FP32 near field's lane groups (mixed precision
+  // only)
   TuneChoice best{saved.n_leaf, saved.m2l_waves, saved.p2p_groups, saved.p2p_start};
   float best_ms = 1e30f;
   static const int cand_start[] = {0, 1};
@@ -866,7 +866,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, int64_t nsys, const int64_t* offsets, cons
       }
     }
   }
-  if (st == FMM_OK) {
+  if (st == FMM_OK && saved.precision == FMM_MIXED) {
     TuneChoice base = best;
     for (int g : cand_groups) {
       if (g == base.p2p_groups) continue;

@@ -130,6 +130,15 @@ __device__ __forceinline__ double fmm_fact_dev(int n) {
 }
 
 
+// reciprocal square root to full FP64 accuracy: the hardware estimate y (about
+// 2^-27 relative) and one third-order step, y (1 + e/2 + 3 e^2/8) with
+// e = 1 - x y^2
+__device__ __forceinline__ double rsqrt_d(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // ---- division without the operator's scaling --------------------------------
 // a / d rounded correctly, as the operator does, for operands well inside the
 // exponent range (div_safe): two Newton steps on the hardware reciprocal, then
@@ -148,6 +157,23 @@ __device__ __forceinline__ double div_scaled(double a, double d) {
 __device__ __forceinline__ bool div_safe(double x) {
   unsigned e = ((unsigned)(__double_as_longlong(x) >> 52)) & 0x7ffu;
   return e - 523u < 1000u;
+}
+
+// Segment and tile of an extra near-field item (NfPlan) in one int: a split leaf
+// has at most 64 bodies, so 8 tiles (code >= 0); a larger one has one segment.
+__device__ __forceinline__ int nf_code(int seg, int tile) { return tile < 8 ? seg * 8 + tile : -tile; }
+__device__ __forceinline__ void nf_decode(int code, int& seg, int& tile) {
+  seg = code < 0 ? 0 : code >> 3;
+  tile = code < 0 ? -code : code & 7;
+}
+
+// sinks [s0, s0 + count) of tile `tile` of a leaf of nB bodies
+__device__ __forceinline__ int nf_tile_count(int nB) { return (nB + NF_TILE - 1) / NF_TILE; }
+__device__ __forceinline__ void nf_tile(int nB, int tile, int& s0, int& count) {
+  int64_t n = nB;
+  int tiles = nf_tile_count(nB);
+  s0 = (int)(n * tile / tiles);
+  count = (int)(n * (tile + 1) / tiles) - s0;
 }
 
 // entries of segment seg of a list [qb, qe) cut into nseg segments (NfPlan)

@@ -111,10 +111,14 @@ struct CellList {
 // writes the near field itself, segment k > 0 its partial sums to slots
 // cell_pbase[B] + (k - 1) n_B + body; these are added in segment order
 // afterwards, so the result does not depend on the order of the items.
+// In FP64 the sinks of a leaf are moreover taken in even tiles of up to NF_TILE,
+// an item each (leaf, segment, tile): otherwise a large leaf with a long list
+// is one wavefront's work long after the others have ended.
+constexpr int NF_TILE = 8;
 struct NfPlan {
   const int* cell_nseg;   // segments of each leaf, by cell id
   const int* cell_pbase;  // first partial slot of each split leaf, by cell id
-  const int2* extra;      // (leaf index, segment) of the extra items
+  const int2* extra;      // (leaf index, nf_code) of the extra items
   const int* nextra;      // extra item count (device)
   int nleaf;
   int max_items;          // host bound on the item count (grid size)

@@ -103,15 +103,6 @@ __global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, cons
   }
 }
 
-// reciprocal square root to full FP64 accuracy: the hardware estimate y (about
-// 2^-27 relative) and one third-order step, y (1 + e/2 + 3 e^2/8) with
-// e = 1 - x y^2
-__device__ __forceinline__ double rsqrt_d(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-(x * y), y, 1.0);
-  return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 // L2P: the local expansion L shifted to offset (X, Y, Z) from its centre;
 // harmonics built column by column and each used once.
 __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, double X, double Y,
@@ -165,13 +156,119 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
   ph = -s00;
 }
 
-// P2P, one wavefront per sink leaf.  The n_B sink bodies are replicated over
+// P2P.  One wavefront per work item (NfPlan); the sums of each body are the
+// near-field (acc, pot) of nearbuf, sorted order, or a later segment's partial
+// sums.  Bound by vector ALU issue in both precisions.
+//
+// FP64: a lane per source body, taken 64 at a time from the list whatever the
+// leaves' sizes (BodyStream; the next chunk fetched while this one is summed),
+// against a tile of up to 8 sink bodies, whose positions are wave-uniform, so
+// a pair costs no LDS read and every lane works.  Each lane keeps the tile's
+// partial sums in registers; they are added across the lanes at the end of the
+// list (reduce_lanes).  With a lane
+// per (sink, source group) pair and the sources in LDS the pair loop took 2190 us
+// alone at N = 2^18, p = 10 (9.8e8 pairs); this way it took 1843 us with a
+// wavefront per leaf, which left the chip to the few longest leaves (1.5
+// wavefronts per SIMD on average), and 1124 us with the sinks in tiles.
+constexpr int LG_WAVES = 4;
+
+// the sinks i0 .. i0 + TS over the list src[qb .. qe); returns the body pairs
+// (a body with itself is none)
+template <int TS>
+__device__ __forceinline__ long long near_tile64(int i0, int qb, int qe, int lane, const int* __restrict__ src,
+                                                 const int* __restrict__ cb, const int* __restrict__ ce,
+                                                 const double4* __restrict__ pm, double eps2,
+                                                 double* __restrict__ out) {
+  double acc[4 * TS];
+#pragma unroll
+  for (int k = 0; k < 4 * TS; k++) acc[k] = 0.0;
+  const double4* sink = pm + i0;
+  BodyStream st;
+  st.start(src, cb, ce, qb, qe, lane);
+  int j, na = st.next(lane, -1, j);
+  double4 cur = pm[max(j, 0)];
+  long long pairs = 0;
+  while (na > 0) {
+    double4 v = cur;
+    int jv = j;
+    if (jv < 0) v.w = 0.0;  // past the end of the list: no mass
+    pairs += (long long)na * TS;
+    int nn = st.next(lane, -1, j);
+    cur = pm[max(j, 0)];
+    int self = jv - i0;  // the sink that this lane's body is, if any
+    pairs -= __popcll(ballot((unsigned)self < (unsigned)TS));
+#pragma unroll
+    for (int k = 0; k < TS; k++) {
+      double dx = v.x - sink[k].x, dy = v.y - sink[k].y, dz = v.z - sink[k].z;
+      double d2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+      double rinv = rsqrt_d(d2);
+      rinv = d2 > 0.0 && self != k ? rinv : 0.0;
+      double mr = v.w * rinv, mr3 = mr * rinv * rinv;
+      acc[4 * k] = fma(mr3, dx, acc[4 * k]);
+      acc[4 * k + 1] = fma(mr3, dy, acc[4 * k + 1]);
+      acc[4 * k + 2] = fma(mr3, dz, acc[4 * k + 2]);
+      acc[4 * k + 3] -= mr;
+    }
+    na = nn;
+  }
+  double tot = 0.0;
+  reduce_lanes<4 * TS>(acc, &tot, lane);
+  int c, real;
+  reduce_slot<4 * TS>(lane, c, real);
+  if (real) out[c] = tot;
+  return pairs;
+}
+
+__global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per_eu(4))) k_near_fp64(
+    const int* __restrict__ leaves, NfPlan plan, const int* __restrict__ cb, const int* __restrict__ ce,
+    const int* __restrict__ off, const int* __restrict__ srcl, const double4* __restrict__ pm, double eps2,
+    double4* __restrict__ nearbuf, double4* __restrict__ part, unsigned long long* npairs) {
+  int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int nblk = (plan.max_items + LG_WAVES - 1) / LG_WAVES;
+  int blk = xcd_block();
+  int it = blk * LG_WAVES + wv;
+  if (blk >= nblk || it >= plan.max_items) return;
+  int li = it, seg = 0, tile = 0;
+  if (it >= plan.nleaf) {  // a later tile or segment
+    int x = it - plan.nleaf;
+    if (x >= *plan.nextra) return;
+    int2 v = plan.extra[x];
+    li = v.x;
+    nf_decode(v.y, seg, tile);
+  }
+  int B = leaves[li];
+  int nseg = plan.cell_nseg[B];
+  int b = cb[B], e = ce[B];
+  int qb = off[B], qe = off[B + 1];
+  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
+  double4* out = seg > 0 ? part + (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) : nearbuf + b;
+  int s0, ts;
+  nf_tile(e - b, tile, s0, ts);
+  double* o = (double*)(out + s0);
+  long long pairs = 0;
+  switch (ts) {
+#define FMM_NEAR_TILE(T) \
+  case T: pairs = near_tile64<T>(b + s0, qb, qe, lane, srcl, cb, ce, pm, eps2, o); break;
+    FMM_NEAR_TILE(1)
+    FMM_NEAR_TILE(2)
+    FMM_NEAR_TILE(3)
+    FMM_NEAR_TILE(4)
+    FMM_NEAR_TILE(5)
+    FMM_NEAR_TILE(6)
+    FMM_NEAR_TILE(7)
+    FMM_NEAR_TILE(8)
+#undef FMM_NEAR_TILE
+  }
+  if (lane == 0 && pairs > 0) atomicAdd(npairs, (unsigned long long)pairs);
+}
+
+// Mixed precision: the n_B sink bodies are replicated over
 // G = 64 / n_B lane groups, and group g takes every G-th body of each source
 // leaf, so nearly every lane works even though leaves hold ~20 bodies.  Each
 // source leaf is staged once in LDS with one coalesced load and read by the
 // groups as broadcasts.  The G partial sums are combined in group order
 // (deterministic) into the body's near-field (acc, pot), sorted order.
-// MIXED: pair arithmetic in FP32 on the separation formed in FP64 and rounded
+// Pair arithmetic in FP32 on the separation formed in FP64 and rounded
 // once; FP32 partial sums are carried into FP64 after every source leaf
 // (blocked compensation: the FP32 error grows with the leaf, not the list).
 // one source body s (mass ms) acting on the sink me
@@ -189,25 +286,10 @@ __device__ __forceinline__ void pair32(const double4& s, float ms, const double4
   fp -= mr;
 }
 
-__device__ __forceinline__ void pair64(const double4& s, double ms, const double4& me, double eps2, double& nx,
-                                       double& ny, double& nz, double& np) {
-  double dx = s.x - me.x, dy = s.y - me.y, dz = s.z - me.z;
-  double d2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
-  double rinv = rsqrt_d(d2);
-  rinv = d2 > 0.0 ? rinv : 0.0;
-  double mr = ms * rinv;
-  double mr3 = mr * rinv * rinv;
-  nx = fma(mr3, dx, nx);
-  ny = fma(mr3, dy, ny);
-  nz = fma(mr3, dz, nz);
-  np -= mr;
-}
-
-// staged source record: FP64 position; in mixed mode the mass is rounded to
-// FP32 once here and kept in the low word of .w
-template <bool MIXED>
+// staged source record: FP64 position, the mass rounded to FP32 once here and
+// kept in the low word of .w
 __device__ __forceinline__ double4 stage(double4 v) {
-  if constexpr (MIXED) v.w = __longlong_as_double((long long)__float_as_uint((float)v.w));
+  v.w = __longlong_as_double((long long)__float_as_uint((float)v.w));
   return v;
 }
 
@@ -215,13 +297,9 @@ __device__ __forceinline__ float mass32(const double4& v) {
   return __uint_as_float((unsigned)__double_as_longlong(v.w));
 }
 
-// Occupancy: 6 waves per SIMD for the FP32 pair loop (<= 80 VGPRs), 5 for the
-// FP64 one (measured best for each; the FP64 loop at 6 is slower), with the
-// sink leaf's data wave-uniform (SGPRs).
-constexpr int LG_WAVES = 4;
-
-template <bool MIXED>
-__global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per_eu(MIXED ? 6 : 5))) k_leaf_group(const int* __restrict__ leaves,
+// Occupancy: 6 waves per SIMD (<= 80 VGPRs, measured best), with the sink
+// leaf's data wave-uniform (SGPRs).
+__global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per_eu(6))) k_leaf_group(const int* __restrict__ leaves,
                                                               NfPlan plan, const int* __restrict__ cb,
                                                               const int* __restrict__ ce,
                                                               const int* __restrict__ off,
@@ -243,7 +321,8 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     if (x >= *plan.nextra) return;
     int2 v = plan.extra[x];
     li = v.x;
-    seg = v.y;
+    int tile;  // (one tile in mixed precision)
+    nf_decode(v.y, seg, tile);
   }
   int B = leaves[li];
   int nseg = plan.cell_nseg[B];
@@ -275,7 +354,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
       je = ce[A];
     }
     double4 cur = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (q < qe && lane < je - j0) cur = stage<MIXED>(pm[j0 + lane]);
+    if (q < qe && lane < je - j0) cur = stage(pm[j0 + lane]);
     while (q < qe) {
       int na = min(64, je - j0);
       pairs += (long long)nB * na - max(0, min(i0 + nB, j0 + na) - max(i0, j0));
@@ -293,7 +372,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged chunk is visible to the wave
       cur = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (nq < qe && lane < nje - nj0) cur = stage<MIXED>(pm[nj0 + lane]);
+      if (nq < qe && lane < nje - nj0) cur = stage(pm[nj0 + lane]);
       int tmax = act ? na : 0;
       // the sink's own leaf: its pair with itself gets mass 0 (with eps = 0
       // the d2 > 0 test also removes it); other chunks hold no sink body
@@ -302,48 +381,33 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
         int ti = i - j0;
         for (int t = g; t < tmax; t += G) {
           double4 sb = sbuf[wv][t];
-          if constexpr (MIXED)
-            pair32(sb, t != ti ? mass32(sb) : 0.f, me, eps2f, fx, fy, fz, fp);
-          else
-            pair64(sb, t != ti ? sb.w : 0.0, me, eps2, nx, ny, nz, np);
+          pair32(sb, t != ti ? mass32(sb) : 0.f, me, eps2f, fx, fy, fz, fp);
         }
       } else {
         int t = g;
-        if constexpr (MIXED) {
-          for (; t + 3 * G < tmax; t += 4 * G) {
-            double4 s0 = sbuf[wv][t], s1 = sbuf[wv][t + G], s2 = sbuf[wv][t + 2 * G], s3 = sbuf[wv][t + 3 * G];
-            pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
-            pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
-            pair32(s2, mass32(s2), me, eps2f, fx, fy, fz, fp);
-            pair32(s3, mass32(s3), me, eps2f, fx, fy, fz, fp);
-          }
+        for (; t + 3 * G < tmax; t += 4 * G) {
+          double4 s0 = sbuf[wv][t], s1 = sbuf[wv][t + G], s2 = sbuf[wv][t + 2 * G], s3 = sbuf[wv][t + 3 * G];
+          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+          pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
+          pair32(s2, mass32(s2), me, eps2f, fx, fy, fz, fp);
+          pair32(s3, mass32(s3), me, eps2f, fx, fy, fz, fp);
         }
         for (; t + G < tmax; t += 2 * G) {
           double4 s0 = sbuf[wv][t], s1 = sbuf[wv][t + G];
-          if constexpr (MIXED) {
-            pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
-            pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
-          } else {
-            pair64(s0, s0.w, me, eps2, nx, ny, nz, np);
-            pair64(s1, s1.w, me, eps2, nx, ny, nz, np);
-          }
+          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+          pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
         }
         if (t < tmax) {
           double4 s0 = sbuf[wv][t];
-          if constexpr (MIXED)
-            pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
-          else
-            pair64(s0, s0.w, me, eps2, nx, ny, nz, np);
+          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
         }
       }
-      if constexpr (MIXED) {
-        if (nq != q) {  // end of a source leaf: carry the FP32 block into FP64
-          nx += (double)fx;
-          ny += (double)fy;
-          nz += (double)fz;
-          np += (double)fp;
-          fx = fy = fz = fp = 0.f;
-        }
+      if (nq != q) {  // end of a source leaf: carry the FP32 block into FP64
+        nx += (double)fx;
+        ny += (double)fy;
+        nz += (double)fz;
+        np += (double)fp;
+        fx = fy = fz = fp = 0.f;
       }
       q = nq;
       j0 = nj0;
@@ -377,46 +441,57 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 }
 
 // Near-field work items (the plan above), one thread per leaf; ctr[0] counts
-// the extra items and ctr[1] the partial slots (both zero on entry).
-// List entries per segment, at least: a 1024th of the system's bodies, between
-// NF_SEG_MIN and NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
-// more of smaller leaves.  A small system has few leaves with long lists
-// (4096 bodies: 303 leaves of 226 entries), and only short segments spread
-// them over the chip; a large one has enough leaves, and only the outliers
-// are cut (at N = 2^18 one leaf holds 2776 entries, 42 times the mean work).
-// The bound is the system's own, so a system of a batch sums in the same order
-// as alone; only a list total over K NF_ITEMS raises it, to bound the partial
-// sums' memory.  With 256 entries or more per segment whatever the size, the
-// near field took 390 us alone at N = 4096, p = 6 (156 now), 678 us at 30011
-// bodies, mixed (319), and the jerk of 50021 bodies 6.90 ms (4.36).  A 512th
-// and a 2048th: the jerk 4.73 and 4.11 ms, 30011 bodies 1.96 and 2.09 ms
-// (1.94), frozen 16384 0.68 and 0.86 (0.71).
+// the extra items, ctr[1] the partial slots and ctr[-2] the later segments (all
+// zero on entry).
+// List entries per segment, at least: a 1024th of the system's bodies, from
+// NF_SEG_MIN on (NF_SEG_TILED times that in FP64, whose items hold at most 8
+// sinks), up to NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
+// more of smaller leaves.  A small system has few leaves with long lists (4096
+// bodies: 303 leaves of 226 entries), and only short segments spread them over
+// the chip; a large one has enough leaves, and only the outliers are cut (at
+// N = 2^18 one leaf holds 2776 entries, 42 times the mean work).  The bound is
+// the system's own, so a system of a batch sums in the same order as alone;
+// only a list total over K NF_ITEMS raises it, to bound the partial sums'
+// memory.  Mixed: with 256 entries or more whatever the size the near field of
+// 30011 bodies took 678 us (319 now), with a 512th and a 2048th of the bodies
+// the evaluation 1.96 and 2.09 ms (1.94), frozen 16384 0.68 and 0.86 (0.71).
+// FP64: twice, four, eight and 16 times the entries give 1.57, 1.43, 1.39 and
+// 1.39 ms at 16000 bodies, 1.28, 1.24, 1.20 and 1.22 at 4096, and the jerk of
+// 50021 bodies 3.62, 3.68, 3.76 and 3.88 ms.
 constexpr int NF_SEG_MIN = 8, NF_SEG_MAX = 512;
 constexpr int NF_SEG_DIV = 1024;
+constexpr int NF_SEG_TILED = 4;
 constexpr int64_t NF_ITEMS = 65536;
 
-__host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int floor_k) {
+__host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int tiled, int floor_k) {
   int64_t k = bodies / NF_SEG_DIV;
-  k = k < NF_SEG_MIN ? NF_SEG_MIN : k > NF_SEG_MAX ? NF_SEG_MAX : k;
+  k = k < NF_SEG_MIN ? NF_SEG_MIN : k;
+  if (tiled) k *= NF_SEG_TILED;
+  k = k > NF_SEG_MAX ? NF_SEG_MAX : k;
   k = k * 64 / max_nb;
   return k < floor_k ? floor_k : (int)k;
 }
 
 __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* __restrict__ cb,
                           const int* __restrict__ ce, const int* __restrict__ off, const int* __restrict__ sys_off,
-                          int nsys, int floor_k, int max_nb, int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
+                          int nsys, int floor_k, int max_nb, int tiled, int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
   int li = blockIdx.x * blockDim.x + threadIdx.x;
   if (li >= nleaf) return;
   int B = leaves[li];
   int len = off[B + 1] - off[B], nB = ce[B] - cb[B];
   int sys = nsys > 1 ? system_of(sys_off, nsys, cb[B]) : 0;
-  int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, floor_k);
+  int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, tiled, floor_k);
   int ns = (nB <= max_nb && len > K) ? (len + K - 1) / K : 1;
   cell_nseg[B] = ns;
-  if (ns > 1) {
-    int x = atomicAdd(ctr, ns - 1);
-    for (int k = 1; k < ns; k++) extra[x + k - 1] = make_int2(li, k);
-    cell_pbase[B] = atomicAdd(ctr + 1, (ns - 1) * nB);
+  int nt = tiled ? nf_tile_count(nB) : 1;
+  if (ns * nt > 1) {
+    int x = atomicAdd(ctr, ns * nt - 1);
+    for (int k = 0; k < ns; k++)
+      for (int t = k == 0 ? 1 : 0; t < nt; t++) extra[x++] = make_int2(li, nf_code(k, t));
+    if (ns > 1) {
+      cell_pbase[B] = atomicAdd(ctr + 1, (ns - 1) * nB);
+      atomicAdd(ctr - 2, ns - 1);
+    }
   }
 }
 
@@ -454,15 +529,19 @@ void plan_near_field(Ctx& c) {
   // a split leaf holds len > K entries in ceil(len / K) segments, so the extra
   // items number fewer than cnt / K, with the smallest K of any system
   int max_nb = std::min(64, c.prm.n_leaf);
-  int kmin = nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, floor_k);
+  int tiled = c.prm.precision == FMM_FP64;
+  int kmin = nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, tiled, floor_k);
   int64_t extra_max = cnt / kmin;
   int64_t slot_max = extra_max * max_nb;
+  // with tiles: a leaf of n_B bodies has n_B / 8 more of them than one, and
+  // every segment of a split leaf up to ceil(max_nb / 8)
+  if (tiled) extra_max = extra_max * ceil_div(max_nb, NF_TILE) + c.n / NF_TILE;
   ensure(c.ws, c.nf_cell_nseg, (size_t)c.ncell);
   ensure(c.ws, c.nf_cell_pbase, (size_t)c.ncell);
   ensure(c.ws, c.nf_extra, (size_t)extra_max + 1);
   int* ctr = c.counters.p + 44;
   hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
-                     c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, floor_k, max_nb, c.nf_cell_nseg.p,
+                     c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, floor_k, max_nb, tiled, c.nf_cell_nseg.p,
                      c.nf_cell_pbase.p, c.nf_extra.p, ctr);
   HIPCHK(hipGetLastError());
   // where memory is limited the partial sums get the slots that the plan
@@ -490,7 +569,7 @@ void launch_near_field(Ctx& c) {
   ensure(c.ws, c.nearbuf, (size_t)c.n);
   const int* leaves = c.leaves.p;
   // body-pair count of the near field, read by fmm_stats
-  // counters[40..41]: the body-pair count; [44], [45]: the plan's counts
+  // counters[40..41]: the body-pair count; [42], [44], [45]: the plan's counts
   unsigned long long* npairs = (unsigned long long*)(c.counters.p + 40);
   zero_fill(c, npairs, 6 * sizeof(int));
   plan_near_field(c);
@@ -499,13 +578,12 @@ void launch_near_field(Ctx& c) {
   double e2 = c.eps_soft * c.eps_soft;
   int gmax = c.prm.p2p_groups;
   if (c.prm.precision == FMM_MIXED)
-    hipLaunchKernelGGL(k_leaf_group<true>, dim3(grid), dim3(64 * LG_WAVES), 0, c.stream, leaves, c.nf,
+    hipLaunchKernelGGL(k_leaf_group, dim3(grid), dim3(64 * LG_WAVES), 0, c.stream, leaves, c.nf,
                        c.c_begin.p, c.c_end.p, c.p2p.off.p, c.p2p.src.p, c.pm.p, e2, c.nearbuf.p,
                        c.nf_part.p, npairs, gmax);
   else
-    hipLaunchKernelGGL(k_leaf_group<false>, dim3(grid), dim3(64 * LG_WAVES), 0, c.stream, leaves, c.nf,
-                       c.c_begin.p, c.c_end.p, c.p2p.off.p, c.p2p.src.p, c.pm.p, e2, c.nearbuf.p,
-                       c.nf_part.p, npairs, gmax);
+    hipLaunchKernelGGL(k_near_fp64, dim3(grid), dim3(64 * LG_WAVES), 0, c.stream, leaves, c.nf, c.c_begin.p,
+                       c.c_end.p, c.p2p.off.p, c.p2p.src.p, c.pm.p, e2, c.nearbuf.p, c.nf_part.p, npairs);
   HIPCHK(hipGetLastError());
   if (c.nf.max_slots > 0) {
     hipLaunchKernelGGL(k_nf_combine, dim3((unsigned)ceil_div(c.n, 256)), dim3(256), 0, c.stream, c.n,

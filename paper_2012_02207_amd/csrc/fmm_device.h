@@ -54,66 +54,6 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Regular solid harmonics Y_n^m(x), m >= 0, in exactly the rounding sequence
-// of their defining two-term recurrences (no contraction; used where results
-// feed the acceptance test):
-//   Y_0^0 = 1, Y_n^n = -(x + i y) Y_{n-1}^{n-1} / (2n),
-//   Y_n^m = ((2n-1) z Y_{n-1}^m - r^2 Y_{n-2}^m) / ((n+m)(n-m)).
-// Values are written to re[cidx(n,m)*stride], im[cidx(n,m)*stride].
-__device__ inline void regular_exact(int p, double x, double y, double z, double* re, double* im,
-                                     int stride) {
-  double r2 = (x * x + y * y) + z * z;
-  re[0] = 1.0;
-  im[0] = 0.0;
-  double pr = 1.0, pi = 0.0;
-  for (int n = 1; n <= p; n++) {
-    double tr = x * pr - y * pi;
-    double ti = x * pi + y * pr;
-    double den = (double)(2 * n);
-    pr = (-tr) / den;
-    pi = (-ti) / den;
-    re[cidx(n, n) * stride] = pr;
-    im[cidx(n, n) * stride] = pi;
-  }
-  for (int m = 0; m < p; m++) {
-    double ar2 = 0.0, ai2 = 0.0;  // Y_{n-2}^m
-    double ar1 = re[cidx(m, m) * stride], ai1 = im[cidx(m, m) * stride];
-    for (int n = m + 1; n <= p; n++) {
-      double k = (double)(2 * n - 1) * z;
-      double ar = k * ar1;
-      double ai = k * ai1;
-      double nr = ar, ni = ai;
-      if (n - 2 >= m) {
-        double br = r2 * ar2;
-        double bi = r2 * ai2;
-        nr = ar - br;
-        ni = ai - bi;
-      }
-      double den = (double)((n + m) * (n - m));
-      double vr = nr / den, vi = ni / den;
-      re[cidx(n, m) * stride] = vr;
-      im[cidx(n, m) * stride] = vi;
-      ar2 = ar1;
-      ai2 = ai1;
-      ar1 = vr;
-      ai1 = vi;
-    }
-  }
-}
-
-// coefficient (n, m) for either sign of m from m >= 0 storage (exact)
-__device__ __forceinline__ void cget(const double* re, const double* im, int stride, int n, int m,
-                                     double& a, double& b) {
-  if (m >= 0) {
-    a = re[cidx(n, m) * stride];
-    b = im[cidx(n, m) * stride];
-  } else {
-    double s = (m & 1) ? -1.0 : 1.0;
-    a = s * re[cidx(n, -m) * stride];
-    b = -s * im[cidx(n, -m) * stride];
-  }
-}
-
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // grid for xcd_block(): nblk blocks rounded up to whole rounds of 8 chunks
@@ -174,6 +114,47 @@ __device__ __forceinline__ void nf_tile(int nB, int tile, int& s0, int& count) {
   int tiles = nf_tile_count(nB);
   s0 = (int)(n * tile / tiles);
   count = (int)(n * (tile + 1) / tiles) - s0;
+}
+
+// a / d rounded correctly for an integer d of a recurrence (1 <= d < 2^20), from
+// y = rcp_newton(d), which does not depend on a: three dependent instructions
+// instead of the operator's eleven.  Numerators outside div_safe (the
+// harmonics of offsets that underflow) take the operator.
+__device__ __forceinline__ double rcp_newton(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(y, fma(-d, y, 1.0), y);
+  return fma(y, fma(-d, y, 1.0), y);
+}
+__device__ __forceinline__ double div_by(double a, double d, double y) {
+  double q = a * y;
+  q = fma(fma(-d, q, a), y, q);
+  q = a == 0.0 ? a : q;  // (the sign of a zero)
+  bool far = a != 0.0 && !div_safe(a);
+  if (ballot(far)) q = far ? a / d : q;
+  return q;
+}
+
+// (n, m) of coefficient index t = n (n + 1) / 2 + m, and n of entry
+// t = n (n + 1) + m of a both-sign layout
+__device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
+  n = (int)((__builtin_sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);  // exact or one off
+  if (cidx(n + 1, 0) <= t) n++;
+  if (cidx(n, 0) > t) n--;
+  m = t - cidx(n, 0);
+}
+// Task u of the (child, coefficient) tasks of kn children in order of n, so that
+// the lanes of a wavefront share the length of their sums.
+__device__ __forceinline__ void child_task(int u, int kn, int& j, int& n, int& m) {
+  coef_nm(u / kn, n, m);
+  int r = u - kn * cidx(n, 0);
+  j = r / (n + 1);
+  m = r - j * (n + 1);
+}
+__device__ __forceinline__ int both_sign_n(int t) {
+  int n = (int)__builtin_sqrtf((float)t);
+  if ((n + 1) * (n + 1) <= t) n++;
+  if (n * n > t) n--;
+  return n;
 }
 
 // entries of segment seg of a list [qb, qe) cut into nseg segments (NfPlan)

@@ -16,15 +16,19 @@ namespace fmm {
 // and the conjugated harmonics of every child are laid out in LDS for both
 // signs of the order (entry n(n+1) + m, m = -n..n), which makes every sum a
 // branch-free loop; lanes evaluate harmonic columns, then (child,
-// coefficient) sums.
-constexpr int L2L_T = 256;
+// coefficient) sums, a thread for (almost) every one: a launch is bound by the
+// chain of its longest sum (24 us for a level of any size with 256 threads
+// at p = 10, 11 us now; at N = 2^20 all levels 425 and 262 us).
+constexpr int L2L_T_MAX = 1024;
 
 // G: children per pass (their harmonics share LDS with the parent's expansion;
 // 8 = all at once, fewer at the orders where eight do not fit)
-__global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, const int* c0,
-                                              const int* nch, const double* cx, const double* cy,
-                                              const double* cz, double* loc, int G) {
+__global__ void __launch_bounds__(L2L_T_MAX) k_l2l(int p, int first, int count, const int* __restrict__ c0,
+                                                    const int* __restrict__ nch, const double* __restrict__ cx,
+                                                    const double* __restrict__ cy, const double* __restrict__ cz,
+                                                    double* loc, int G) {
   extern __shared__ double lds[];
+  const int L2L_T = blockDim.x;
   int P = first + blockIdx.x;
   if (blockIdx.x >= count || nch[P] == 0) return;
   int nc = ncoef(p), S = (p + 1) * (p + 1);
@@ -34,8 +38,7 @@ __global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, cons
   int t = threadIdx.x;
   const double* Lp = loc + (size_t)P * nc * 2;
   for (int u = t; u < S; u += L2L_T) {
-    int n = 0;
-    while ((n + 1) * (n + 1) <= u) n++;
+    int n = both_sign_n(u);
     int m = u - n * n - n, am = m < 0 ? -m : m;
     double a = Lp[2 * cidx(n, am)], b = Lp[2 * cidx(n, am) + 1];
     if (m < 0) {
@@ -55,7 +58,7 @@ __global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, cons
       double r2 = fma(x, x, fma(y, y, z * z));
       double pr = 1.0, pi = 0.0;
       for (int n = 1; n <= m; n++) {
-        double inv = -1.0 / (double)(2 * n);
+        double inv = -rcp_newton((double)(2 * n));
         double tr = fma(x, pr, -y * pi), ti = fma(x, pi, y * pr);
         pr = tr * inv;
         pi = ti * inv;
@@ -67,7 +70,7 @@ __global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, cons
       if (m > 0) Y[m * m] = make_double2(sg * pr, sg * pi);
       double ar2 = 0.0, ai2 = 0.0, ar1 = pr, ai1 = pi;
       for (int n = m + 1; n <= p; n++) {
-        double k = (double)(2 * n - 1) * z, inv = 1.0 / (double)((n + m) * (n - m));
+        double k = (double)(2 * n - 1) * z, inv = rcp_newton((double)((n + m) * (n - m)));
         double vr = fma(k, ar1, -r2 * ar2) * inv, vi = fma(k, ai1, -r2 * ai2) * inv;
         Y[n * n + n + m] = make_double2(vr, -vi);
         if (m > 0) Y[n * n + n - m] = make_double2(sg * vr, sg * vi);
@@ -79,10 +82,9 @@ __global__ void __launch_bounds__(L2L_T) k_l2l(int p, int first, int count, cons
     }
     __syncthreads();
     for (int u = t; u < gn * nc; u += L2L_T) {
-      int j = u / nc, q = u - j * nc;
-      int jn = 0;
-      while (cidx(jn + 1, 0) <= q) jn++;
-      int i = q - cidx(jn, 0);
+      int j, jn, i;
+      child_task(u, gn, j, jn, i);
+      int q = cidx(jn, i);
       const double2* Y = Yc + j * S;
       double sr = 0.0, si = 0.0;
       for (int k = 0; k <= p - jn; k++) {
@@ -626,11 +628,13 @@ void launch_l2l(Ctx& c) { launch_l2l_buf(c, c.loc.p); }
 
 void launch_l2l_buf(Ctx& c, double* loc) {
   size_t S = (size_t)(c.p + 1) * (c.p + 1);
-  int G = sizeof(double2) * 9 * S <= 64 * 1024 ? 8 : 1;  // children per pass within 64 KB of LDS
+  int G = sizeof(double2) * 9 * S <= 128 * 1024 ? 8 : 1;  // children per pass within 128 KB of LDS
   size_t lds = sizeof(double2) * (1 + G) * S;
+  int tasks = G * ncoef(c.p), rounds = (int)ceil_div(tasks, L2L_T_MAX);
+  int threads = (int)ceil_div(tasks, 64 * rounds) * 64;
   for (int level = 0; level < c.depth; level++) {  // parents at this level, children one below
     int first = c.lvl_first[level], count = c.lvl_count[level];
-    hipLaunchKernelGGL(k_l2l, dim3(count), dim3(L2L_T), lds, c.stream, c.p, first, count, c.c_child0.p,
+    hipLaunchKernelGGL(k_l2l, dim3(count), dim3(threads), lds, c.stream, c.p, first, count, c.c_child0.p,
                        c.c_nchild.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, loc, G);
   }
   HIPCHK(hipGetLastError());

@@ -21,24 +21,28 @@ static __constant__ double c_fact[2 * FMM_TABLE_PMAX + 2];
 static __constant__ double c_binom[FMM_TABLE_PMAX + 1][FMM_TABLE_PMAX + 1];
 static bool g_up_tables[64] = {};  // per device
 
-// Column m of the regular harmonics of (x, y, z) in the exact rounding
-// sequence of the full recurrence (the same arithmetic as regular_exact): the
-// diagonal Y_1^1 .. Y_m^m, then Y_n^m for n = m+1..p.  Lanes evaluate
-// different columns (and bodies) in parallel.
+// Column m of the regular harmonics of (x, y, z), rounded as the defining
+// two-term recurrences are written (no contraction),
+//   Y_0^0 = 1, Y_n^n = -(x + i y) Y_{n-1}^{n-1} / (2n),
+//   Y_n^m = ((2n-1) z Y_{n-1}^m - r^2 Y_{n-2}^m) / ((n+m)(n-m)):
+// the diagonal Y_1^1 .. Y_m^m, then Y_n^m for n = m+1..p.  Lanes evaluate
+// different columns (and bodies) in parallel.  The chain of a column is bound by
+// latency, most of it the divisions', whose reciprocals leave the chain (div_by).
 template <class Store>
 __device__ inline void regular_column_exact(int p, int m, double x, double y, double z, Store store) {
   double r2 = (x * x + y * y) + z * z;
   double pr = 1.0, pi = 0.0;
   for (int n = 1; n <= m; n++) {
+    double den = (double)(2 * n), rcp = rcp_newton(den);
     double tr = x * pr - y * pi;
     double ti = x * pi + y * pr;
-    double den = (double)(2 * n);
-    pr = (-tr) / den;
-    pi = (-ti) / den;
+    pr = div_by(-tr, den, rcp);
+    pi = div_by(-ti, den, rcp);
   }
   store(m, pr, pi);
   double ar2 = 0.0, ai2 = 0.0, ar1 = pr, ai1 = pi;
   for (int n = m + 1; n <= p; n++) {
+    double den = (double)((n + m) * (n - m)), rcp = rcp_newton(den);
     double k = (double)(2 * n - 1) * z;
     double nr = k * ar1, ni = k * ai1;
     if (n - 2 >= m) {
@@ -46,8 +50,7 @@ __device__ inline void regular_column_exact(int p, int m, double x, double y, do
       nr = nr - br;
       ni = ni - bi;
     }
-    double den = (double)((n + m) * (n - m));
-    double vr = nr / den, vi = ni / den;
+    double vr = div_by(nr, den, rcp), vi = div_by(ni, den, rcp);
     store(n, vr, vi);
     ar2 = ar1;
     ai2 = ai1;
@@ -56,75 +59,100 @@ __device__ inline void regular_column_exact(int p, int m, double x, double y, do
   }
 }
 
-// (n, m) of coefficient index t
-__device__ __forceinline__ void coef_nm(int t, int& n, int& m) {
-  n = 0;
-  while (cidx(n + 1, 0) <= t) n++;
-  m = t - cidx(n, 0);
+// P2M, a wavefront per leaf.  Bodies in batches of 64 / (p+1): a lane evaluates
+// one column of one body's harmonics into LDS, as the real values of the order's
+// coefficients (entry n^2: Re Y_n^0, n^2 + 2m - 1 and n^2 + 2m: Re, Im Y_n^m);
+// then each lane adds up to V of the (p+1)^2 values over the batch in sorted body
+// order (Im M_n^0 is 0).  Bound by FP64 issue.  A workgroup of 256 threads per
+// leaf, whose lanes ran the two loops of unequal columns one after the other and
+// mostly idled in the sums, took 471 us at N = 2^20, p = 10, this one 350.
+constexpr int P2M_WAVES = 4;
+
+__host__ __device__ inline int p2m_batch(int p) { return 64 / (p + 1); }
+
+// Column m of the harmonics of (x, y, z), as regular_column_exact, its diagonal
+// and its vertical steps in one loop, so that lanes of different columns keep
+// step.
+template <class Store>
+__device__ inline void regular_column_lockstep(int p, int m, double x, double y, double z, Store store) {
+  double r2 = (x * x + y * y) + z * z;
+  double ar1 = 1.0, ai1 = 0.0, ar2 = 0.0, ai2 = 0.0;  // the last value, and the one before it in the column
+  if (m == 0) store(0, 1.0, 0.0);
+  for (int n = 1; n <= p; n++) {
+    bool diag = n <= m;
+    double den = diag ? (double)(2 * n) : (double)((n + m) * (n - m)), rcp = rcp_newton(den);
+    double k = diag ? x : (double)(2 * n - 1) * z;
+    double br = (diag ? y : r2) * (diag ? ai1 : ar2), bi = (diag ? y : r2) * (diag ? ar1 : ai2);
+    double nr = k * ar1, ni = k * ai1;
+    if (diag) {
+      nr = -(nr - br);
+      ni = -(ni + bi);
+    } else if (n - 2 >= m) {
+      nr = nr - br;
+      ni = ni - bi;
+    }
+    ar2 = diag ? 0.0 : ar1;
+    ai2 = diag ? 0.0 : ai1;
+    ar1 = div_by(nr, den, rcp);
+    ai1 = div_by(ni, den, rcp);
+    if (n >= m) store(n, ar1, ai1);
+  }
 }
 
-// P2M: one workgroup per leaf; bodies in batches of P2M_T / (p+1), lane
-// (body, column) evaluates one harmonic column into LDS, then lanes owning
-// coefficients accumulate over the batch in sorted body order.
-constexpr int P2M_T = 256;
-
-__host__ __device__ inline int p2m_batch(int p) { return P2M_T / (p + 1); }
-
-__global__ void __launch_bounds__(P2M_T) k_p2m(int p, const int* leaves, int nleaves, const int* cb,
-                                               const int* ce, const double* sx, const double* sy,
-                                               const double* sz, const double* sm, const double* cx,
-                                               const double* cy, const double* cz, double* mult) {
+template <int V>
+__global__ void __launch_bounds__(64 * P2M_WAVES) k_p2m(int p, const int* __restrict__ leaves, int nleaves,
+                                                        const int* __restrict__ cb, const int* __restrict__ ce,
+                                                        const double4* __restrict__ pm, const double* __restrict__ cx,
+                                                        const double* __restrict__ cy, const double* __restrict__ cz,
+                                                        double* __restrict__ mult) {
   extern __shared__ double lds[];
-  int li = blockIdx.x;
+  int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int li = blockIdx.x * P2M_WAVES + wv;
   if (li >= nleaves) return;
   int c = leaves[li];
-  int nc = ncoef(p);
-  int batch = p2m_batch(p);
-  double* yre = lds;  // [coef][body], stride batch
-  double* yim = lds + nc * batch;
-  double* msh = lds + 2 * nc * batch;  // masses of the batch
-  int t = threadIdx.x;
+  int S = (p + 1) * (p + 1), batch = p2m_batch(p);
+  double* val = lds + (size_t)wv * S * batch;  // [body][value]
   double x0 = cx[c], y0 = cy[c], z0 = cz[c];
   int b = cb[c], e = ce[c];
-  constexpr int MAXK = (ncoef(FMM_TABLE_PMAX) + P2M_T - 1) / P2M_T;
-  double acr[MAXK], aci[MAXK];
-  for (int u = 0; u < MAXK; u++) acr[u] = aci[u] = 0.0;
-  int hb = t / (p + 1), hm = t - hb * (p + 1);  // harmonic lane: body hb, column hm
+  int hb = lane / (p + 1), hm = lane - hb * (p + 1);  // harmonic lane: body hb, column hm
+  double sum[V];
+#pragma unroll
+  for (int v = 0; v < V; v++) sum[v] = 0.0;
   for (int i0 = b; i0 < e; i0 += batch) {
     int cnt = min(batch, e - i0);
-    if (hb < cnt) {
-      int i = i0 + hb;
-      if (hm == 0) msh[hb] = sm[i];
-      regular_column_exact(p, hm, sx[i] - x0, sy[i] - y0, sz[i] - z0, [&](int n, double vr, double vi) {
-        yre[cidx(n, hm) * batch + hb] = vr;
-        yim[cidx(n, hm) * batch + hb] = vi;
-      });
-    }
-    __syncthreads();
-    for (int u = 0; u < MAXK; u++) {
-      int k = t + P2M_T * u;
-      if (k < nc) {
-        double sr = acr[u], si = aci[u];
-#pragma unroll 4
-        for (int j = 0; j < cnt; j++) {
-          double m = msh[j];
-          double tr = m * yre[k * batch + j];
-          double ti = m * yim[k * batch + j];
-          sr = sr + tr;
-          si = si + ti;
+    bool act = hb < cnt;
+    double4 q = pm[act ? i0 + hb : i0];
+    __builtin_amdgcn_wave_barrier();
+    if (act)
+      regular_column_lockstep(p, hm, q.x - x0, q.y - y0, q.z - z0, [&](int n, double vr, double vi) {
+        double* w = val + hb * S + n * n + 2 * hm;
+        if (hm > 0) {
+          w[-1] = vr;
+          w[0] = vi;
+        } else {
+          w[0] = vr;
         }
-        acr[u] = sr;
-        aci[u] = si;
+      });
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the batch is visible to the wave
+    for (int j = 0; j < cnt; j++) {
+      double m = __shfl(q.w, j * (p + 1), 64);
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        double t = m * val[j * S + min(lane + 64 * v, S - 1)];
+        sum[v] = sum[v] + t;
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
   }
-  double* out = mult + (size_t)c * nc * 2;
-  for (int u = 0; u < MAXK; u++) {
-    int k = t + P2M_T * u;
-    if (k < nc) {
-      out[2 * k] = acr[u];
-      out[2 * k + 1] = aci[u];
+  double* out = mult + (size_t)c * ncoef(p) * 2;
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    int k = lane + 64 * v;
+    if (k < S) {
+      int n = both_sign_n(k), j = k - n * n, m = (j + 1) >> 1;
+      out[2 * cidx(n, m) + (j > 0 && !(j & 1) ? 1 : 0)] = sum[v];
+      if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
     }
   }
 }
@@ -137,15 +165,22 @@ __global__ void __launch_bounds__(P2M_T) k_p2m(int p, const int* leaves, int nle
 // shifted moment summed over k, then l ascending, products rounded
 // separately; the parent's coefficient then adds its children's sums in
 // octant order.  A sum is at most p + 1 terms of one child long, not eight
-// children long, so the few parents of the top levels finish quickly.
-constexpr int M2M_T = 128;
-constexpr int M2M_ALL_CHILDREN_PMAX = 16;  // the eight-children layout up to this order
-constexpr int M2M_TASKS = (8 * ncoef(M2M_ALL_CHILDREN_PMAX) + M2M_T - 1) / M2M_T;
+// children long, and the workgroup has a thread for (almost) every task, so a
+// level's launch, bound by the chain of its longest sum, is short: with 128
+// threads and five tasks each a launch took 47 us at p = 10 whatever the
+// level of up to a thousand parents (16 us now), and at p = 20, a child at a
+// time, 334 us (60).
+constexpr int M2M_T = 128;                 // threads of k_m2m_stream
+constexpr int M2M_ALL_CHILDREN_PMAX = 22;  // the eight-children layout up to this order (135 KB of LDS)
+constexpr int M2M_T_MAX = 1024;
+constexpr int M2M_TASKS = (8 * ncoef(M2M_ALL_CHILDREN_PMAX) + M2M_T_MAX - 1) / M2M_T_MAX;
 
-__global__ void __launch_bounds__(M2M_T) k_m2m(int p, int first, int count, const int* c0,
-                                                const int* nch, const double* cx, const double* cy,
-                                                const double* cz, double* mult) {
+__global__ void __launch_bounds__(M2M_T_MAX) k_m2m(int p, int first, int count, const int* __restrict__ c0,
+                                                    const int* __restrict__ nch, const double* __restrict__ cx,
+                                                    const double* __restrict__ cy, const double* __restrict__ cz,
+                                                    double* mult) {
   extern __shared__ double lds[];
+  const int M2M_T = blockDim.x;
   int c = first + blockIdx.x;
   if (blockIdx.x >= count || nch[c] == 0) return;
   int nc = ncoef(p);
@@ -168,8 +203,7 @@ __global__ void __launch_bounds__(M2M_T) k_m2m(int p, int first, int count, cons
   const double* src = mult + (size_t)k0 * nc * 2;
   for (int u = t; u < kn * S; u += M2M_T) {  // moments, both signs of q
     int j = u / S, r = u - j * S;
-    int n = 0;
-    while ((n + 1) * (n + 1) <= r) n++;
+    int n = both_sign_n(r);
     int q = r - n * n - n;
     const double* cm = src + (size_t)j * nc * 2;
     int aq = q < 0 ? -q : q;
@@ -189,9 +223,8 @@ __global__ void __launch_bounds__(M2M_T) k_m2m(int p, int first, int count, cons
     pr[w] = pi[w] = 0.0;
     int u = t + M2M_T * w;
     if (u < kn * nc) {
-      int j = u / nc, q = u - j * nc;
-      int n, m;
-      coef_nm(q, n, m);
+      int j, n, m;
+      child_task(u, kn, j, n, m);
       const double2* Y = Yx + j * S;
       const double2* M = Mx + j * S;
       double sr = 0.0, si = 0.0;
@@ -219,7 +252,11 @@ __global__ void __launch_bounds__(M2M_T) k_m2m(int p, int first, int count, cons
 #pragma unroll
   for (int w = 0; w < M2M_TASKS; w++) {
     int u = t + M2M_T * w;
-    if (u < kn * nc) part[u] = make_double2(pr[w], pi[w]);
+    if (u < kn * nc) {
+      int j, n, m;
+      child_task(u, kn, j, n, m);
+      part[j * nc + cidx(n, m)] = make_double2(pr[w], pi[w]);
+    }
   }
   __syncthreads();
   double* out = mult + (size_t)c * nc * 2;
@@ -233,6 +270,12 @@ __global__ void __launch_bounds__(M2M_T) k_m2m(int p, int first, int count, cons
     out[2 * q] = sr;
     out[2 * q + 1] = si;
   }
+}
+
+// threads for the 8 ncoef(p) tasks of eight children in the fewest rounds
+static int m2m_threads(int p) {
+  int tasks = 8 * ncoef(p), rounds = (int)ceil_div(tasks, M2M_T_MAX);
+  return (int)ceil_div(tasks, 64 * rounds) * 64;
 }
 
 size_t m2m_lds_bytes(int p) { return sizeof(double2) * 2 * 8 * (size_t)(p + 1) * (p + 1); }
@@ -269,8 +312,7 @@ __global__ void __launch_bounds__(M2M_T) k_m2m_stream(int p, int first, int coun
     }
     const double* cm = mult + (size_t)ch * nc * 2;
     for (int r = t; r < S; r += M2M_T) {
-      int n = 0;
-      while ((n + 1) * (n + 1) <= r) n++;
+      int n = both_sign_n(r);
       int q = r - n * n - n;
       int aq = q < 0 ? -q : q;
       double a = cm[2 * cidx(n, aq)], bb = cm[2 * cidx(n, aq) + 1];
@@ -341,7 +383,7 @@ void m2m_levels(Ctx& c, double* mult) {
   for (int level = c.depth - 1; level >= 0; level--) {
     int first = c.lvl_first[level], count = c.lvl_count[level];
     if (c.p <= M2M_ALL_CHILDREN_PMAX)
-      hipLaunchKernelGGL(k_m2m, dim3(count), dim3(M2M_T), m2m_lds_bytes(c.p), c.stream, c.p, first, count,
+      hipLaunchKernelGGL(k_m2m, dim3(count), dim3(m2m_threads(c.p)), m2m_lds_bytes(c.p), c.stream, c.p, first, count,
                          c.c_child0.p, c.c_nchild.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult);
     else
       hipLaunchKernelGGL(k_m2m_stream, dim3(count), dim3(M2M_T), m2m_lds_bytes(c.p) / 8, c.stream, c.p, first,
@@ -373,11 +415,11 @@ void upward_pass(Ctx& c) {
 void expansions_up(Ctx& c) {
   hipStream_t s = c.stream;
   int p = c.p, nc = (int)c.ncell;
-  const int* leaves = c.leaves.p;
-  size_t p2m_lds = sizeof(double) * (2 * ncoef(p) + 1) * p2m_batch(p);
-  hipLaunchKernelGGL(k_p2m, dim3((unsigned)c.nleaf), dim3(P2M_T), p2m_lds, s, p, leaves, (int)c.nleaf,
-                     c.c_begin.p, c.c_end.p, c.sx.p, c.sy.p, c.sz.p, c.sm.p, c.c_cx.p, c.c_cy.p,
-                     c.c_cz.p, c.mult.p);
+  int S = (p + 1) * (p + 1);
+  auto p2m = S <= 2 * 64 ? k_p2m<2> : S <= 4 * 64 ? k_p2m<4> : S <= 9 * 64 ? k_p2m<9> : k_p2m<16>;
+  hipLaunchKernelGGL(p2m, dim3((unsigned)ceil_div(c.nleaf, P2M_WAVES)), dim3(64 * P2M_WAVES),
+                     sizeof(double) * S * p2m_batch(p) * P2M_WAVES, s, p, c.leaves.p, (int)c.nleaf, c.c_begin.p,
+                     c.c_end.p, c.pm.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.mult.p);
   HIPCHK(hipGetLastError());
   m2m_levels(c, c.mult.p);
   int64_t npk = (int64_t)nc * (p + 1);

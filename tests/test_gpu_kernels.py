@@ -134,3 +134,25 @@ def test_near_field_segment_lengths(fmm, precision, n, n_leaf, eps_soft):
                                  np.array([0, 333, 333 + n]), eps_soft=eps_soft)
         assert torch.equal(both[333:], acc)
     f.close()
+
+
+# orders at the edges of the upward kernels' splits: P2M values per lane (p <= 10,
+# 14, 22, 30), M2M tasks in one round of threads or two, the eight-children
+# layout (p <= 22) and the streamed one
+@pytest.mark.parametrize("p", [1, 7, 10, 11, 14, 15, 16, 21, 22, 23, 30])
+def test_upward_orders(fmm, p):
+    """Multipoles and norms of the oracle, bit for bit: leaves of one body to
+    many batches, offsets whose high powers underflow (the division's general
+    path) and masses of zero."""
+    pos, mass = _clumps(600, 90)
+    pos[5:25] = pos[5] + np.random.default_rng(1).normal(size=(20, 3)) * 1e-7
+    pos[30:50] = 1e-30 * np.random.default_rng(2).normal(size=(20, 3))
+    mass[::9] = 0.0
+    print(f"[gpu] upward p={p}", flush=True)
+    f = fmm.FMM(p=p, n_leaf=24)
+    f.build(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    o.run(pos, mass, p=p, err_tol=1e-7, n_leaf=24, stage="upward")
+    assert np.array_equal(f.export("mult"), o.get("mult"))
+    assert np.array_equal(f.export("pk"), o.get("pk"))
+    f.close()

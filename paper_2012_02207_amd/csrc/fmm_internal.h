@@ -320,6 +320,10 @@ void direct_sum(int64_t n, const double* pos, const double* mass, double eps2, i
                 const int32_t* sinks, double* acc, double* pot, hipStream_t s);
 bool check_inputs_dev(Ctx& c, const double* pos, const double* mass, int64_t n);
 
+// the M2L's segment plan, and the sums of the split sinks' partial expansions
+constexpr int M2L_SEG = 512, M2L_HI_SEG = 512;  // pairs per segment, at least
+M2lSeg plan_m2l(Ctx& c, int seg_min);
+void combine_m2l(Ctx& c, const M2lSeg& sg, double* loc);
 // M2L launchers (one per compiled order)
 void launch_m2l_fp64(Ctx& c);
 // constant tables of the kernels, uploaded once per device at context creation

@@ -390,14 +390,14 @@ __global__ void k_m2l_combine(int ncd, int max_extra, const int* __restrict__ ns
   loc[(size_t)B * ncd + k] = s;
 }
 
-constexpr int M2L_SEG_MIN = 512;    // pairs per segment, at least
-constexpr int M2L_SEG_DIV = 8192;   // and at least the list total / M2L_SEG_DIV
+constexpr int M2L_SEG_DIV = 8192;  // pairs per segment: at least the list total / M2L_SEG_DIV
 
-// the plan for the M2L over whole lists (on c.stream)
-static M2lSeg plan_m2l(Ctx& c) {
+// the plan for the M2L over whole lists (on c.stream), at least seg_min pairs
+// per segment
+M2lSeg plan_m2l(Ctx& c, int seg_min) {
   int nc = (int)c.ncell;
   int64_t cnt = c.m2l.count;
-  int K = (int)std::max<int64_t>(M2L_SEG_MIN, ceil_div(cnt, M2L_SEG_DIV));
+  int K = (int)std::max<int64_t>(seg_min, ceil_div(cnt, M2L_SEG_DIV));
   // a split sink holds len > K pairs in ceil(len / K) < 2 len / K segments, so
   // the extra items number fewer than cnt / K <= M2L_SEG_DIV
   int64_t extra_max = std::min<int64_t>(M2L_SEG_DIV, ceil_div(cnt, K));
@@ -415,6 +415,15 @@ static M2lSeg plan_m2l(Ctx& c) {
   return M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p, K, (int)(nc + extra_max)};
 }
 
+// adds the partial expansions of the plan's split sinks
+void combine_m2l(Ctx& c, const M2lSeg& sg, double* loc) {
+  int ncd = ncoef(c.p) * 2, max_extra = sg.max_items - (int)c.ncell;
+  if (max_extra > 0)
+    hipLaunchKernelGGL(k_m2l_combine, dim3((unsigned)ceil_div((int64_t)max_extra * ncd, 256)), dim3(256), 0,
+                       c.stream, ncd, max_extra, sg.nseg, sg.pbase, sg.extra, sg.nextra, sg.part, loc);
+  HIPCHK(hipGetLastError());
+}
+
 // sinks == nullptr: every sink cell; otherwise the listed sinks (count on the
 // device, so the launch needs no host synchronisation)
 template <int P>
@@ -427,19 +436,14 @@ static void launch_p(Ctx& c, int first_lo, const double* mult, double* loc, cons
     return;
   }
   M2lSeg sg{};
-  if (first_lo >= nc) sg = plan_m2l(c);  // whole lists: long ones in segments
+  if (first_lo >= nc) sg = plan_m2l(c, M2L_SEG);  // whole lists: long ones in segments
   int nitems = sg.nseg ? sg.max_items : nc;
   int nblk = (nitems + M2L_WAVES - 1) / M2L_WAVES;
   unsigned grid = xcd_grid(nblk);
   hipLaunchKernelGGL((k_m2l_fp64<P, false>), dim3(grid), dim3(64 * M2L_WAVES), 0, c.stream, nc, first_lo,
                      (const int*)nullptr, (const int*)nullptr, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p,
                      c.c_cz.p, mult, loc, sg);
-  if (sg.nseg) {
-    int ncd = ncoef(P) * 2, max_extra = sg.max_items - nc;
-    if (max_extra > 0)
-      hipLaunchKernelGGL(k_m2l_combine, dim3((unsigned)ceil_div((int64_t)max_extra * ncd, 256)), dim3(256), 0,
-                         c.stream, ncd, max_extra, sg.nseg, sg.pbase, sg.extra, sg.nextra, sg.part, loc);
-  }
+  if (sg.nseg) combine_m2l(c, sg, loc);
 }
 
 template <int P>

@@ -1,22 +1,29 @@
-// Rotation-accelerated M2L for any order up to 30 (section 2.4), FP64.
+// Rotation-accelerated M2L for any order up to 30 (section 2.4), FP64, on the
+// matrix cores.
 //
 // The same operator as k_m2l_fp64 (m2l.hip): for a directed pair A -> B the
 // source moments are rotated about z by alpha = pi/2 - phi, their x and z
 // swapped, rotated about z by -theta and swapped again, so that R = z_B - z_A
 // lies along +z; translated along z, where only T_j^0(r z) = j!/r^{j+1} is
 // non-zero; then rotated back with the transposed sequence in the scaled basis
-// Lhat_n^m = L_n^m / ((n-m)!(n+m)!).  Real basis per order n: index 0 = Re c^0,
-// 2m-1 = Re c^m, 2m = Im c^m; W_n couples Re^m with Re^m' only when
-// m + m' + n is even (Im parts: odd), and those zeros are never stored.
+// Lhat_n^m = L_n^m / ((n-m)!(n+m)!).  W_n, the swap of order n, couples Re^m with
+// Re^m' only when m + m' + n is even and Im^m with Im^m' when it is odd, so it is
+// four blocks: the Re or the Im parts, input orders m of one parity.
 //
 // The register-resident kernel holds a whole expansion per lane, which stops
-// fitting beyond p = 16 (441 values at p = 20, 961 at p = 30).  Here the
-// order is a run-time value and the wavefront works on one pair at a time:
-// the 64 lanes share the (p+1)^2 real coefficients of the rotated moments,
-// which live in LDS between the steps (every swap mixes the coefficients of
-// one order), and each lane keeps a fixed slice of the sink's local
-// expansion in registers.  One wavefront per workgroup and per sink, so the
-// steps are separated by workgroup barriers of a single wave.
+// fitting beyond p = 16 (441 values at p = 20).  Here a workgroup of eight
+// wavefronts takes 16 NT pairs of one sink at a time, and each wavefront owns
+// four orders, n = w, 15 - w, 16 + w, 31 - w, whose swap matrices stay in its
+// registers.  A swap is a product of a constant block (up to 16 x 16) with the
+// coefficients of 16 pairs: v_mfma_f64_16x16x4f64, the pairs as columns.  Its
+// result, row 4r + lane/16 of column lane%16 in register r, is the operand layout
+// of the next product, and the Re and the Im block of a parity have the same
+// rows, so rotation, swap, rotation and swap of an order run in registers, from
+// the moments' loads on; only the translation, which couples the orders, goes
+// through LDS.
+// Measured at N = 10^5, p = 20, err_tol = 1e-7 (9.1e5 pairs): 4.34 ms alone; a
+// wavefront per pair with its coefficients shared by the lanes, two loads per
+// multiply-add, took 28.2 ms.
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -29,105 +36,223 @@ namespace fmm {
 namespace hi {
 
 constexpr int PMAX = FMM_TABLE_PMAX;  // orders with swap tables (section 2.4: p <= 30)
-constexpr int SMAX = (PMAX + 1) * (PMAX + 1);
-constexpr int TMAX = (SMAX + 63) / 64;  // local-expansion entries per lane
+constexpr int WAVES = 8;
+constexpr int SLOTS = 4;  // orders per wavefront; slot s: 8s <= n < 8s + 8, up to s + 1 K-steps of four orders m
 
-constexpr int rb_m(int j) { return (j + 1) >> 1; }
-constexpr bool rb_re(int j) { return j == 0 || (j & 1); }
-constexpr bool swap_nz(int n, int i, int j) {
-  return rb_re(i) == rb_re(j) && (((rb_m(i) + rb_m(j) + n) & 1) == (rb_re(i) ? 0 : 1));
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// order of slot s of wavefront w
+__host__ __device__ constexpr int slot_order(int s, int w) { return (s & 1) ? 8 * s + 7 - w : 8 * s + w; }
+
+// swap block of (n, part, parity of the input order) in operand layout: K-step
+// ks, lane l: output row l % 16, input order m = parity + 2 (4 ks + l / 16)
+__host__ __device__ constexpr int frag_index(int n, int part, int par, int ks) {
+  return ((n * 2 + part) * 2 + par) * 4 + ks;
 }
-constexpr int nnz_upto(int p) {  // structural non-zeros of W_0 .. W_p
-  int c = 0;
-  for (int n = 0; n <= p; n++)
-    for (int i = 0; i < 2 * n + 1; i++)
-      for (int j = 0; j < 2 * n + 1; j++) c += swap_nz(n, i, j) ? 1 : 0;
-  return c;
-}
-constexpr int CSW = nnz_upto(PMAX);
 
 }  // namespace hi
 
-// compacted W_n (n <= 30), row by row, columns ascending; offset of row i of
-// order n at [n^2 + i]
-static __device__ double g_cswap_hi[hi::CSW];
-static __device__ int g_rowoff_hi[hi::SMAX];
+static __device__ double g_swap_frag[hi::frag_index(hi::PMAX + 1, 0, 0, 0) * 64];
 static __constant__ double c_fact_hi[2 * hi::PMAX + 2];
 static bool g_hi_tables[64] = {};  // per device
 
-// Row i of order n: the first structurally non-zero column's order m0 and the
-// number of non-zeros; the columns are orders m0, m0 + 2, ... of the same part
-// (Re: column index 0 for m = 0, 2m - 1 otherwise; Im: 2m).
-__device__ __forceinline__ void hi_row(int n, int i, int& m0, int& cnt, bool& re) {
-  re = i == 0 || (i & 1);
-  int mi = (i + 1) >> 1;
-  if (re) {
-    m0 = (n + mi) & 1;
-  } else {
-    m0 = ((n + mi + 1) & 1) ? 1 : 2;
-  }
-  cnt = m0 <= n ? (n - m0) / 2 + 1 : 0;
-}
+// One order of one wavefront: its swap blocks, and the coefficients of 16 NT
+// pairs as operands.  c[part][b][t][ks]: parity slot b of tile t; the orders m of
+// slot b have parity b before the first swap and after the second, b ^ (n & 1)
+// between them.
+template <int SLOT, int NT>
+struct HiOrder {
+  static constexpr int KS = SLOT + 1;
+  double w[2][2][KS];
 
-// out[n^2 + i] = sum_j W_n[i][j] v[n^2 + j] for every row of orders 0..p
-__device__ __forceinline__ void hi_swap(int S, const double* __restrict__ v, double* __restrict__ out, int lane) {
-  for (int u = lane; u < S; u += 64) {
-    int n = (int)sqrtf((float)u);
-    while (n * n > u) n--;
-    while ((n + 1) * (n + 1) <= u) n++;
-    int i = u - n * n;
-    int m0, cnt;
-    bool re;
-    hi_row(n, i, m0, cnt, re);
-    const double* w = g_cswap_hi + g_rowoff_hi[u];
-    const double* vn = v + n * n;
-    double s = 0.0;
-    for (int t = 0; t < cnt; t++) {
-      int m = m0 + 2 * t;
-      int j = re ? (m == 0 ? 0 : 2 * m - 1) : 2 * m;
-      s = fma(w[t], vn[j], s);
-    }
-    out[u] = s;
+  __device__ __forceinline__ void load_swap(int n, int lane) {
+#pragma unroll
+    for (int part = 0; part < 2; part++)
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++)
+          w[part][b][ks] = g_swap_frag[hi::frag_index(n, part, b, ks) * 64 + lane];
   }
-}
 
-// rotation about z of every order: (C, S)_m <- (C cos ma - S sin ma, C sin ma + S cos ma)
-// with (cos ma, sin ma) from the table cs[m]; sgn = -1 rotates by -a
-__device__ __forceinline__ void hi_zrot(int S, double* v, const double2* cs, double sgn, int lane) {
-  for (int u = lane; u < S; u += 64) {
-    int n = (int)sqrtf((float)u);
-    while (n * n > u) n--;
-    while ((n + 1) * (n + 1) <= u) n++;
-    int j = u - n * n;
-    if (j & 1) {  // Re c^m at j = 2m - 1, Im c^m next to it
-      int m = (j + 1) >> 1;
-      double cm = cs[m].x, sm = sgn * cs[m].y;
-      double C = v[u], Sv = v[u + 1];
-      v[u] = fma(C, cm, -Sv * sm);
-      v[u + 1] = fma(C, sm, Sv * cm);
-    }
+  // c <- W c; odd: the input of slot b has parity 1 - b.  The Im parts change
+  // slots, so that a slot's Re and Im rows stay the same orders m.
+  template <bool ODD>
+  __device__ __forceinline__ void swap(double (&c)[2][2][NT][KS]) const {
+#pragma unroll
+    for (int part = 0; part < 2; part++)
+#pragma unroll
+      for (int t = 0; t < NT; t++) {
+        hi::v4d d[2];
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          d[b] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int ks = 0; ks < KS; ks++)
+            d[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[part][ODD ? 1 - b : b][ks], c[part][b][t][ks], d[b], 0, 0, 0);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+          for (int ks = 0; ks < KS; ks++) c[part][b ^ part][t][ks] = d[b][ks];
+      }
   }
-}
 
-// M2L of the list of sink B; with B >= first_lo only the sources below
-// first_lo are taken (the FP64 part of mixed precision)
-template <bool LIST>
-__global__ void __launch_bounds__(64) k_m2l_hi(int p, int ncell, int first_lo, const int* __restrict__ sinks,
-                                               const int* __restrict__ nsinks, const int* __restrict__ off,
-                                               const int* __restrict__ src, const double* __restrict__ cx,
-                                               const double* __restrict__ cy, const double* __restrict__ cz,
-                                               const double* __restrict__ mult, double* __restrict__ loc) {
+  // rotation about z, (C, S)_m <- (C cos ma - S sin ma, C sin ma + S cos ma), with
+  // (cos ma, sin ma) of pair col at tab[m * 16 NT + col]; flip: slot b holds
+  // parity 1 - b; sgn = -1 rotates by -a
+  __device__ __forceinline__ static void rotate(double (&c)[2][2][NT][KS], const double2* tab, int p, int flip,
+                                                double sgn, int lane) {
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        int m = min((b ^ flip) + 2 * (4 * ks + (lane >> 4)), p);  // (rows past the order are zero)
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          double2 cs = tab[m * 16 * NT + 16 * t + (lane & 15)];
+          double sn = sgn * cs.y, C = c[0][b][t][ks], S = c[1][b][t][ks];
+          c[0][b][t][ks] = fma(C, cs.x, -S * sn);
+          c[1][b][t][ks] = fma(C, sn, S * cs.x);
+        }
+      }
+  }
+
+  // rotation, swap, rotation, swap: forward (by a, then b) or back (by -b after
+  // the first swap, by -a after the second)
+  template <bool BACK>
+  __device__ __forceinline__ void turn(double (&c)[2][2][NT][KS], int n, int p, const double2* ta, const double2* tb,
+                                       int lane) const {
+    int odd = n & 1;
+    if (!BACK) rotate(c, ta, p, 0, 1.0, lane);
+    swap<false>(c);
+    rotate(c, tb, p, odd, BACK ? -1.0 : 1.0, lane);
+    if (odd)
+      swap<true>(c);
+    else
+      swap<false>(c);
+    if (BACK) rotate(c, ta, p, 0, -1.0, lane);
+  }
+
+  // the moments of the pairs' sources, turned, to v (row n^2 + real-basis entry,
+  // rs values apart)
+  __device__ __forceinline__ void forward(int n, int p, const double2* const (&M)[NT], const double2* ta,
+                                          const double2* tb, double* v, int rs, int lane) const {
+    double c[2][2][NT][KS];
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        int m = b + 2 * (4 * ks + (lane >> 4));
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          double2 x = M[t][cidx(n, min(m, n))];
+          c[0][b][t][ks] = m <= n ? x.x : 0.0;
+          c[1][b][t][ks] = m <= n && m > 0 ? x.y : 0.0;
+        }
+      }
+    turn<false>(c, n, p, ta, tb, lane);
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        int m = b + 2 * (4 * ks + (lane >> 4));
+        if (m <= n) {
+#pragma unroll
+          for (int t = 0; t < NT; t++) {
+            double* o = v + (n * n + 2 * m) * rs + 16 * t + (lane & 15);
+            if (m > 0) {
+              o[-rs] = c[0][b][t][ks];
+              o[0] = c[1][b][t][ks];
+            } else {
+              o[0] = c[0][b][t][ks];
+            }
+          }
+        }
+      }
+  }
+
+  // the translated coefficients from v, turned back and added over the pairs to
+  // acc (real basis)
+  __device__ __forceinline__ void back(int n, int p, const double2* ta, const double2* tb, const double* v, int rs,
+                                       double* acc, int lane) const {
+    double c[2][2][NT][KS];
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        int m = b + 2 * (4 * ks + (lane >> 4));
+        bool ok = m <= n && m + n <= p;  // (the translation reaches no others)
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          const double* o = v + (n * n + 2 * min(m, n)) * rs + 16 * t + (lane & 15);
+          c[0][b][t][ks] = ok ? o[m > 0 ? -rs : 0] : 0.0;
+          c[1][b][t][ks] = ok && m > 0 ? o[0] : 0.0;
+        }
+      }
+    turn<true>(c, n, p, ta, tb, lane);
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        int m = b + 2 * (4 * ks + (lane >> 4));
+#pragma unroll
+        for (int part = 0; part < 2; part++) {
+          double s = c[part][b][0][ks];
+#pragma unroll
+          for (int t = 1; t < NT; t++) s += c[part][b][t][ks];
+          s += dpp_read<0x140>(s);  // over the 16 lanes of the row
+          s += dpp_read<0x141>(s);
+          s += dpp_read<0x4E>(s);
+          s += dpp_read<0xB1>(s);
+          if ((lane & 15) == 0 && m <= n && m >= part) acc[n * n + (part ? 2 * m : m > 0 ? 2 * m - 1 : 0)] += s;
+        }
+      }
+  }
+};
+
+// M2L of the list of each sink (a workgroup per sink, or per segment of a long
+// list, see M2lSeg), or of the listed sinks; with B >= first_lo only the sources
+// below first_lo are taken (the FP64 part of mixed precision).
+// NT tiles of 16 pairs at a time, orders up to PM.
+template <int NT, int PM>
+__global__ void __launch_bounds__(64 * hi::WAVES) k_m2l_hi(int p, int ncell, int first_lo,
+                                                           const int* __restrict__ sinks,
+                                                           const int* __restrict__ nsinks,
+                                                           const int* __restrict__ off, const int* __restrict__ src,
+                                                           const double* __restrict__ cx, const double* __restrict__ cy,
+                                                           const double* __restrict__ cz,
+                                                           const double* __restrict__ mult, double* __restrict__ loc,
+                                                           M2lSeg sg) {
   extern __shared__ double lds[];
+  constexpr int PT = 16 * NT, RS = PT + 1;  // pairs at a time; row stride in V
+  constexpr int T_MAX = PM + 1;
   const int S = (p + 1) * (p + 1), NC = ncoef(p);
   double* V = lds;
-  double* U = lds + S;
-  double2* ca_t = (double2*)(lds + 2 * S);  // (cos m alpha, sin m alpha), m = 0..p
-  double2* cb_t = ca_t + (p + 1);           // (cos m theta', sin m theta') of -theta
-  double* g = (double*)(cb_t + (p + 1));    // g_j = j! / r^{j+1}, j = 0..p
-  const int lane = threadIdx.x;
-  int count = LIST ? *nsinks : ncell;
+  double2* ta = (double2*)(lds + ((S * RS + 1) & ~1));  // (cos m alpha, sin m alpha) [m][pair]
+  double2* tb = ta + (p + 1) * PT;                      // of -theta
+  double* rin = (double*)(tb + (p + 1) * PT);           // 1 / r of each pair, 0 past the end of the list
+  double* acc = rin + PT;                               // [S] the sink's expansion
+  int* ids = (int*)(acc + S);                           // sources of the pairs
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  HiOrder<0, NT> o0;
+  HiOrder<1, NT> o1;
+  HiOrder<2, NT> o2;
+  HiOrder<3, NT> o3;
+  const int n0 = hi::slot_order(0, wv), n1 = hi::slot_order(1, wv), n2 = hi::slot_order(2, wv),
+            n3 = hi::slot_order(3, wv);
+  if (n0 <= p) o0.load_swap(n0, lane);
+  if (n1 <= p) o1.load_swap(n1, lane);
+  if (n2 <= p) o2.load_swap(n2, lane);
+  if (PM >= 24 && n3 <= p) o3.load_swap(n3, lane);
+  int count = sinks ? *nsinks : sg.nseg ? ncell + *sg.nextra : ncell;
   for (int it = blockIdx.x; it < count; it += gridDim.x) {
-    int B = LIST ? sinks[it] : it;
+    int B = sinks ? sinks[it] : it, seg = 0;
+    if (!sinks && it >= ncell) {
+      int2 x = sg.extra[it - ncell];
+      B = x.x;
+      seg = x.y;
+    }
     int b = off[B], e = off[B + 1];
     if (B >= first_lo) {
       int lo = b, hi = e;
@@ -141,115 +266,114 @@ __global__ void __launch_bounds__(64) k_m2l_hi(int p, int ncell, int first_lo, c
       e = lo;
     }
     double* out = loc + (size_t)B * NC * 2;
+    if (sg.nseg && sg.nseg[B] > 1) {
+      b += seg * sg.K;
+      e = min(e, b + sg.K);
+      if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
+    }
     if (b == e) {
-      for (int k = lane; k < NC * 2; k += 64) out[k] = 0.0;
+      for (int k = tid; k < NC * 2; k += 64 * hi::WAVES) out[k] = 0.0;
       continue;
     }
-    double acc[hi::TMAX];
-#pragma unroll
-    for (int t = 0; t < hi::TMAX; t++) acc[t] = 0.0;
+    __syncthreads();  // the previous item's sums have been read
+    for (int k = tid; k < S; k += 64 * hi::WAVES) acc[k] = 0.0;
     double bx = cx[B], by = cy[B], bz = cz[B];
-    for (int k = b; k < e; k++) {
-      int A = src[k];
-      double Rx = bx - cx[A], Ry = by - cy[A], Rz = bz - cz[A];
-      double rho2 = fma(Rx, Rx, Ry * Ry);
-      double r2 = fma(Rz, Rz, rho2);
-      double rinv = 1.0 / sqrt(r2);
-      double rho = sqrt(rho2);
-      double ca, sa;
-      if (rho > 0.0) {
-        double ri = 1.0 / rho;
-        ca = Ry * ri;
-        sa = Rx * ri;
-      } else {
-        ca = 0.0;
-        sa = 1.0;
+    for (int base = b; base < e; base += PT) {
+      __syncthreads();  // the previous pairs' tables have been read
+      if (tid < 2 * PT) {  // angle multiples by the angle-addition recurrence, alpha and -theta
+        int pr = tid % PT, k = base + pr;
+        bool act = k < e;
+        int A = src[act ? k : b];
+        double Rx = bx - cx[A], Ry = by - cy[A], Rz = bz - cz[A];
+        double rho2 = fma(Rx, Rx, Ry * Ry);
+        double r2 = fma(Rz, Rz, rho2);
+        double rinv = 1.0 / sqrt(r2), rho = sqrt(rho2);
+        double c1, s1;
+        double2* t;
+        if (tid < PT) {
+          c1 = rho > 0.0 ? Ry / rho : 0.0;
+          s1 = rho > 0.0 ? Rx / rho : 1.0;
+          t = ta;
+          ids[pr] = A;
+          rin[pr] = act ? rinv : 0.0;
+        } else {
+          c1 = Rz * rinv;
+          s1 = -rho * rinv;
+          t = tb;
+        }
+        double cm = 1.0, sm = 0.0;
+        for (int m = 0; m <= p; m++) {
+          t[m * PT + pr] = make_double2(cm, sm);
+          double c2 = fma(cm, c1, -sm * s1);
+          sm = fma(sm, c1, cm * s1);
+          cm = c2;
+        }
       }
-      double cb = Rz * rinv, sb = -rho * rinv;
-      // angle tables by the angle-addition recurrence, one lane per order m
-      // (lanes 0..p for alpha, 32..32+p for -theta), and the translation
-      // factors (lanes 0..p)
+      __syncthreads();
       {
-        int m = lane & 31;
-        if (m <= p) {
-          double c1 = lane < 32 ? ca : cb, s1 = lane < 32 ? sa : sb;
-          double cm = 1.0, sm = 0.0;
-          for (int q = 1; q <= m; q++) {
-            double c2 = fma(cm, c1, -sm * s1);
-            sm = fma(sm, c1, cm * s1);
-            cm = c2;
-          }
-          (lane < 32 ? ca_t : cb_t)[m] = make_double2(cm, sm);
-          if (lane < 32) {
-            double rp = rinv;
-            for (int q = 0; q < m; q++) rp *= rinv;
-            g[m] = c_fact_hi[m] * rp;
-          }
-        }
-      }
-      // source moments in the real basis
-      const double* M = mult + (size_t)A * NC * 2;
-      for (int u = lane; u < S; u += 64) {
-        int n = (int)sqrtf((float)u);
-        while (n * n > u) n--;
-        while ((n + 1) * (n + 1) <= u) n++;
-        int j = u - n * n, m = (j + 1) >> 1;
-        bool im = j > 0 && !(j & 1);
-        V[u] = M[2 * cidx(n, m) + (im ? 1 : 0)];
-      }
-      __syncthreads();
-      hi_zrot(S, V, ca_t, 1.0, lane);
-      __syncthreads();
-      hi_swap(S, V, U, lane);
-      __syncthreads();
-      hi_zrot(S, U, cb_t, 1.0, lane);
-      __syncthreads();
-      hi_swap(S, U, V, lane);
-      __syncthreads();
-      // translation along z in the scaled basis:
-      // Lhat_n^m = (-1)^{n+m} / ((n-m)!(n+m)!) sum_{k=m}^{p-n} M'_k^m g_{n+k}
-      for (int u = lane; u < S; u += 64) {
-        int n = (int)sqrtf((float)u);
-        while (n * n > u) n--;
-        while ((n + 1) * (n + 1) <= u) n++;
-        int j = u - n * n, m = (j + 1) >> 1;
-        double s = 0.0;
-        if (m <= p - n) {
-          for (int kk = m; kk <= p - n; kk++) s = fma(V[kk * kk + j], g[n + kk], s);
-          double f = (((n + m) & 1) ? -1.0 : 1.0) / (c_fact_hi[n - m] * c_fact_hi[n + m]);
-          s = s * f;
-        }
-        U[u] = s;
-      }
-      __syncthreads();
-      hi_swap(S, U, V, lane);
-      __syncthreads();
-      hi_zrot(S, V, cb_t, -1.0, lane);
-      __syncthreads();
-      hi_swap(S, V, U, lane);
-      __syncthreads();
-      hi_zrot(S, U, ca_t, -1.0, lane);
-      __syncthreads();
+        const double2* M[NT];
 #pragma unroll
-      for (int t = 0; t < hi::TMAX; t++) {
-        int u = lane + 64 * t;
-        if (u < S) acc[t] += U[u];
+        for (int t = 0; t < NT; t++) M[t] = (const double2*)mult + (size_t)ids[16 * t + (lane & 15)] * NC;
+        if (n0 <= p) o0.forward(n0, p, M, ta, tb, V, RS, lane);
+        if (n1 <= p) o1.forward(n1, p, M, ta, tb, V, RS, lane);
+        if (n2 <= p) o2.forward(n2, p, M, ta, tb, V, RS, lane);
+        if (PM >= 24 && n3 <= p) o3.forward(n3, p, M, ta, tb, V, RS, lane);
       }
-      __syncthreads();  // U and the tables are rewritten by the next pair
+      __syncthreads();
+      // Translation along z, Lhat_n^m = (-1)^{n+m} / ((n-m)!(n+m)!)
+      // sum_{k=m}^{p-n} M'_k^m j!/r^{j+1}, j = n + k: a wavefront per order m, a
+      // lane per pair and part, in place (the lane reads its column, then writes)
+      for (int h = 0; h < 2; h++) {
+        int m = h ? 15 - wv : wv, part = lane / PT, col = lane % PT, K = p - 2 * m;
+        if (K < 0) continue;
+        double g[T_MAX], s[T_MAX];
+        double ri = rin[col], rp = ri;
+        for (int j = 0; j < 2 * m; j++) rp *= ri;
+#pragma unroll
+        for (int j = 0; j < T_MAX; j++) {
+          s[j] = 0.0;
+          if (j <= K) {
+            g[j] = c_fact_hi[2 * m + j] * rp;
+            rp *= ri;
+          } else {
+            g[j] = 0.0;
+          }
+        }
+        if (part < 2 && !(m == 0 && part == 1)) {
+          int row = part ? 2 * m : m > 0 ? 2 * m - 1 : 0;
+#pragma unroll
+          for (int kk = 0; kk < T_MAX; kk++) {
+            if (kk <= K) {
+              int k = m + kk;
+              double x = V[(k * k + row) * RS + col];
+#pragma unroll
+              for (int nn = 0; nn < T_MAX - kk; nn++)
+                if (nn + kk <= K) s[nn] = fma(x, g[nn + kk], s[nn]);
+            }
+          }
+#pragma unroll
+          for (int nn = 0; nn < T_MAX; nn++) {
+            if (nn <= K) {
+              int n = m + nn;
+              double f = ((nn & 1) ? -1.0 : 1.0) / (c_fact_hi[nn] * c_fact_hi[n + m]);
+              V[(n * n + row) * RS + col] = s[nn] * f;
+            }
+          }
+        }
+      }
+      __syncthreads();
+      if (n0 <= p) o0.back(n0, p, ta, tb, V, RS, acc, lane);
+      if (n1 <= p) o1.back(n1, p, ta, tb, V, RS, acc, lane);
+      if (n2 <= p) o2.back(n2, p, ta, tb, V, RS, acc, lane);
+      if (PM >= 24 && n3 <= p) o3.back(n3, p, ta, tb, V, RS, acc, lane);
     }
+    __syncthreads();
     // back to the unscaled basis: L_n^m = (n-m)!(n+m)! Lhat_n^m
-#pragma unroll
-    for (int t = 0; t < hi::TMAX; t++) {
-      int u = lane + 64 * t;
-      if (u < S) {
-        int n = (int)sqrtf((float)u);
-        while (n * n > u) n--;
-        while ((n + 1) * (n + 1) <= u) n++;
-        int j = u - n * n, m = (j + 1) >> 1;
-        bool im = j > 0 && !(j & 1);
-        out[2 * cidx(n, m) + (im ? 1 : 0)] = acc[t] * (c_fact_hi[n - m] * c_fact_hi[n + m]);
-        if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
-      }
+    for (int u = tid; u < S; u += 64 * hi::WAVES) {
+      int n = both_sign_n(u), j = u - n * n, m = (j + 1) >> 1;
+      bool im = j > 0 && !(j & 1);
+      out[2 * cidx(n, m) + (im ? 1 : 0)] = acc[u] * (c_fact_hi[n - m] * c_fact_hi[n + m]);
+      if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
     }
   }
 }
@@ -258,45 +382,47 @@ void upload_hi_tables() {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   if (g_hi_tables[dev & 63]) return;
-  std::vector<double> cs;
-  std::vector<int> ro(hi::SMAX, 0);
-  cs.reserve(hi::CSW);
+  std::vector<double> fr((size_t)hi::frag_index(hi::PMAX + 1, 0, 0, 0) * 64, 0.0);
   for (int n = 0; n <= hi::PMAX; n++) {
     int D = 2 * n + 1, sw = n * (4 * n * n - 1) / 3;  // dense table offset of order n
-    for (int i = 0; i < D; i++) {
-      ro[n * n + i] = (int)cs.size();
-      for (int j = 0; j < D; j++)
-        if (hi::swap_nz(n, i, j)) cs.push_back(fmm_swap_table[sw + i * D + j]);
-    }
+    for (int part = 0; part < 2; part++)
+      for (int par = 0; par < 2; par++)
+        for (int ks = 0; ks < 4; ks++)
+          for (int l = 0; l < 64; l++) {
+            int mo = (par ^ (n & 1) ^ part) + 2 * (l & 15), mi = par + 2 * (4 * ks + (l >> 4));
+            if (mo > n || mi > n || (part && (mo == 0 || mi == 0))) continue;
+            int i = part ? 2 * mo : mo > 0 ? 2 * mo - 1 : 0, j = part ? 2 * mi : mi > 0 ? 2 * mi - 1 : 0;
+            fr[(size_t)hi::frag_index(n, part, par, ks) * 64 + l] = fmm_swap_table[sw + i * D + j];
+          }
   }
-  if ((int)cs.size() != hi::CSW) throw hip_error{hipErrorInvalidValue, "compacted swap table size"};
-  HIPCHK(hipMemcpyToSymbol(HIP_SYMBOL(g_cswap_hi), cs.data(), sizeof(double) * cs.size()));
-  HIPCHK(hipMemcpyToSymbol(HIP_SYMBOL(g_rowoff_hi), ro.data(), sizeof(int) * ro.size()));
+  HIPCHK(hipMemcpyToSymbol(HIP_SYMBOL(g_swap_frag), fr.data(), sizeof(double) * fr.size()));
   HIPCHK(hipMemcpyToSymbol(HIP_SYMBOL(c_fact_hi), fmm_fact_table, sizeof(double) * (2 * hi::PMAX + 2)));
   g_hi_tables[dev & 63] = true;
 }
 
-size_t m2l_hi_lds_bytes(int p) {
-  size_t S = (size_t)(p + 1) * (p + 1);
-  return sizeof(double) * (2 * S + 5 * (size_t)(p + 1));
+static size_t m2l_hi_lds_bytes(int p, int nt) {
+  size_t S = (size_t)(p + 1) * (p + 1), pt = 16 * (size_t)nt;
+  return sizeof(double) * (((S * (pt + 1) + 1) & ~(size_t)1) + 4 * (p + 1) * pt + pt + S) + sizeof(int) * pt;
 }
 
-// any order up to 30; sinks == nullptr: every sink cell, else the listed ones
+// any order up to 30; sinks == nullptr: every sink cell (its long lists in
+// segments, whole lists only), else the listed ones
 void launch_m2l_hi(Ctx& c, int first_lo, const double* mult, double* loc, const int* sinks,
                    const int* nsinks) {
   if (c.p > hi::PMAX) throw unsupported_error{"expansion order above 30"};
   upload_hi_tables();
   int nc = (int)c.ncell;
-  size_t lds = m2l_hi_lds_bytes(c.p);
-  if (sinks) {
-    hipLaunchKernelGGL((k_m2l_hi<true>), dim3(2048), dim3(64), lds, c.stream, c.p, nc, first_lo, sinks, nsinks,
-                       c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult, loc);
-  } else {
-    hipLaunchKernelGGL((k_m2l_hi<false>), dim3((unsigned)std::max(nc, 1)), dim3(64), lds, c.stream, c.p, nc,
-                       first_lo, (const int*)nullptr, (const int*)nullptr, c.m2l.off.p, c.m2l.src.p, c.c_cx.p,
-                       c.c_cy.p, c.c_cz.p, mult, loc);
-  }
+  M2lSeg sg{};
+  if (!sinks && first_lo >= nc) sg = plan_m2l(c, M2L_HI_SEG);
+  unsigned grid = sinks ? 2048u : (unsigned)std::max(sg.nseg ? sg.max_items : nc, 1);
+  // 32 pairs at a time where their coefficients fit the 160 KB of LDS (p <= 20)
+  constexpr int P_TWO = 20;
+  auto kern = c.p <= P_TWO ? k_m2l_hi<2, P_TWO> : k_m2l_hi<1, hi::PMAX>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * hi::WAVES), m2l_hi_lds_bytes(c.p, c.p <= P_TWO ? 2 : 1), c.stream,
+                     c.p, nc, first_lo, sinks, nsinks, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult,
+                     loc, sg);
   HIPCHK(hipGetLastError());
+  if (sg.nseg) combine_m2l(c, sg, loc);
 }
 
 }  // namespace fmm

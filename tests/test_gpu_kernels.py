@@ -156,3 +156,28 @@ def test_upward_orders(fmm, p):
     assert np.array_equal(f.export("mult"), o.get("mult"))
     assert np.array_equal(f.export("pk"), o.get("pk"))
     f.close()
+
+
+# the matrix-core M2L: one and two tiles of 16 pairs at a time (p <= 20), orders
+# owned by two, three and four slots of a wavefront, lists of one pair to several
+# segments
+@pytest.mark.parametrize("p,n,n_leaf,err_tol", [(17, 400, 40, 1e-3), (18, 3000, 8, 1e-6), (20, 9000, 4, 1e-8),
+                                                (21, 3000, 16, 1e-6), (23, 2000, 8, 1e-6), (25, 2500, 16, 1e-6),
+                                                (29, 1500, 4, 1e-9)])
+def test_high_order_m2l(fmm, p, n, n_leaf, err_tol):
+    """Local expansions and forces of the oracle to rounding (the FP64 parity
+    bounds: median 1e-12, maximum 1e-9), with the same lists."""
+    pos, _, mass = W.plummer(n, 80 + p)
+    print(f"[gpu] high order p={p} n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=p, err_tol=err_tol, n_leaf=n_leaf)
+    acc, _ = f.forces(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    oacc, _ = o.run(pos, mass, p=p, err_tol=err_tol, n_leaf=n_leaf)
+    rel = np.linalg.norm(acc.cpu().numpy() - oacc, axis=1) / np.linalg.norm(oacc, axis=1)
+    assert np.median(rel) <= 1e-12 and rel.max() <= 1e-9, (np.median(rel), rel.max())
+    lg, lo = f.export("local"), o.get("local")
+    scale = np.abs(lo).max(axis=1, keepdims=True) + 1e-300
+    assert np.median(np.abs(lg - lo) / scale) < 1e-12
+    a2, _ = f.forces(_dev(pos), _dev(mass))
+    assert torch.equal(acc, a2)
+    f.close()

@@ -178,6 +178,91 @@ __device__ __forceinline__ int system_of(const int* off, int nsys, int64_t i) {
   return lo;
 }
 
+// ---- stable LSD radix sort within one workgroup of 1024 threads ---------------
+// Up to I keys per thread (and payloads, with VAL), in registers: wavefront w
+// holds positions (w C + c) 64 + lane, c < C, of the 1024 C keys (pad with all
+// ones: they stay last).  Per 8-bit pass a key's rank among equal digits comes
+// from ballots, as in the tiled sort of tree.hip, and the keys move through LDS.
+constexpr int BS_T = 1024, BS_W = BS_T / 64;
+template <class K, int I, bool VAL>
+struct BlockSort {
+  K sk[BS_T * I];
+  int sv[VAL ? BS_T * I : 1];
+  int wcnt[BS_W][256];
+  int dstart[256], wsum[4];
+};
+
+template <class K, int I, bool VAL>
+__device__ inline void block_sort(BlockSort<K, I, VAL>& s, K (&k)[I], int (&v)[I], int C, int nbits) {
+  int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint64_t lt = lanemask_lt();
+  for (int shift = 0; shift < nbits; shift += 8) {
+    for (int t = tid; t < BS_W * 256; t += BS_T) (&s.wcnt[0][0])[t] = 0;
+    __syncthreads();
+    int rank[I];
+#pragma unroll
+    for (int c = 0; c < I; c++) {
+      if (c < C) {
+        int d = (int)((k[c] >> shift) & 255);
+        uint64_t peers = ~0ull;
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+          bool bit = (d >> b) & 1;
+          uint64_t bb = ballot(bit);
+          peers &= bit ? bb : ~bb;
+        }
+        int cnt = s.wcnt[w][d];
+        rank[c] = cnt + __popcll(peers & lt);
+        __builtin_amdgcn_wave_barrier();
+        if ((peers >> lane) == 1ull) s.wcnt[w][d] = cnt + __popcll(peers);  // the highest peer
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    if (tid < 256) {  // per digit: starts of the wavefronts' runs, and of the digit
+      int tot = 0;
+      for (int ww = 0; ww < BS_W; ww++) {
+        int t = s.wcnt[ww][tid];
+        s.wcnt[ww][tid] = tot;
+        tot += t;
+      }
+      int incl = tot;
+      for (int o = 1; o < 64; o <<= 1) {
+        int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      if (lane == 63) s.wsum[w] = incl;
+      s.dstart[tid] = incl - tot;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      int before = 0;
+      for (int ww = 0; ww < w; ww++) before += s.wsum[ww];
+      s.dstart[tid] += before;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < I; c++) {
+      if (c < C) {
+        int d = (int)((k[c] >> shift) & 255);
+        int lp = s.dstart[d] + s.wcnt[w][d] + rank[c];
+        s.sk[lp] = k[c];
+        if (VAL) s.sv[lp] = v[c];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < I; c++) {
+      if (c < C) {
+        int at = (w * C + c) * 64 + lane;
+        k[c] = s.sk[at];
+        if (VAL) v[c] = s.sv[at];
+      }
+    }
+    // (the next pass writes sk only after further barriers)
+  }
+}
+
 // ---- the bodies of a list of leaves as a stream of 64-body chunks ----------
 // One wavefront reads the bodies of the list src[q .. qe) (cells, bodies
 // [cb, ce) each) in list order, 64 at a time whatever the leaves' sizes: short

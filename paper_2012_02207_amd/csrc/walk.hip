@@ -260,6 +260,40 @@ __global__ void k_extract_src(const K* keys, int64_t cnt, uint64_t mask, int* sr
   if (i < cnt) src[i] = (int)((uint64_t)keys[i] & mask);
 }
 
+// A list of up to GS_MAX entries of 32-bit keys by one workgroup: sort, sources
+// and offsets in one launch instead of three per pass and two (a launch costs
+// some 5 us whatever its size).
+constexpr int GS_I = 20;
+constexpr int GS_MAX = BS_T * GS_I;
+
+__global__ void __launch_bounds__(BS_T) k_group_small(const uint64_t* __restrict__ raw, int cnt, int nseg, int bits,
+                                                      int* __restrict__ src, int* __restrict__ off) {
+  __shared__ BlockSort<uint32_t, GS_I, false> bs;
+  int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int C = (cnt + BS_T - 1) / BS_T;
+  uint32_t k[GS_I];
+  int v[GS_I];
+#pragma unroll
+  for (int c = 0; c < GS_I; c++) {
+    int i = (w * C + c) * 64 + lane;
+    k[c] = c < C && i < cnt ? (uint32_t)raw[i] : 0xffffffffu;
+  }
+  block_sort(bs, k, v, C, 2 * bits);
+  // (bs.sk holds the sorted keys) entry i starts the lists of the sinks after
+  // the one before it, up to its own; the sinks after the last start at the end
+  uint32_t mask = (1u << bits) - 1u;
+  for (int i = tid; i <= cnt; i += BS_T) {
+    int from = i > 0 ? (int)(bs.sk[i - 1] >> bits) + 1 : 0;
+    int to = nseg;
+    if (i < cnt) {
+      uint32_t q = bs.sk[i];
+      src[i] = (int)(q & mask);
+      to = (int)(q >> bits);
+    }
+    for (int t = from; t <= to; t++) off[t] = i;
+  }
+}
+
 static int list_bits(int64_t ncell) {
   int b = 1;
   while (((int64_t)1 << b) < ncell) b++;
@@ -272,6 +306,11 @@ static void group_by_sink(Ctx& c, CellList& L) {
   int bits = list_bits(c.ncell);
   ensure(c.ws, L.off, (size_t)nc + 1);
   ensure(c.ws, L.src, (size_t)std::max<int64_t>(L.count, 1));
+  if (2 * bits <= 32 && L.count <= GS_MAX) {
+    hipLaunchKernelGGL(k_group_small, dim3(1), dim3(BS_T), 0, s, L.raw.p, (int)L.count, nc, bits, L.src.p, L.off.p);
+    HIPCHK(hipGetLastError());
+    return;
+  }
   ensure(c.ws, L.tmp, (size_t)std::max<int64_t>(L.count, 1));
   uint64_t mask = ((uint64_t)1 << bits) - 1;
   unsigned g = (unsigned)std::max<int64_t>(1, ceil_div(L.count, 256));

@@ -181,3 +181,27 @@ def test_high_order_m2l(fmm, p, n, n_leaf, err_tol):
     a2, _ = f.forces(_dev(pos), _dev(mass))
     assert torch.equal(acc, a2)
     f.close()
+
+
+# up to 8192 bodies are sorted, and lists of up to 20480 entries grouped, by one
+# workgroup of 1024 threads
+@pytest.mark.parametrize("n,n_leaf", [(1, 64), (63, 4), (1023, 64), (1025, 30), (3000, 40), (8191, 200), (8192, 300),
+                                      (8193, 300)])
+def test_one_workgroup_sorts(fmm, n, n_leaf):
+    """Keys, order (ties in the caller's) and lists of the oracle, bit for bit,
+    the lists ascending by sink and source."""
+    pos, mass = _clumps(n, 70 + n)
+    print(f"[gpu] sorts n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=3, err_tol=1e-4, n_leaf=n_leaf)
+    f.forces(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    o.run(pos, mass, p=3, err_tol=1e-4, n_leaf=n_leaf, stage="walk")
+    assert np.array_equal(f.export("keys"), o.get("keys"))
+    assert np.array_equal(f.export("perm").astype(np.int64), o.get("perm"))
+    assert np.array_equal(f.export("rootbox"), o.get("rootbox"))
+    for k in ("est_far", "est_near", "m2l", "p2p"):
+        want = np.asarray(o.get(k), dtype=np.int64).reshape(-1, 2)
+        want = want[np.lexsort((want[:, 1], want[:, 0]))]
+        print(k, len(want), flush=True)
+        assert np.array_equal(f.export(k).astype(np.int64).reshape(-1, 2), want), k
+    f.close()

@@ -273,13 +273,15 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 // Pair arithmetic in FP32 on the separation formed in FP64 and rounded
 // once; FP32 partial sums are carried into FP64 after every source leaf
 // (blocked compensation: the FP32 error grows with the leaf, not the list).
-// one source body s (mass ms) acting on the sink me
+// one source body s (mass ms) acting on the sink me; CHECK: a pair at d2 = 0
+// (or NaN) counts as rinv = 0, without it as rinv = inf (NaN)
+template <bool CHECK>
 __device__ __forceinline__ void pair32(const double4& s, float ms, const double4& me, float eps2f, float& fx,
                                        float& fy, float& fz, float& fp) {
   float dx = (float)(s.x - me.x), dy = (float)(s.y - me.y), dz = (float)(s.z - me.z);
   float d2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2f)));
   float rinv = __builtin_amdgcn_rsqf(d2);
-  rinv = d2 > 0.f ? rinv : 0.f;
+  if (CHECK) rinv = d2 > 0.f ? rinv : 0.f;
   float mr = ms * rinv;
   float mr3 = mr * rinv * rinv;
   fx = fmaf(mr3, dx, fx);
@@ -289,18 +291,49 @@ __device__ __forceinline__ void pair32(const double4& s, float ms, const double4
 }
 
 // staged source record: FP64 position, the mass rounded to FP32 once here and
-// kept in the low word of .w
-__device__ __forceinline__ double4 stage(double4 v) {
-  v.w = __longlong_as_double((long long)__float_as_uint((float)v.w));
-  return v;
+// kept in the low word of .w (the high word is not read)
+struct Staged {
+  double2 xy;
+  uint4 zm;
+};
+// body min(j0 + lane, je - 1) (lane32: 32 times the lane; the address is a scalar
+// base plus a 32-bit offset)
+__device__ __forceinline__ Staged load_staged(const double4* pm, int j0, int je, unsigned lane32) {
+  const char* base = (const char*)(pm + min(j0, je - 1));
+  unsigned o = min(lane32, (unsigned)max(je - j0 - 1, 0) * 32u);
+  Staged r;
+  r.xy = *(const double2*)(base + o);
+  r.zm = *(const uint4*)(base + o + 16u);
+  return r;
+}
+__device__ __forceinline__ void put_staged(double4* d, Staged r) {
+  double m = __hiloint2double((int)r.zm.w, (int)r.zm.z);
+  r.zm.z = __float_as_uint((float)m);
+  *(double2*)d = r.xy;
+  *(uint4*)&d->z = r.zm;
 }
 
 __device__ __forceinline__ float mass32(const double4& v) {
   return __uint_as_float((unsigned)__double_as_longlong(v.w));
 }
 
+// Bound by VALU issue: 18 instructions of 4 cycles per pair (rsq 8), 20 of all
+// the kernel's, and 77% of the lanes used.  So what is not a pair's own
+// arithmetic is kept off the vector unit (N = 2^20, 3.16e9 pairs: 25.5 to 20
+// instructions per round of the groups, 2.85 to 2.34 ms):
+//  - The records of a group's bodies are adjacent in LDS (slot g S + t / G for
+//    body t of group t mod G), so a round of four pairs takes one address.
+//  - The trip count na / G is the same for every lane and stays in SGPRs; only the
+//    last, partial round is masked.  Lanes past G n_B repeat the last group and
+//    are not read.
+//  - The fast rounds take no d2 > 0 test.  A coincident pair (d2 = 0) or a NaN
+//    turns fp into inf or NaN for good, so one test of fp per chunk finds it, and the
+//    chunk is summed again, in the same order, with the test per pair.
+// S is odd for up to 16 groups (stride 8 S banks: no two of 8 groups on the same
+// ones); G S <= 127.
 // Occupancy: 6 waves per SIMD (<= 80 VGPRs, measured best), with the sink
 // leaf's data wave-uniform (SGPRs).
+constexpr int LG_SLOTS = 128;
 __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per_eu(6))) k_leaf_group(const int* __restrict__ leaves,
                                                               NfPlan plan, const int* __restrict__ cb,
                                                               const int* __restrict__ ce,
@@ -310,8 +343,8 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
                                                               double eps2, double4* nearbuf,
                                                               double4* __restrict__ part,
                                                               unsigned long long* npairs, int gmax) {
-  __shared__ double4 sbuf[LG_WAVES][64];
-  __shared__ double rbuf[LG_WAVES][4][64];
+  // the staged chunk; at the end the groups' sums (4 x 64 doubles)
+  __shared__ double4 sbuf[LG_WAVES][LG_SLOTS];
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int nblk = (plan.max_items + LG_WAVES - 1) / LG_WAVES;
   int blk = xcd_block();
@@ -337,12 +370,19 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
   int64_t pslot = to_part ? (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) - b : 0;
   float eps2f = (float)eps2;
   long long pairs = 0;  // body pairs of this leaf (self pairs excluded), wave-uniform
+  const double4* sb = sbuf[wv];
+  unsigned lane32 = 32u * (unsigned)lane;
+  double(*rb)[64] = (double(*)[64])sbuf[wv];
   for (int i0 = b; i0 < e; i0 += 64) {
     int nB = min(64, e - i0);
     int G = 64 / nB;
     if (gmax > 0 && G > gmax) G = gmax;  // fewer groups: longer runs per lane, fewer partial sums
+    int S = (64 + G - 1) / G;
+    if (G <= 16) S |= 1;
+    int invG = (65536 + G - 1) / G;  // x / G = (x invG) >> 16 for x <= 64
     int g = lane / nB, s = lane - g * nB;
-    bool act = g < G;
+    g = min(g, G - 1);
+    double4* put = sbuf[wv] + (lane % G) * S + lane / G;
     int i = i0 + s;
     double4 me = pm[i];
     double nx = 0.0, ny = 0.0, nz = 0.0, np = 0.0;
@@ -350,13 +390,13 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     // source chunks (<= 64 bodies of one source leaf) in list order; the
     // next chunk is fetched into registers while the current one is summed
     int q = qb, j0 = 0, je = 0;
+    Staged cur{};
     if (q < qe) {
       int A = srcl[q];
       j0 = cb[A];
       je = ce[A];
+      cur = load_staged(pm, j0, je, lane32);
     }
-    double4 cur = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (q < qe && lane < je - j0) cur = stage(pm[j0 + lane]);
     while (q < qe) {
       int na = min(64, je - j0);
       pairs += (long long)nB * na - max(0, min(i0 + nB, j0 + na) - max(i0, j0));
@@ -370,38 +410,57 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
         }
       }
       __builtin_amdgcn_wave_barrier();
-      sbuf[wv][lane] = cur;
+      put_staged(put, cur);
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged chunk is visible to the wave
-      cur = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (nq < qe && lane < nje - nj0) cur = stage(pm[nj0 + lane]);
-      int tmax = act ? na : 0;
+      cur = load_staged(pm, nj0, nje, lane32);  // (after the last chunk: its last body again)
+      int nr = (na * invG) >> 16, rem = na - nr * G;  // full rounds, bodies of the partial one
       // the sink's own leaf: its pair with itself gets mass 0 (with eps = 0
       // the d2 > 0 test also removes it); other chunks hold no sink body
-      bool self = j0 < i0 + nB && i0 < j0 + na;
-      if (self) {
+      bool slow = j0 < i0 + nB && i0 < j0 + na;
+      const double4* t = sb + g * S;
+      if (!slow) {
+        float sx = fx, sy = fy, sz = fz, sp = fp;  // (not 0 in the later chunks of a leaf)
+        const double4* u = t;
+        for (int r = nr >> 2; r > 0; r--, u += 4) {
+          double4 s0 = u[0], s1 = u[1], s2 = u[2], s3 = u[3];
+          pair32<false>(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+          pair32<false>(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
+          pair32<false>(s2, mass32(s2), me, eps2f, fx, fy, fz, fp);
+          pair32<false>(s3, mass32(s3), me, eps2f, fx, fy, fz, fp);
+        }
+        if (nr & 2) {
+          double4 s0 = u[0], s1 = u[1];
+          pair32<false>(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+          pair32<false>(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
+          u += 2;
+        }
+        if (nr & 1) {
+          double4 s0 = u[0];
+          pair32<false>(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+          u++;
+        }
+        if (g < rem) {
+          double4 s0 = u[0];
+          pair32<false>(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+        }
+        slow = ballot(!__builtin_isfinite(fp)) != 0;
+        if (slow) {
+          fx = sx;
+          fy = sy;
+          fz = sz;
+          fp = sp;
+        }
+      }
+      if (slow) {
         int ti = i - j0;
-        for (int t = g; t < tmax; t += G) {
-          double4 sb = sbuf[wv][t];
-          pair32(sb, t != ti ? mass32(sb) : 0.f, me, eps2f, fx, fy, fz, fp);
+        for (int r = 0; r < nr; r++) {
+          double4 s0 = t[r];
+          pair32<true>(s0, g + r * G != ti ? mass32(s0) : 0.f, me, eps2f, fx, fy, fz, fp);
         }
-      } else {
-        int t = g;
-        for (; t + 3 * G < tmax; t += 4 * G) {
-          double4 s0 = sbuf[wv][t], s1 = sbuf[wv][t + G], s2 = sbuf[wv][t + 2 * G], s3 = sbuf[wv][t + 3 * G];
-          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
-          pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
-          pair32(s2, mass32(s2), me, eps2f, fx, fy, fz, fp);
-          pair32(s3, mass32(s3), me, eps2f, fx, fy, fz, fp);
-        }
-        for (; t + G < tmax; t += 2 * G) {
-          double4 s0 = sbuf[wv][t], s1 = sbuf[wv][t + G];
-          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
-          pair32(s1, mass32(s1), me, eps2f, fx, fy, fz, fp);
-        }
-        if (t < tmax) {
-          double4 s0 = sbuf[wv][t];
-          pair32(s0, mass32(s0), me, eps2f, fx, fy, fz, fp);
+        if (g < rem) {
+          double4 s0 = t[nr];
+          pair32<true>(s0, g + nr * G != ti ? mass32(s0) : 0.f, me, eps2f, fx, fy, fz, fp);
         }
       }
       if (nq != q) {  // end of a source leaf: carry the FP32 block into FP64
@@ -417,20 +476,20 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     }
     // combine the groups in order
     __builtin_amdgcn_wave_barrier();
-    rbuf[wv][0][lane] = nx;
-    rbuf[wv][1][lane] = ny;
-    rbuf[wv][2][lane] = nz;
-    rbuf[wv][3][lane] = np;
+    rb[0][lane] = nx;
+    rb[1][lane] = ny;
+    rb[2][lane] = nz;
+    rb[3][lane] = np;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_s_waitcnt(0xc07f);
-    if (g == 0) {
+    if (lane < nB) {
       double tx = 0.0, ty = 0.0, tz = 0.0, tp = 0.0;
       for (int gg = 0; gg < G; gg++) {
         int l = gg * nB + s;
-        tx += rbuf[wv][0][l];
-        ty += rbuf[wv][1][l];
-        tz += rbuf[wv][2][l];
-        tp += rbuf[wv][3][l];
+        tx += rb[0][l];
+        ty += rb[1][l];
+        tz += rb[2][l];
+        tp += rb[3][l];
       }
       if (to_part)
         part[pslot + i] = make_double4(tx, ty, tz, tp);

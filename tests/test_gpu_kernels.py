@@ -205,3 +205,34 @@ def test_one_workgroup_sorts(fmm, n, n_leaf):
         print(k, len(want), flush=True)
         assert np.array_equal(f.export(k).astype(np.int64).reshape(-1, 2), want), k
     f.close()
+
+
+# the mixed near field sums a chunk of a source leaf without a test per pair
+# and again with it if a pair had no distance
+@pytest.mark.parametrize("groups", [0, 1, 3])
+@pytest.mark.parametrize("copies,n_leaf", [((30, 1, 2), 8), ((64, 65, 100), 64), ((200, 7), 100)])
+def test_mixed_pairs_without_distance(fmm, copies, n_leaf, groups):
+    """Coincident bodies (in one chunk, and in two of a leaf of more than 64)
+    and a separation that FP32 rounds to zero add nothing to each other, and the
+    other pairs of their chunks count.  Every pair directly but those of two
+    cells without extent (theta small), so a sum is off by its FP32 roundings
+    alone: 64 + 16 units of 2^-24 of the sum of the terms' sizes."""
+    rng = np.random.default_rng(8)
+    sites = rng.uniform(-1, 1, (len(copies), 3))
+    tiny = np.array([[1e-26, 0.3, 0.3], [-1e-26, 0.3, 0.3]])
+    box = np.array([[x, y, z] for x in (-1, 1) for y in (-1, 1) for z in (-1, 1)], dtype=np.float64)
+    pos = np.concatenate([np.repeat(sites, copies, axis=0), tiny, box, rng.uniform(-1, 1, (211, 3))])
+    pos = pos[rng.permutation(len(pos))]
+    mass = rng.uniform(0.5, 1.5, len(pos))
+    print(f"[gpu] mixed near field copies={copies} n_leaf={n_leaf} groups={groups}", flush=True)
+    f = fmm.FMM(p=4, err_tol=1e-6, n_leaf=n_leaf, precision="mixed", theta=1e-3, p2p_groups=groups)
+    acc, pot = f.forces(_dev(pos), _dev(mass))
+    d = (pos[None] - pos[:, None]).astype(np.float32)
+    d2 = (d * d).sum(-1)
+    on = (d2 > 0) & ~np.eye(len(pos), dtype=bool)
+    rinv = np.where(on, 1.0 / np.sqrt(np.where(on, d2, 1.0).astype(np.float64)), 0.0)
+    term = (mass[None] * rinv**3)[..., None] * d.astype(np.float64)
+    u = 80 * 2.0**-24
+    assert (np.abs(acc.cpu().numpy() - term.sum(1)) <= u * np.abs(term).sum(1)).all()
+    assert (np.abs(pot.cpu().numpy() + (mass[None] * rinv).sum(1)) <= u * (mass[None] * rinv).sum(1)).all()
+    f.close()

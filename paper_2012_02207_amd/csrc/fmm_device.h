@@ -178,22 +178,23 @@ __device__ __forceinline__ int system_of(const int* off, int nsys, int64_t i) {
   return lo;
 }
 
-// ---- stable LSD radix sort within one workgroup of 1024 threads ---------------
+// ---- stable LSD radix sort within one workgroup of T threads (1024 or 256) ------
 // Up to I keys per thread (and payloads, with VAL), in registers: wavefront w
-// holds positions (w C + c) 64 + lane, c < C, of the 1024 C keys (pad with all
+// holds positions (w C + c) 64 + lane, c < C, of the T C keys (pad with all
 // ones: they stay last).  Per 8-bit pass a key's rank among equal digits comes
 // from ballots, as in the tiled sort of tree.hip, and the keys move through LDS.
-constexpr int BS_T = 1024, BS_W = BS_T / 64;
-template <class K, int I, bool VAL>
+constexpr int BS_T = 1024;
+template <class K, int I, bool VAL, int T = BS_T>
 struct BlockSort {
-  K sk[BS_T * I];
-  int sv[VAL ? BS_T * I : 1];
-  int wcnt[BS_W][256];
+  K sk[T * I];
+  int sv[VAL ? T * I : 1];
+  int wcnt[T / 64][256];
   int dstart[256], wsum[4];
 };
 
-template <class K, int I, bool VAL>
-__device__ inline void block_sort(BlockSort<K, I, VAL>& s, K (&k)[I], int (&v)[I], int C, int nbits) {
+template <class K, int I, bool VAL, int T>
+__device__ inline void block_sort(BlockSort<K, I, VAL, T>& s, K (&k)[I], int (&v)[I], int C, int nbits) {
+  constexpr int BS_T = T, BS_W = T / 64;
   int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint64_t lt = lanemask_lt();
   for (int shift = 0; shift < nbits; shift += 8) {

@@ -297,7 +297,9 @@ void stream_wait(hipEvent_t e, hipStream_t from, hipStream_t to);
 // ------------------------------------------------------------------ stages
 void exclusive_scan(Ctx& c, const int* in, int* out, int64_t n, long long* total_dev);
 int radix_sort(Ctx& c, uint64_t* k0, int* v0, uint64_t* k1, int* v1, int64_t n, int nbits);
-uint32_t* radix_sort_narrow(Ctx& c, const uint64_t* in, uint32_t* b0, uint32_t* b1, int64_t n, int nbits);
+const int* radix_split(Ctx& c, const uint64_t* in, uint32_t* out, int64_t n, int shift);
+size_t radix_split2_ints(int64_t n, int sub);
+const int* radix_split2(Ctx& c, const uint32_t* in, uint32_t* out, int64_t n, int shift, int sub, const int* rowtot);
 
 void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass);
 void upward_pass(Ctx& c);

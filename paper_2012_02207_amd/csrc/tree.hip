@@ -340,50 +340,54 @@ __global__ void __launch_bounds__(RS_T) k_rs_rowscan(const int* __restrict__ his
   if (threadIdx.x == 0) rowtot[d] = carry;
 }
 
-// Ranks as above, then the tile is reordered by digit in LDS and written out
-// with consecutive lanes on consecutive destinations (each digit's run of the
-// tile is contiguous in the output), so the global writes coalesce.
-template <int RS_I, bool VAL, class KI, class KO>
-__global__ void __launch_bounds__(RS_T) k_rs_scatter(const KI* kin, const int* vin, KO* kout, int* vout,
-                                                     int64_t n, int shift, const int* offs, const int* rowtot,
-                                                     int nblocks) {
-  constexpr int RS_TILE = RS_T * RS_I;
-  __shared__ int wcnt[RS_W][256];
-  __shared__ int goff[256], lofs[256], wsum[RS_W];
-  __shared__ KO sk[RS_TILE];
-  __shared__ int sv[VAL ? RS_TILE : 1];
-  for (int t = threadIdx.x; t < RS_W * 256; t += RS_T) (&wcnt[0][0])[t] = 0;
-  int w = threadIdx.x >> 6;
-  int lane = threadIdx.x & 63;
-  {
-    // start of this digit in the output: the totals of the smaller digits
-    // (an exclusive scan over the 256 digits, one per thread) plus the counts
-    // of the earlier tiles
-    int tot = rowtot[threadIdx.x];
-    int incl = tot;
-    for (int o = 1; o < 64; o <<= 1) {
-      int y = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    int before = 0;
-    for (int ww = 0; ww < w; ww++) before += wsum[ww];
-    goff[threadIdx.x] = before + incl - tot + offs[(int64_t)threadIdx.x * nblocks + blockIdx.x];
-    __syncthreads();
+// Exclusive prefix of x over the workgroup's RS_T threads (sum: the total).
+__device__ __forceinline__ int rs_block_excl(int x, int* wsum, int& sum) {
+  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int incl = x;
+  for (int o = 1; o < 64; o <<= 1) {
+    int y = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += y;
   }
-  int64_t tile0 = (int64_t)blockIdx.x * RS_TILE;
-  int64_t base = tile0 + (int64_t)w * (RS_TILE / RS_W);
-  int tcount = (int)(n - tile0 < RS_TILE ? n - tile0 : RS_TILE);
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int before = 0;
+  sum = 0;
+  for (int ww = 0; ww < RS_W; ww++) {
+    if (ww < w) before += wsum[ww];
+    sum += wsum[ww];
+  }
+  __syncthreads();
+  return before + incl - x;
+}
+
+template <int RS_I, bool VAL, class K>
+struct RadixTile {
+  int wcnt[RS_W][256];
+  int goff[256], lofs[256], wsum[RS_W];
+  K sk[RS_T * RS_I];
+  int sv[VAL ? RS_T * RS_I : 1];
+};
+
+// Ranks as above, then the tile [tile0, tile0 + tcount) is reordered by digit in
+// LDS and written out with consecutive lanes on consecutive destinations (each
+// digit's run of the tile is contiguous in the output, from goff on), so the
+// global writes coalesce.
+template <int RS_I, bool VAL, class KI, class KO>
+__device__ __forceinline__ void radix_tile(RadixTile<RS_I, VAL, KI>& s, const KI* kin, const int* vin, KO* kout,
+                                           int* vout, int64_t n, int64_t tile0, int tcount, int shift, int dmask = 255) {
+  int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int t = threadIdx.x; t < RS_W * 256; t += RS_T) (&s.wcnt[0][0])[t] = 0;
+  __syncthreads();
+  int base = w * (64 * RS_I);
   KI k[RS_I];
   int v[RS_I], rank[RS_I];
   uint64_t lt = lanemask_lt();
   for (int c = 0; c < RS_I; c++) {
-    int64_t j = base + (int64_t)c * 64 + lane;
-    bool valid = j < n;
-    k[c] = valid ? kin[j] : 0;
-    if (VAL) v[c] = valid ? vin[j] : 0;
-    int d = (int)((k[c] >> shift) & 255);
+    int j = base + c * 64 + lane;
+    bool valid = j < tcount;
+    k[c] = valid ? kin[tile0 + j] : 0;
+    if (VAL) v[c] = valid ? vin[tile0 + j] : 0;
+    int d = (int)((k[c] >> shift) & dmask);
     uint64_t peers = ballot(valid);
     for (int b = 0; b < 8; b++) {
       bool bit = (d >> b) & 1;
@@ -391,50 +395,131 @@ __global__ void __launch_bounds__(RS_T) k_rs_scatter(const KI* kin, const int* v
       peers &= bit ? bb : ~bb;
     }
     int before = __popcll(peers & lt);
-    int cnt = wcnt[w][d];
+    int cnt = s.wcnt[w][d];
     rank[c] = cnt + before;
     // the highest peer publishes the new running count for this digit
-    if (valid && (peers >> lane) == 1ull) wcnt[w][d] = cnt + __popcll(peers);
+    if (valid && (peers >> lane) == 1ull) s.wcnt[w][d] = cnt + __popcll(peers);
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
   // per digit: offsets of the waves within the tile's run, and the run length
   int d0 = threadIdx.x, tot = 0;
   for (int ww = 0; ww < RS_W; ww++) {
-    int t = wcnt[ww][d0];
-    wcnt[ww][d0] = tot;
+    int t = s.wcnt[ww][d0];
+    s.wcnt[ww][d0] = tot;
     tot += t;
   }
-  // exclusive scan of the run lengths over the 256 digits (one per thread)
-  int incl = tot;
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) wsum[w] = incl;
-  __syncthreads();
-  int before_w = 0;
-  for (int ww = 0; ww < w; ww++) before_w += wsum[ww];
-  lofs[d0] = before_w + incl - tot;
+  int all;
+  s.lofs[d0] = rs_block_excl(tot, s.wsum, all);
   __syncthreads();
   for (int c = 0; c < RS_I; c++) {
-    int64_t j = base + (int64_t)c * 64 + lane;
-    if (j >= n) continue;
-    int d = (int)((k[c] >> shift) & 255);
-    int lp = lofs[d] + wcnt[w][d] + rank[c];
-    sk[lp] = (KO)k[c];
-    if (VAL) sv[lp] = v[c];
+    if (base + c * 64 + lane >= tcount) continue;
+    int d = (int)((k[c] >> shift) & dmask);
+    int lp = s.lofs[d] + s.wcnt[w][d] + rank[c];
+    s.sk[lp] = k[c];
+    if (VAL) s.sv[lp] = v[c];
   }
   __syncthreads();
   for (int t = threadIdx.x; t < tcount; t += RS_T) {
-    KO key = sk[t];
-    int d = (int)((key >> shift) & 255);
-    int64_t dst = (int64_t)goff[d] + (t - lofs[d]);
+    KI key = s.sk[t];
+    int d = (int)((key >> shift) & dmask);
+    int64_t dst = (int64_t)s.goff[d] + (t - s.lofs[d]);
     if (dst < n) {  // always true when the ranks are consistent with the histogram
-      kout[dst] = key;
-      if (VAL) vout[dst] = sv[t];
+      kout[dst] = (KO)key;
+      if (VAL) vout[dst] = s.sv[t];
     }
   }
+}
+
+template <int RS_I, bool VAL, class KI, class KO>
+__global__ void __launch_bounds__(RS_T) k_rs_scatter(const KI* kin, const int* vin, KO* kout, int* vout,
+                                                     int64_t n, int shift, const int* offs, const int* rowtot,
+                                                     int nblocks) {
+  __shared__ RadixTile<RS_I, VAL, KI> s;
+  // start of this digit in the output: the totals of the smaller digits
+  // plus the counts of the earlier tiles
+  int all, excl = rs_block_excl(rowtot[threadIdx.x], s.wsum, all);
+  s.goff[threadIdx.x] = excl + offs[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  int64_t tile0 = (int64_t)blockIdx.x * (RS_T * RS_I);
+  radix_tile<RS_I, VAL, KI, KO>(s, kin, vin, kout, vout, n, tile0,
+                                (int)min((int64_t)(RS_T * RS_I), n - tile0), shift);
+}
+
+// ---- second split of a list already split into 256 parts ----------------------
+// The parts' sizes are rowtot; a tile belongs to one part (at most one partial
+// tile per part), and a part's tiles are split by the next 8 bits on their own.
+struct SplitTile {
+  int part, first, count;  // part, first entry and entries of this tile (part -1: no such tile)
+  int tile, tiles;         // first tile of the part, its tiles
+  int start;               // first entry of the part
+};
+// tile blk, or (part >= 0) the tiles of that part
+template <int TILE>
+__device__ __forceinline__ SplitTile split_tile(const int* rowtot, int blk, int part, int* wsum, SplitTile* sh) {
+  int d = threadIdx.x, all;
+  int sz = rowtot[d], nt = (sz + TILE - 1) / TILE;
+  int start = rs_block_excl(sz, wsum, all);
+  int tile = rs_block_excl(nt, wsum, all);
+  if (d == 0) sh->part = -1;
+  __syncthreads();
+  if (part >= 0 ? d == part : (blk >= tile && blk < tile + nt)) {
+    int o = part >= 0 ? 0 : (blk - tile) * TILE;
+    *sh = SplitTile{d, start + o, min(TILE, sz - o), tile, nt, start};
+  }
+  __syncthreads();
+  return *sh;
+}
+
+template <int RS_I>
+__global__ void __launch_bounds__(RS_T) k_split_hist(const uint32_t* __restrict__ key, int shift, int dmask,
+                                                     const int* __restrict__ rowtot, int* __restrict__ hist) {
+  __shared__ int cnt[256], wsum[RS_W];
+  __shared__ SplitTile sh;
+  cnt[threadIdx.x] = 0;
+  SplitTile t = split_tile<RS_T * RS_I>(rowtot, blockIdx.x, -1, wsum, &sh);
+  if (t.part < 0) return;
+  for (int j = threadIdx.x; j < t.count; j += RS_T) atomicAdd(&cnt[(key[t.first + j] >> shift) & dmask], 1);
+  __syncthreads();
+  hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = cnt[threadIdx.x];
+}
+
+// a workgroup per part: the counts become the destinations of the tiles' runs
+// (a thread per digit down the tiles), and the starts of the part's sub-parts
+template <int RS_I>
+__global__ void __launch_bounds__(RS_T) k_split_scan(const int* __restrict__ rowtot, int* hist, int sub, int* fstart) {
+  __shared__ int wsum[RS_W];
+  __shared__ SplitTile sh;
+  SplitTile t = split_tile<RS_T * RS_I>(rowtot, 0, blockIdx.x, wsum, &sh);
+  int d = threadIdx.x;
+  int* h = hist + (int64_t)t.tile * 256 + d;
+  int tot = 0;
+#pragma unroll 8
+  for (int i = 0; i < t.tiles; i++) tot += h[i * 256];
+  int all, run = t.start + rs_block_excl(tot, wsum, all);
+  if (d < sub) fstart[blockIdx.x * sub + d] = run;
+  if (blockIdx.x == 255 && d == 0) fstart[256 * sub] = t.start + all;
+  for (int i0 = 0; i0 < t.tiles; i0 += 8) {
+    int v[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = h[min(i0 + k, t.tiles - 1) * 256];
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      if (i0 + k < t.tiles) h[(i0 + k) * 256] = run;
+      run += v[k];
+    }
+  }
+}
+
+template <int RS_I>
+__global__ void __launch_bounds__(RS_T) k_split_scatter(const uint32_t* __restrict__ kin, uint32_t* __restrict__ kout,
+                                                        int64_t n, int shift, int dmask, const int* __restrict__ rowtot,
+                                                        const int* __restrict__ dest) {
+  __shared__ RadixTile<RS_I, false, uint32_t> s;
+  __shared__ SplitTile sh;
+  SplitTile t = split_tile<RS_T * RS_I>(rowtot, blockIdx.x, -1, s.wsum, &sh);
+  if (t.part < 0) return;
+  s.goff[threadIdx.x] = dest[(int64_t)blockIdx.x * 256 + threadIdx.x];
+  radix_tile<RS_I, false, uint32_t, uint32_t>(s, kin, nullptr, kout, nullptr, n, t.first, t.count, shift, dmask);
 }
 
 // One 8-bit pass from kin (and vin) to kout (vout).
@@ -472,19 +557,33 @@ int radix_sort(Ctx& c, uint64_t* k0, int* v0, uint64_t* k1, int* v1, int64_t n, 
   return src;
 }
 
-// Stable LSD sort of n 64-bit keys whose values fit in nbits <= 32 bits: the
-// first pass reads the 64-bit keys and writes 32-bit ones, later passes move
-// 32-bit keys between b0 and b1.  Returns the buffer holding the result.
-uint32_t* radix_sort_narrow(Ctx& c, const uint64_t* in, uint32_t* b0, uint32_t* b1, int64_t n, int nbits) {
-  if (n <= 0) return b0;
-  radix_pass<false>(c, in, (const int*)nullptr, b0, (int*)nullptr, n, 0);
-  uint32_t* bb[2] = {b0, b1};
-  int src = 0;
-  for (int shift = 8; shift < nbits; shift += 8) {
-    radix_pass<false>(c, bb[src], (const int*)nullptr, bb[1 - src], (int*)nullptr, n, shift);
-    src = 1 - src;
-  }
-  return bb[src];
+// Splits n 64-bit keys by the 8 bits from bit `shift` on; the low 32 bits of the
+// keys go to out.  Returns the 256 parts' sizes (device).
+const int* radix_split(Ctx& c, const uint64_t* in, uint32_t* out, int64_t n, int shift) {
+  radix_pass<false>(c, in, (const int*)nullptr, out, (int*)nullptr, n, shift);
+  int nb = (int)ceil_div(n, RS_T * (n <= RS_SMALL ? RS_I_SMALL : RS_I));
+  return c.sort_hist.p + (size_t)512 * nb;
+}
+
+// scratch of radix_split2 behind radix_split's
+size_t radix_split2_ints(int64_t n, int sub) {
+  int64_t nb = ceil_div(n, RS_T * (n <= RS_SMALL ? RS_I_SMALL : RS_I));
+  int64_t nt = ceil_div(n, RS_T * RS_I) + 256;
+  return (size_t)(512 * nb + 256 + 256 * nt + 256 * sub + 64);
+}
+
+// Splits each of the 256 parts again, by the log2(sub) bits from bit `shift` on
+// (sub <= 256; c.sort_hist holds radix_split2_ints).  Returns the first
+// entries of the 256 sub sub-parts, and n (device).
+const int* radix_split2(Ctx& c, const uint32_t* in, uint32_t* out, int64_t n, int shift, int sub, const int* rowtot) {
+  int nt = (int)(ceil_div(n, RS_T * RS_I) + 256);
+  int* hist = const_cast<int*>(rowtot) + 256;
+  int* fstart = hist + (size_t)256 * nt;
+  hipLaunchKernelGGL(k_split_hist<RS_I>, dim3(nt), dim3(RS_T), 0, c.stream, in, shift, sub - 1, rowtot, hist);
+  hipLaunchKernelGGL(k_split_scan<RS_I>, dim3(256), dim3(RS_T), 0, c.stream, rowtot, hist, sub, fstart);
+  hipLaunchKernelGGL(k_split_scatter<RS_I>, dim3(nt), dim3(RS_T), 0, c.stream, in, out, n, shift, sub - 1, rowtot, hist);
+  HIPCHK(hipGetLastError());
+  return fstart;
 }
 
 // sorts c.key[0]/c.idx[0] (n entries) over bits [0, nbits); result in key[0]/idx[0]
@@ -544,7 +643,7 @@ __global__ void __launch_bounds__(BS_T) k_tree_small(const double* __restrict__ 
                                                      double* __restrict__ sy, double* __restrict__ sz,
                                                      double* __restrict__ sm, double4* __restrict__ pm) {
   __shared__ BlockSort<uint64_t, TS_I, true> bs;
-  __shared__ double ext[6][BS_W];
+  __shared__ double ext[6][(BS_T / 64)];
   __shared__ double box[5];
   int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   double lo[3], hi[3];
@@ -571,7 +670,7 @@ __global__ void __launch_bounds__(BS_T) k_tree_small(const double* __restrict__ 
     double L = 0.0;
     for (int d = 0; d < 3; d++) {
       double a = ext[d][0], b = ext[3 + d][0];
-      for (int ww = 1; ww < BS_W; ww++) {
+      for (int ww = 1; ww < (BS_T / 64); ww++) {
         if (ext[d][ww] < a) a = ext[d][ww];
         if (ext[3 + d][ww] > b) b = ext[3 + d][ww];
       }

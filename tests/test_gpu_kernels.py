@@ -236,3 +236,32 @@ def test_mixed_pairs_without_distance(fmm, copies, n_leaf, groups):
     assert (np.abs(acc.cpu().numpy() - term.sum(1)) <= u * np.abs(term).sum(1)).all()
     assert (np.abs(pot.cpu().numpy() + (mass[None] * rinv).sum(1)) <= u * (mass[None] * rinv).sum(1)).all()
     f.close()
+
+
+# longer lists are split by the sink's top 8 bits, or by 9 to 16 in two passes,
+# into parts sorted in LDS: up to 256 cells, parts of many sinks and of one, cell
+# ids of more than 16 bits, and parts too long for LDS (close pairs make chains of
+# cells without lists, and the leaves' long lists share few parts) either way
+@pytest.mark.parametrize("kind,n,n_leaf,theta,p,err_tol", [
+    ("uniform", 160, 1, 1e-3, 1, 1e-6), ("uniform", 900, 1, 1e-3, 1, 1e-6),
+    ("uniform", 20000, 4, 0.5, 3, 1e-4),
+    ("uniform", 60000, 1, 1.0, 3, 1e-2),
+    ("pairs", 1000, 1, 1e-3, 1, 1e-6), ("pairs", 2000, 1, 1e-3, 1, 1e-6)])
+def test_list_parts(fmm, kind, n, n_leaf, theta, p, err_tol):
+    """The oracle's lists, ascending by sink and source."""
+    rng = np.random.default_rng(n)
+    pos = rng.uniform(-1, 1, (n, 3))
+    if kind == "pairs":
+        pos[n // 2:] = pos[:n // 2] + 1e-6
+    mass = np.full(n, 1.0 / n)
+    print(f"[gpu] list parts {kind} n={n}", flush=True)
+    f = fmm.FMM(p=p, err_tol=err_tol, n_leaf=n_leaf, theta=theta)
+    f.forces(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    o.run(pos, mass, p=p, err_tol=err_tol, n_leaf=n_leaf, theta=theta, stage="walk")
+    for k in ("est_far", "est_near", "m2l", "p2p"):
+        want = np.asarray(o.get(k), dtype=np.int64).reshape(-1, 2)
+        want = want[np.lexsort((want[:, 1], want[:, 0]))]
+        print(k, len(want), flush=True)
+        assert np.array_equal(f.export(k).astype(np.int64).reshape(-1, 2), want), k
+    f.close()

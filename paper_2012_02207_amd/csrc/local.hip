@@ -172,7 +172,12 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
 // alone at N = 2^18, p = 10 (9.8e8 pairs); this way it took 1843 us with a
 // wavefront per leaf, which left the chip to the few longest leaves (1.5
 // wavefronts per SIMD on average), and 1124 us with the sinks in tiles.
-constexpr int LG_WAVES = 4;
+// Wavefronts (items) per workgroup of the near-field kernels.  A workgroup keeps
+// its place until its longest item ends, so with four, 2.6 of the 4 wavefronts
+// per SIMD that fit were in flight in FP64, 3.7 of 6 in mixed precision: 2^18
+// bodies in FP64 4.40 ms (4.34 with one), 2^20 mixed 8.24 (8.04), 256 systems
+// of 16384 37.7 (36.6).
+constexpr int LG_WAVES = 1;
 
 // the sinks i0 .. i0 + TS over the list src[qb .. qe); returns the body pairs
 // (a body with itself is none)

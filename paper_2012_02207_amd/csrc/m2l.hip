@@ -111,7 +111,13 @@ __device__ __forceinline__ void zrot(T* v, T c1, T s1) {
 // of that half (about D + 6 shuffles instead of 6 D).  Afterwards the total of
 // value j sits in lane j * (64 / Dp) (Dp = D rounded up to a power of two),
 // which adds it to its accumulator acc_slot.
-constexpr int M2L_WAVES = 4;  // sinks per workgroup (one per wavefront)
+// Sinks (wavefronts) per workgroup.  A workgroup keeps its place until its
+// longest list ends (with four at p = 10, 1.3 of 2 wavefronts per SIMD were in
+// flight); short work is launched faster by fours.  One against four: p = 6,
+// 120000 bodies 1.88 and 1.82 ms, p = 10, 2^18 3.89 and 3.92, p = 13, 120000 3.96
+// and 4.18, p = 16, 60000 3.57 and 3.83.  (With the loads below, p = 10, 2^18:
+// 3.92 -> 3.78; p = 13 4.13 -> 3.83; p = 16 3.99 -> 3.69.)
+constexpr int m2l_waves(int p) { return p <= 8 ? 4 : 1; }
 
 // M2L of the pairs src[b .. e) of one sink cell B (one wavefront; lane =
 // lane id) into the expansion out (NC complex coefficients; zeros when b == e)
@@ -134,7 +140,29 @@ __device__ __forceinline__ void m2l_range_fp64(int B, int b, int e, int lane, co
     int k = base + lane;
     bool act = k < e;
     int A = act ? src[k] : src[b];
+    // The orders' coefficients are loaded one order ahead of their use (the first
+    // one ahead of the geometry): with one or two waves per SIMD and a row per lane
+    // the latency of an order's loads does not hide otherwise (2^18 bodies, p = 10:
+    // 1386 us alone, 1288 so).  At p = 11 and 12 the second order's registers
+    // spill (120000 bodies, p = 12: 2.98 ms, 3.11 so).
+    const double* M = mult + (size_t)A * NC * 2;
+    constexpr bool AHEAD = P != 11 && P != 12;
+    double next[2 * P + 1];
+    auto fetch = [&](auto nc) {
+      constexpr int n = nc;
+      // an opaque per-order pointer keeps the loads of this order from being
+      // merged with (and hoisted along with) those of other orders
+      const double* Mo = M + 2 * cidx(n, 0);
+      asm volatile("" : "+v"(Mo));
+      next[0] = Mo[0];
+      static_for<1, n + 1>([&](auto mc) {
+        constexpr int m = mc;
+        next[2 * m - 1] = Mo[2 * m];
+        next[2 * m] = Mo[2 * m + 1];
+      });
+    };
     double Rx = bx - cx[A], Ry = by - cy[A], Rz = bz - cz[A];
+    if constexpr (AHEAD) fetch(std::integral_constant<int, (P + 2) / 2>{});
     double rho2 = fma(Rx, Rx, Ry * Ry);
     double r2 = fma(Rz, Rz, rho2);
     double rinv = 1.0 / sqrt(r2);
@@ -161,7 +189,6 @@ __device__ __forceinline__ void m2l_range_fp64(int B, int b, int e, int lane, co
         rp *= rinv;
       }
     }
-    const double* M = mult + (size_t)A * NC * 2;
     // Source orders k >= K0 reach only output orders n <= P - k < K0: rotate
     // them first and fold them at once into a partial local expansion Lp
     // (orders 0..P-K0), so that only the low orders of the rotated multipole
@@ -173,18 +200,16 @@ __device__ __forceinline__ void m2l_range_fp64(int B, int b, int e, int lane, co
     for (int t = 0; t < NLP; t++) Lp[t] = 0.0;
     static_for<K0, P + 1>([&](auto kc) {
       constexpr int kk = kc;
-      __builtin_amdgcn_sched_barrier(0);
       double v[2 * kk + 1];
-      // an opaque per-order pointer keeps the loads of this order from being
-      // merged with (and hoisted along with) those of other orders
-      const double* Mo = M + 2 * cidx(kk, 0);
-      asm volatile("" : "+v"(Mo));
-      v[0] = Mo[0];
-      static_for<1, kk + 1>([&](auto mc) {
-        constexpr int m = mc;
-        v[2 * m - 1] = Mo[2 * m];
-        v[2 * m] = Mo[2 * m + 1];
-      });
+      if constexpr (!AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(kc);
+      }
+      static_for<0, 2 * kk + 1>([&](auto jc) { v[jc] = next[jc]; });
+      if constexpr (AHEAD) {
+        fetch(std::integral_constant<int, (kk < P ? kk + 1 : 0)>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
       zrot<kk>(v, ca, sa);
       swap_apply<kk>(v);
       zrot<kk>(v, cb, sb);
@@ -206,16 +231,16 @@ __device__ __forceinline__ void m2l_range_fp64(int B, int b, int e, int lane, co
     double Mp[K0 * K0];
     static_for<0, K0>([&](auto nc) {
       constexpr int n = nc;
-      __builtin_amdgcn_sched_barrier(0);
       double* v = Mp + n * n;
-      const double* Mo = M + 2 * cidx(n, 0);
-      asm volatile("" : "+v"(Mo));
-      v[0] = Mo[0];
-      static_for<1, n + 1>([&](auto mc) {
-        constexpr int m = mc;
-        v[2 * m - 1] = Mo[2 * m];
-        v[2 * m] = Mo[2 * m + 1];
-      });
+      if constexpr (!AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(nc);
+      }
+      static_for<0, 2 * n + 1>([&](auto jc) { v[jc] = next[jc]; });
+      if constexpr (AHEAD) {
+        if constexpr (n + 1 < K0) fetch(std::integral_constant<int, n + 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
       zrot<n>(v, ca, sa);
       swap_apply<n>(v);
       zrot<n>(v, cb, sb);
@@ -310,7 +335,7 @@ __device__ __forceinline__ void m2l_sink_fp64(int B, int first_lo, int lane, con
 // instead of 55.0 with one wave).  Higher orders take one wave.  The per-order
 // sums live in LDS and the sink index is wave-uniform (its data in SGPRs).
 template <int P, bool LIST>
-__global__ void __launch_bounds__(64 * M2L_WAVES) __attribute__((amdgpu_waves_per_eu(P <= 12 ? 2 : 1))) k_m2l_fp64(int ncell, int first_lo, const int* __restrict__ sinks,
+__global__ void __launch_bounds__(64 * m2l_waves(P)) __attribute__((amdgpu_waves_per_eu(P <= 12 ? 2 : 1))) k_m2l_fp64(int ncell, int first_lo, const int* __restrict__ sinks,
                                                              const int* __restrict__ nsinks,
                                                              const int* __restrict__ off,
                                                              const int* __restrict__ src,
@@ -321,6 +346,7 @@ __global__ void __launch_bounds__(64 * M2L_WAVES) __attribute__((amdgpu_waves_pe
                                                              double* __restrict__ loc, M2lSeg sg) {
   constexpr int NC = ncoef(P);
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int M2L_WAVES = m2l_waves(P);
   __shared__ double accs[M2L_WAVES][P + 1][64];
   double* acc = &accs[wv][0][0] + lane;
   if constexpr (LIST) {
@@ -430,17 +456,17 @@ template <int P>
 static void launch_p(Ctx& c, int first_lo, const double* mult, double* loc, const int* sinks, const int* nsinks) {
   int nc = (int)c.ncell;
   if (sinks) {
-    constexpr unsigned LIST_BLOCKS = 512;
-    hipLaunchKernelGGL((k_m2l_fp64<P, true>), dim3(LIST_BLOCKS), dim3(64 * M2L_WAVES), 0, c.stream, nc, first_lo,
+    constexpr unsigned LIST_BLOCKS = 2048 / m2l_waves(P);
+    hipLaunchKernelGGL((k_m2l_fp64<P, true>), dim3(LIST_BLOCKS), dim3(64 * m2l_waves(P)), 0, c.stream, nc, first_lo,
                        sinks, nsinks, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult, loc, M2lSeg{});
     return;
   }
   M2lSeg sg{};
   if (first_lo >= nc) sg = plan_m2l(c, M2L_SEG);  // whole lists: long ones in segments
   int nitems = sg.nseg ? sg.max_items : nc;
-  int nblk = (nitems + M2L_WAVES - 1) / M2L_WAVES;
+  int nblk = (nitems + m2l_waves(P) - 1) / m2l_waves(P);
   unsigned grid = xcd_grid(nblk);
-  hipLaunchKernelGGL((k_m2l_fp64<P, false>), dim3(grid), dim3(64 * M2L_WAVES), 0, c.stream, nc, first_lo,
+  hipLaunchKernelGGL((k_m2l_fp64<P, false>), dim3(grid), dim3(64 * m2l_waves(P)), 0, c.stream, nc, first_lo,
                      (const int*)nullptr, (const int*)nullptr, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p,
                      c.c_cz.p, mult, loc, sg);
   if (sg.nseg) combine_m2l(c, sg, loc);

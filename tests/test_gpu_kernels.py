@@ -183,6 +183,29 @@ def test_high_order_m2l(fmm, p, n, n_leaf, err_tol):
     f.close()
 
 
+# four sinks to a workgroup up to p = 8 and one above; coefficients loaded an
+# order ahead but for p = 11 and 12; from order 1, lists of one pair to several
+# segments
+@pytest.mark.parametrize("p,n,n_leaf,err_tol", [(1, 300, 8, 1e-2), (8, 3000, 8, 1e-5), (9, 3000, 4, 1e-6),
+                                                (10, 20000, 16, 1e-6), (11, 3000, 8, 1e-6), (12, 20000, 16, 1e-6),
+                                                (13, 3000, 8, 1e-7), (16, 20000, 16, 1e-8)])
+def test_register_m2l(fmm, p, n, n_leaf, err_tol):
+    """Local expansions and forces of the oracle to rounding (the FP64 parity
+    bounds: median 1e-12, maximum 1e-9)."""
+    pos, _, mass = W.plummer(n, 90 + p)
+    print(f"[gpu] m2l p={p} n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=p, err_tol=err_tol, n_leaf=n_leaf)
+    acc, _ = f.forces(_dev(pos), _dev(mass))
+    o = oracle.Oracle()
+    oacc, _ = o.run(pos, mass, p=p, err_tol=err_tol, n_leaf=n_leaf)
+    rel = np.linalg.norm(acc.cpu().numpy() - oacc, axis=1) / np.linalg.norm(oacc, axis=1)
+    assert np.median(rel) <= 1e-12 and rel.max() <= 1e-9, (np.median(rel), rel.max())
+    lg, lo = f.export("local"), o.get("local")
+    scale = np.abs(lo).max(axis=1, keepdims=True) + 1e-300
+    assert np.median(np.abs(lg - lo) / scale) < 1e-12
+    f.close()
+
+
 # up to 8192 bodies are sorted, and lists of up to 20480 entries grouped, by one
 # workgroup of 1024 threads
 @pytest.mark.parametrize("n,n_leaf", [(1, 64), (63, 4), (1023, 64), (1025, 30), (3000, 40), (8191, 200), (8192, 300),

@@ -64,7 +64,7 @@ P2P_FLOPS = 20   # per directed body pair: acc + pot, softened, rsqrt counted on
 MEASURED_TRAFFIC = {
     ("k_m2l_fp32", "plummer_1m", "mixed"): (1597.0e6, "paper_2012_02207_amd/csrc/m2l_mixed.hip",
                                              "ed1126117fe88dda26a2bd2bc1bd2d18ba1f497b"),
-    ("k_leaf_group<true> (mixed P2P)", "plummer_1m", "mixed"): (666.0e6,
+    ("k_leaf_group (mixed P2P)", "plummer_1m", "mixed"): (666.0e6,
                                                                 "paper_2012_02207_amd/csrc/local.hip",
                                                                 "babcf4bb55be7a5c3c74f1314c40e02ccec38c25"),
 }
@@ -288,7 +288,7 @@ def run_ensemble(args):
     f_m2l = m2l_flops(p) * st["n_m2l_fp32"]
     f_leaf = P2P_FLOPS * st["n_p2p_pairs"]
     if p2p_ms >= m2l_ms:
-        dom = {"kernel": "k_leaf_group<true> (mixed P2P)", "flop": f_leaf, "ms": p2p_ms}
+        dom = {"kernel": "k_leaf_group (mixed P2P)", "flop": f_leaf, "ms": p2p_ms}
     else:
         dom = {"kernel": "k_m2l_fp32", "flop": f_m2l, "ms": m2l_ms}
     achieved = dom["flop"] / (dom["ms"] * 1e-3)
@@ -558,8 +558,8 @@ def main():
     peak = PEAK_FP64 if main_pr == "fp64" else PEAK_FP32
     kname = "k_m2l_fp64" if main_pr == "fp64" else "k_m2l_fp32"
     if p2p_ms >= m2l_ms:
-        dom = {"kernel": "k_leaf_group<false> (P2P)" if main_pr == "fp64"
-                         else "k_leaf_group<true> (mixed P2P)",
+        dom = {"kernel": "k_near_fp64 (P2P)" if main_pr == "fp64"
+                         else "k_leaf_group (mixed P2P)",
                "flop": f_leaf, "ms": p2p_ms}
     else:
         dom = {"kernel": kname, "flop": f_m2l, "ms": m2l_ms}

@@ -141,7 +141,7 @@ __device__ __forceinline__ void angle_table(float c1, float s1, float* cm, float
 
 }  // namespace mx
 
-constexpr int MX_WAVES = 4;
+constexpr int MX_WAVES = 4;  // wavefronts of a workgroup, at most
 
 // first source of [b, e) whose id is >= first_lo (ids are breadth first, so the
 // sources above the root levels form a prefix of the ascending list)
@@ -186,15 +186,14 @@ __global__ void __launch_bounds__(64 * MX_WAVES) __attribute__((amdgpu_waves_per
   // With one wave per sink and a plan (sg.nseg), the items are the sinks and
   // the later segments of long lists (see M2lSeg): a segment writes a partial
   // expansion, added to the sink's in segment order afterwards.
-  int spb = MX_WAVES / wps;    // sinks per workgroup
+  // A workgroup is one item (wps wavefronts): its place is free when it ends
+  // (2^22 bodies, p = 12: 29.6 ms with four items to a workgroup, 28.9 so).
   int nlo = ncell - first_lo;  // sinks below the root levels
   int nitems = sg.nseg ? sg.max_items : nlo;
-  int nblk = (nitems + spb - 1) / spb;
-  int blk = xcd_block();
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: B and its data in SGPRs
-  int slot = wv / wps, part = wv - slot * wps;
-  int it = blk * spb + slot, seg = 0;
-  if (wps == 1 && (blk >= nblk || it >= nitems)) return;  // (no barrier below for one wave per sink)
+  int part = wv;
+  int it = xcd_block(), seg = 0;
+  if (wps == 1 && it >= nitems) return;  // (no barrier below for one wave per sink)
   int B = first_lo + it;
   if (sg.nseg && it >= nlo) {  // a later segment of a long list (one wave per sink)
     int x = it - nlo;
@@ -203,7 +202,7 @@ __global__ void __launch_bounds__(64 * MX_WAVES) __attribute__((amdgpu_waves_per
     B = v.x;
     seg = v.y;
   }
-  bool live = blk < nblk && B < ncell;
+  bool live = it < nitems && B < ncell;
   int b = 0, e = 0;
   double* out = loc + (size_t)B * NC * 2;
   if (live) {
@@ -222,8 +221,8 @@ __global__ void __launch_bounds__(64 * MX_WAVES) __attribute__((amdgpu_waves_per
   }
   int nbat = (e - b + 63) >> 6;
   int pb = b + 64 * (nbat * part / wps), pe = min(e, b + 64 * (nbat * (part + 1) / wps));
-  __shared__ double accs[MX_WAVES][P + 1][64];
-  double* acc = &accs[wv][0][0] + lane;
+  extern __shared__ double accs[];  // [wavefront][order][lane]
+  double* acc = accs + wv * ((P + 1) * 64) + lane;
 #pragma unroll
   for (int t = 0; t <= P; t++) acc[64 * t] = 0.0;
   double bx = 0.0, by = 0.0, bz = 0.0, sB = 1.0;
@@ -375,7 +374,7 @@ __global__ void __launch_bounds__(64 * MX_WAVES) __attribute__((amdgpu_waves_per
       bool im = j > 0 && !(j & 1);
       double f = (m == 0 ? 1.0 : sqrt(0.5)) * sqrt(fmm_fact_dev(n - m) * fmm_fact_dev(n + m)) * pw;
       double t = acc[64 * n];
-      for (int k = 1; k < wps; k++) t += accs[wv + k][n][lane];  // the other parts, in order
+      for (int k = 1; k < wps; k++) t += accs[((wv + k) * (P + 1) + n) * 64 + lane];  // the other parts, in order
       out[2 * cidx(n, m) + (im ? 1 : 0)] = t * f;
       if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
     }
@@ -449,7 +448,6 @@ static void launch_p32(Ctx& c, int first_lo) {
   int nlo = nc - first_lo;
   if (nlo <= 0) return;
   int wps = c.prm.m2l_waves;
-  int spb = MX_WAVES / wps;
   M2lSeg sg{};
   int64_t extra_max = 0;
   if (wps == 1) {  // long lists in segments (see M2lSeg)
@@ -472,9 +470,8 @@ static void launch_p32(Ctx& c, int first_lo) {
     sg = M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p, K, (int)(nlo + extra_max)};
   }
   int nitems = sg.nseg ? sg.max_items : nlo;
-  int nblk = (nitems + spb - 1) / spb;
-  unsigned grid = xcd_grid(nblk);
-  hipLaunchKernelGGL(k_m2l_fp32<P>, dim3(grid), dim3(64 * MX_WAVES), 0, c.stream, nc, first_lo,
+  unsigned grid = xcd_grid(nitems);
+  hipLaunchKernelGGL(k_m2l_fp32<P>, dim3(grid), dim3(64 * wps), sizeof(double) * wps * (P + 1) * 64, c.stream, nc, first_lo,
                      c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.scale.p, c.nmult.p, c.loc.p,
                      wps, sg);
   if (sg.nseg && extra_max > 0) {

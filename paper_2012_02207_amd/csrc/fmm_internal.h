@@ -94,8 +94,8 @@ void release(Workspace& w, dbuf<T>& b) {
 // ------------------------------------------------------------------ lists
 // directed (sink, source) cell pairs grouped by sink: off[ncell+1], src[count]
 struct CellList {
-  dbuf<uint64_t> raw;  // emitted keys (sink << bits | source), any order
-  dbuf<uint64_t> tmp;  // radix-sort ping-pong
+  dbuf<uint64_t> raw;  // emitted keys (sink << bits | source), any order; scratch of the grouping
+  dbuf<uint64_t> tmp;  // scratch of the grouping
   dbuf<int> off;       // CSR offsets by sink
   dbuf<int> src;       // sources, ascending within each sink
   int64_t count = 0;

@@ -506,6 +506,11 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
   if (lane == 0 && pairs > 0) atomicAdd(npairs, (unsigned long long)pairs);
 }
 
+// Which of the two kernels the near field of a context takes: in every precision
+// but mixed the FP64 one (a frozen evaluation may run under FMM_DIRECT), whose
+// plan has tiles.
+static bool nf_tiled(const Ctx& c) { return c.prm.precision != FMM_MIXED; }
+
 // Near-field work items (the plan above), one thread per leaf; ctr[0] counts
 // the extra items, ctr[1] the partial slots and ctr[-2] the later segments (all
 // zero on entry).
@@ -595,7 +600,7 @@ void plan_near_field(Ctx& c) {
   // a split leaf holds len > K entries in ceil(len / K) segments, so the extra
   // items number fewer than cnt / K, with the smallest K of any system
   int max_nb = std::min(64, c.prm.n_leaf);
-  int tiled = c.prm.precision == FMM_FP64;
+  int tiled = nf_tiled(c);
   int kmin = nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, tiled, floor_k);
   int64_t extra_max = cnt / kmin;
   int64_t slot_max = extra_max * max_nb;
@@ -643,7 +648,7 @@ void launch_near_field(Ctx& c) {
   unsigned grid = xcd_grid(nblk);
   double e2 = c.eps_soft * c.eps_soft;
   int gmax = c.prm.p2p_groups;
-  if (c.prm.precision == FMM_MIXED)
+  if (!nf_tiled(c))
     hipLaunchKernelGGL(k_leaf_group, dim3(grid), dim3(64 * LG_WAVES), 0, c.stream, leaves, c.nf,
                        c.c_begin.p, c.c_end.p, c.p2p.off.p, c.p2p.src.p, c.pm.p, e2, c.nearbuf.p,
                        c.nf_part.p, npairs, gmax);

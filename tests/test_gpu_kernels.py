@@ -288,3 +288,28 @@ def test_list_parts(fmm, kind, n, n_leaf, theta, p, err_tol):
         print(k, len(want), flush=True)
         assert np.array_equal(f.export(k).astype(np.int64).reshape(-1, 2), want), k
     f.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("first", ["forces", "jerk"])
+def test_frozen_under_direct_precision(fmm, first, graph):
+    """A frozen evaluation under precision "direct" is the FP64 one, bit for
+    bit: leaves of more than one tile of sinks, split and unsplit lists."""
+    pos, vel, mass = (_dev(a) for a in W.plummer(6000, 12))
+    moved = pos + 1e-3 * vel
+    print(f"[gpu] frozen under direct, after {first}, graph={graph}", flush=True)
+    f = fmm.FMM(p=6, err_tol=1e-6)
+    f.forces(pos, mass)
+    want = f.forces_frozen(moved, mass)
+    f.close()
+    f = fmm.FMM(p=6, err_tol=1e-6, precision="fp64" if first == "forces" else "direct")
+    if first == "forces":
+        f.forces(pos, mass)
+        f.set_params(precision="direct")
+    else:  # evaluates in FP64 whatever the precision
+        f.jerk(pos, vel, mass)
+    got = [torch.full_like(t, 7.0) for t in want]
+    for _ in range(2):
+        f.forces_frozen(moved, mass, out=got, graph=graph)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    f.close()

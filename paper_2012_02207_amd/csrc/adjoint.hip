@@ -279,14 +279,16 @@ __device__ __forceinline__ void adj_tile(int i0, int qb, int qe, int lane, const
   BodyStream st;
   st.start(srcl, cb, ce, qb, qe, lane);
   int j, na = st.next(lane, -1, j);
-  double4 cpm = pm[max(j, 0)], csrc = src[max(j, 0)];
+  int jj = j >= 0 ? j : i0;  // (past the end of the list a body of the item's own, not used)
+  double4 cpm = pm[jj], csrc = src[jj];
   while (na > 0) {
     double4 s = cpm, gj = csrc;
     bool live = j >= 0;  // (past the end of the list: nothing)
     int self = j - i0;   // the sink that this lane's body is, if any
     na = st.next(lane, -1, j);
-    cpm = pm[max(j, 0)];
-    csrc = src[max(j, 0)];
+    jj = j >= 0 ? j : i0;
+    cpm = pm[jj];
+    csrc = src[jj];
 #pragma unroll
     for (int k = 0; k < TS; k++) adj_pair(me[k], g[k], s, gj, live && self != k, eps2, acc + 7 * k);
   }

@@ -165,7 +165,9 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
 // FP64: a lane per source body, taken 64 at a time from the list whatever the
 // leaves' sizes (BodyStream; the next chunk fetched while this one is summed),
 // against a tile of up to 8 sink bodies, whose positions are wave-uniform, so
-// a pair costs no LDS read and every lane works.  Each lane keeps the tile's
+// a pair costs no LDS read and every lane works.  Past the end of the list a lane
+// holds the tile's first sink, without mass: a body of the item's own, so that
+// nothing of another system is read.  Each lane keeps the tile's
 // partial sums in registers; they are added across the lanes at the end of the
 // list (reduce_lanes).  With a lane
 // per (sink, source group) pair and the sources in LDS the pair loop took 2190 us
@@ -193,7 +195,7 @@ __device__ __forceinline__ long long near_tile64(int i0, int qb, int qe, int lan
   BodyStream st;
   st.start(src, cb, ce, qb, qe, lane);
   int j, na = st.next(lane, -1, j);
-  double4 cur = pm[max(j, 0)];
+  double4 cur = pm[j >= 0 ? j : i0];
   long long pairs = 0;
   while (na > 0) {
     double4 v = cur;
@@ -201,7 +203,7 @@ __device__ __forceinline__ long long near_tile64(int i0, int qb, int qe, int lan
     if (jv < 0) v.w = 0.0;  // past the end of the list: no mass
     pairs += (long long)na * TS;
     int nn = st.next(lane, -1, j);
-    cur = pm[max(j, 0)];
+    cur = pm[j >= 0 ? j : i0];
     int self = jv - i0;  // the sink that this lane's body is, if any
     pairs -= __popcll(ballot((unsigned)self < (unsigned)TS));
 #pragma unroll

@@ -313,3 +313,21 @@ def test_frozen_under_direct_precision(fmm, first, graph):
         f.forces_frozen(moved, mass, out=got, graph=graph)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     f.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_batch_isolates_a_bad_system(fmm, precision, bad):
+    """Systems of a batch feel only their own bodies: one whose positions are
+    not finite, at the start of the sorted order, leaves the others' sums as
+    they are alone, bit for bit."""
+    pos, mass = W.uniform_cube(70, 3)
+    pos[10:14] = bad
+    q, _, mq = W.plummer(700, 4)
+    print(f"[gpu] batch with a bad system {bad} {precision}", flush=True)
+    f = fmm.FMM(p=4, err_tol=1e-5, precision=precision)
+    alone = f.forces(_dev(q), _dev(mq))
+    both = f.forces_batch(_dev(np.concatenate([pos, q, pos])), _dev(np.concatenate([mass, mq, mass])),
+                          np.array([0, 70, 770, 840]))
+    assert torch.equal(both[0][70:770], alone[0]) and torch.equal(both[1][70:770], alone[1])
+    f.close()

@@ -187,8 +187,22 @@ static fmm_status validate_params(const fmm_params* p) {
   return FMM_OK;
 }
 
+// After a call that failed on the way: waits for what it had enqueued.  Its work
+// on the side streams was not joined with the caller's, and the next call reuses
+// the buffers (the scratch of the allocation-free entry point above all) while a
+// kernel of the failed one would still read its cells' indices from them.
+static void settle(Ctx& c) {
+  for (hipStream_t s : {c.side, c.side2, c.stream}) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) (void)hipStreamSynchronize(s);
+  }
+  (void)hipGetLastError();
+}
+
+// f with its exceptions as a status; c: the state that f enqueues work for (if any)
 template <class F>
-static fmm_status guarded(fmm_ctx* ctx, F&& f) {
+static fmm_status guarded(fmm_ctx* ctx, Ctx* c, F&& f) {
+  fmm_status st = FMM_EHIP;
   try {
     return f();
   } catch (const hip_error& e) {
@@ -196,17 +210,22 @@ static fmm_status guarded(fmm_ctx* ctx, F&& f) {
       ctx->c.err = std::string(e.where) + ": " + hipGetErrorString(e.code);
       (void)hipGetLastError();
     }
-    return FMM_EHIP;
   } catch (const oom_error&) {
     if (ctx) ctx->c.err = "device workspace allocation failed or exceeded the cap";
-    return FMM_ENOMEM;
+    st = FMM_ENOMEM;
   } catch (const unsupported_error& e) {
     if (ctx) ctx->c.err = e.what;
-    return FMM_EUNSUPPORTED;
+    st = FMM_EUNSUPPORTED;
   } catch (const std::bad_alloc&) {
     if (ctx) ctx->c.err = "host allocation failed";
-    return FMM_ENOMEM;
+    st = FMM_ENOMEM;
   }
+  if (c) settle(*c);
+  return st;
+}
+template <class F>
+static fmm_status guarded(fmm_ctx* ctx, F&& f) {
+  return guarded(ctx, (Ctx*)nullptr, f);
 }
 
 extern "C" {
@@ -331,7 +350,7 @@ fmm_status fmm_build(fmm_ctx* ctx, int64_t n, const double* pos, const double* m
   fmm_status st = common_checks(ctx, n, pos, mass);
   if (st != FMM_OK) return st;
   Ctx& c = ctx->c;
-  return guarded(ctx, [&]() {
+  return guarded(ctx, &c, [&]() {
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.p = c.prm.p;
@@ -357,7 +376,7 @@ static fmm_status forces_on(fmm_ctx* ctx, Ctx& c, int64_t nsys, const int64_t* o
   if (!(eps_soft >= 0) || !std::isfinite(eps_soft)) return FMM_EINVAL;
   if (p < 1 || p > 30) return FMM_EINVAL;
   if (!(err_tol > 0) || !std::isfinite(err_tol)) return FMM_EINVAL;
-  return guarded(ctx, [&]() {
+  return guarded(ctx, &c, [&]() {
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.adjoint_ready = false;
@@ -626,7 +645,7 @@ fmm_status fmm_forces_frozen(fmm_ctx* ctx, int64_t n, const double* pos, const d
   fmm_status st = frozen_checks(ctx, n, pos, mass, eps_soft, acc, pot);
   if (st != FMM_OK) return st;
   Ctx& c = ctx->c;
-  return guarded(ctx, [&]() {
+  return guarded(ctx, &c, [&]() {
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.eps_soft = eps_soft;
@@ -642,7 +661,7 @@ fmm_status fmm_forces_frozen_graph(fmm_ctx* ctx, int64_t n, const double* pos, c
   fmm_status st = frozen_checks(ctx, n, pos, mass, eps_soft, acc, pot);
   if (st != FMM_OK) return st;
   Ctx& c = ctx->c;
-  return guarded(ctx, [&]() {
+  return guarded(ctx, &c, [&]() {
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.eps_soft = eps_soft;
@@ -701,7 +720,7 @@ fmm_status fmm_adjoint(fmm_ctx* ctx, int64_t n, const double* pos, const double*
     st = forces_impl(ctx, 1, off, n, pos, mass, eps_soft, p, err_tol, c.fwd_acc.p, c.fwd_pot.p, stream);
   }
   if (st == FMM_OK)
-    st = guarded(ctx, [&]() {
+    st = guarded(ctx, &c, [&]() {
       adjoint_pass(c, gacc, gpot, c.fwd_acc.p, gpos, gmass);
       return FMM_OK;
     });
@@ -717,7 +736,7 @@ fmm_status fmm_adjoint_last(fmm_ctx* ctx, int64_t n, const double* acc, const do
     c.err = "fmm_adjoint_last: the last evaluation was not one FP64 system of this many bodies";
     return FMM_ENOTBUILT;
   }
-  return guarded(ctx, [&]() {
+  return guarded(ctx, &c, [&]() {
     c.stream = (hipStream_t)stream;
     c.err.clear();
     adjoint_pass(c, gacc, gpot, acc, gpos, gmass);
@@ -736,7 +755,7 @@ fmm_status fmm_jerk(fmm_ctx* ctx, int64_t n, const double* pos, const double* ve
   int64_t off[2] = {0, n};
   fmm_status st = forces_impl(ctx, 1, off, n, pos, mass, eps_soft, p, err_tol, acc, pot, stream);
   if (st == FMM_OK)
-    st = guarded(ctx, [&]() {
+    st = guarded(ctx, &c, [&]() {
       jerk_pass(c, vel, mass, jerk);
       return FMM_OK;
     });

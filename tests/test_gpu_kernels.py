@@ -331,3 +331,38 @@ def test_batch_isolates_a_bad_system(fmm, precision, bad):
                           np.array([0, 70, 770, 840]))
     assert torch.equal(both[0][70:770], alone[0]) and torch.equal(both[1][70:770], alone[1])
     f.close()
+
+
+def test_calls_after_a_failed_one(fmm):
+    """A call that runs out of scratch on the way leaves nothing running on the
+    buffers that the next call takes: small calls right behind such ones, in the
+    fixed scratch and in a context's own under a limit, give what they give on
+    their own."""
+    big, _, mbig = (_dev(a) for a in W.plummer(65536, 15))
+    pos, _, mass = (_dev(a) for a in W.plummer(3000, 16))
+    f = fmm.FMM(p=20, err_tol=1e-9, n_leaf=8)
+    want = f.forces(pos, mass)
+    for _ in range(4):
+        print("[gpu] noalloc after a failed call", flush=True)
+        with pytest.raises(fmm.FmmError) as e:
+            f.forces(big, mbig, noalloc=True)
+        assert e.value.status == fmm.FMM_ENOMEM
+        got = f.forces(pos, mass, noalloc=True)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    f.close()
+    f = fmm.FMM(p=8, err_tol=1e-6)
+    f.forces(big, mbig)
+    need = f.stats()["workspace_bytes"]
+    f.close()
+    f = fmm.FMM(p=8, err_tol=1e-6)
+    want = f.forces(pos, mass)
+    for part in (0.15, 0.3, 0.45, 0.6, 0.75, 0.9):
+        print(f"[gpu] forces after a call failed at {part} of its workspace", flush=True)
+        f.set_workspace_limit(int(part * need))
+        with pytest.raises(fmm.FmmError) as e:
+            f.forces(big, mbig)
+        assert e.value.status == fmm.FMM_ENOMEM
+        f.set_workspace_limit(0)
+        got = f.forces(pos, mass)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    f.close()

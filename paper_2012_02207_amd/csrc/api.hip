@@ -649,6 +649,7 @@ fmm_status fmm_forces_frozen(fmm_ctx* ctx, int64_t n, const double* pos, const d
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.eps_soft = eps_soft;
+    c.adjoint_ready = false;
     c.have_events = true;
     run_frozen(c, pos, mass, acc, pot);
     c.adjoint_ready = c.prm.precision == FMM_FP64 && c.nsys == 1;
@@ -665,6 +666,7 @@ fmm_status fmm_forces_frozen_graph(fmm_ctx* ctx, int64_t n, const double* pos, c
     c.stream = (hipStream_t)stream;
     c.err.clear();
     c.eps_soft = eps_soft;
+    c.adjoint_ready = false;
     c.have_events = false;  // no timing events inside the graph
     const void* key[5] = {pos, mass, acc, pot, stream};
     bool same = c.graph_valid && c.gkey_eps == eps_soft;

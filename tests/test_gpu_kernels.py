@@ -366,3 +366,22 @@ def test_calls_after_a_failed_one(fmm):
         got = f.forces(pos, mass)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     f.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_no_adjoint_of_a_failed_frozen_evaluation(fmm, graph):
+    """A frozen evaluation that runs out of workspace has changed the bodies and
+    not finished the expansions: there is nothing left to differentiate."""
+    pos, vel, mass = (_dev(a) for a in W.plummer(3000, 18))
+    print(f"[gpu] adjoint after a failed frozen evaluation, graph={graph}", flush=True)
+    f = fmm.FMM(p=6, err_tol=1e-6)
+    acc, _ = f.forces(pos, mass)
+    f.set_workspace_limit(f.stats()["workspace_bytes"])
+    f.set_params(precision="mixed")  # needs the normalised moments too
+    with pytest.raises(fmm.FmmError) as e:
+        f.forces_frozen(pos + 0.1 * vel, mass, graph=graph)
+    assert e.value.status == fmm.FMM_ENOMEM
+    with pytest.raises(fmm.FmmError) as e:
+        f.adjoint_last(acc, vel)
+    assert e.value.status == fmm.FMM_ENOTBUILT
+    f.close()

@@ -871,10 +871,12 @@ __global__ void __launch_bounds__(CT_T) k_cell_emit(int n, const unsigned short*
 
 // Mass, first moments and centre of mass; leaves sum their bodies in sorted order,
 // internal cells their children in octant order.  The leaves of all levels in one
-// launch, then the internal cells: by one workgroup, level by level, from the
-// first level of up to MC_TOP cells, below it a launch per level.  A launch per
-// level for leaves and cells alike took 87 us at 16384 bodies and 150 us at 2^20;
-// this takes 20 and 48 us.
+// launch, then the internal cells from the deepest level up: every run of
+// consecutive levels of up to MC_TOP cells each by one workgroup, level by level,
+// a larger level by a launch of its own.  (Levels do not only shrink towards the
+// root: a tight clump leaves a few cells on each of many levels below the widest
+// one.)  A launch per level for leaves and cells alike took 87 us at 16384 bodies
+// and 150 us at 2^20; this takes 20 and 48 us.
 struct MomentView {
   const int *cb, *c0, *nch, *level;
   const uint64_t* key;
@@ -962,12 +964,12 @@ __global__ void k_cell_sums(int first, int count, MomentView v) {
   if (t < count) cell_sums(v, first + t);
 }
 
-// the levels from `from` up to the roots, one workgroup; lvl: first ids (by level)
+// the levels from `from` up to `to`, one workgroup; lvl: first ids (by level)
 struct LevelIds {
   int first[FMM_MAX_LEVEL + 2];
 };
-__global__ void __launch_bounds__(1024) k_cell_sums_top(int from, LevelIds lvl, MomentView v) {
-  for (int l = from; l >= 0; l--) {
+__global__ void __launch_bounds__(1024) k_cell_sums_run(int from, int to, LevelIds lvl, MomentView v) {
+  for (int l = from; l >= to; l--) {
     for (int c = lvl.first[l] + threadIdx.x; c < lvl.first[l + 1]; c += 1024) cell_sums(v, c);
     __syncthreads();  // (global writes of the level are visible to the workgroup)
   }
@@ -1038,7 +1040,7 @@ unsigned cell_chunk_blocks(const Ctx& c, int waves_per_block) {
   return (unsigned)ceil_div(max_chunks, waves_per_block);
 }
 
-constexpr int MC_TOP = 2048;  // cells of a level, up to which one workgroup takes it and those above
+constexpr int MC_TOP = 2048;  // cells of a level, up to which one workgroup takes it
 
 // mass, centre of mass and radius of every cell from the sorted bodies
 void cell_moments(Ctx& c, bool with_radius) {
@@ -1058,14 +1060,18 @@ void cell_moments(Ctx& c, bool with_radius) {
                c.c_mass.p, c.c_sx.p, c.c_sy.p, c.c_sz.p, c.c_cx.p, c.c_cy.p, c.c_cz.p};
   hipLaunchKernelGGL(k_leaf_moments, grid1(c.nleaf, 64), dim3(64), 0, s, (int)c.nleaf, c.leaves.p, c.c_end.p, v,
                      c.pm.p);
-  int level = c.depth - 1;
-  for (; level >= 0 && c.lvl_count[level] > MC_TOP; level--)
-    hipLaunchKernelGGL(k_cell_sums, grid1(c.lvl_count[level], 64), dim3(64), 0, s, c.lvl_first[level],
-                       c.lvl_count[level], v);
-  if (level >= 0) {
-    LevelIds ids{};
-    for (int l = 0; l <= level + 1; l++) ids.first[l] = c.lvl_first[l];
-    hipLaunchKernelGGL(k_cell_sums_top, dim3(1), dim3(1024), 0, s, level, ids, v);
+  LevelIds ids{};
+  for (int l = 0; l <= c.depth; l++) ids.first[l] = c.lvl_first[l];
+  for (int level = c.depth - 1; level >= 0;) {
+    int to = level;
+    if (c.lvl_count[level] <= MC_TOP) {
+      while (to > 0 && c.lvl_count[to - 1] <= MC_TOP) to--;
+      hipLaunchKernelGGL(k_cell_sums_run, dim3(1), dim3(1024), 0, s, level, to, ids, v);
+    } else {
+      hipLaunchKernelGGL(k_cell_sums, grid1(c.lvl_count[level], 64), dim3(64), 0, s, c.lvl_first[level],
+                         c.lvl_count[level], v);
+    }
+    level = to - 1;
   }
   HIPCHK(hipGetLastError());
   if (!with_radius) return;

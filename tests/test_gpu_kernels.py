@@ -385,3 +385,31 @@ def test_no_adjoint_of_a_failed_frozen_evaluation(fmm, graph):
         f.adjoint_last(acc, vel)
     assert e.value.status == fmm.FMM_ENOTBUILT
     f.close()
+
+
+# internal cells' sums: a workgroup per run of levels of up to 2048 cells, a launch
+# per larger level, in any succession
+@pytest.mark.parametrize("kind", ["chain", "two widths"])
+def test_cell_sums_of_clumped_trees(fmm, kind):
+    """Masses and centres of the oracle, bit for bit, where the widest level is
+    not the deepest internal one."""
+    rng = np.random.default_rng(5)
+    pos = rng.uniform(-1.0, 1.0, (24000, 3))
+    if kind == "chain":  # a few cells on each of many levels below the widest
+        pos[:12] = 0.3 + 1e-7 * rng.normal(size=(12, 3))
+    else:  # wide, narrow, wide again
+        pos[:12000] = 0.3 + 1e-4 * pos[:12000]
+    mass = rng.uniform(0.5, 1.5, len(pos))
+    print(f"[gpu] cell sums, {kind}", flush=True)
+    f = fmm.FMM(p=1, n_leaf=4)
+    f.build(_dev(pos), _dev(mass))
+    level, nchild = f.export("cell_level"), f.export("cell_nchild")
+    internal = np.bincount(level[nchild > 0])
+    wide = np.bincount(level)[:len(internal)] > 2048
+    assert wide.any() and not wide[0] and not wide[-1 if kind == "chain" else 8]
+    assert kind == "chain" or wide[9:].any() and wide[:8].any()
+    o = oracle.Oracle()
+    o.run(pos, mass, p=1, err_tol=1e-7, n_leaf=4, stage="upward")
+    for k in ("cell_mass", "cell_com"):
+        assert np.array_equal(f.export(k), o.get(k).reshape(f.export(k).shape)), k
+    f.close()

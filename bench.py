@@ -86,7 +86,7 @@ def measured_traffic(kernel, workload, precision):
 
 SORT_PASSES = 8          # LSD passes of 8 bits over the 63-bit Morton keys
 SORT_BYTES = 24          # per body and pass: read key (8) + index (4), write both
-GATHER_BYTES = 36 + 64   # per body: read index, position, mass; write SoA x, y, z, m and packed (x, y, z, m)
+GATHER_BYTES = 36 + 56   # per body: read index, position, mass; write SoA x, y, z and packed (x, y, z, m)
 
 
 def hbm_rates(stages, n):

@@ -160,7 +160,7 @@ struct Ctx {
   // bodies (sorted order)
   dbuf<uint64_t> key[2];
   dbuf<int> idx[2];
-  dbuf<double> sx, sy, sz, sm;
+  dbuf<double> sx, sy, sz;
   dbuf<double4> pm;   // packed (x, y, z, m), sorted order
   dbuf<double> fpart;
   dbuf<int> leaf_of;  // leaf id of each sorted body

@@ -615,7 +615,7 @@ __global__ void k_apply_pos(const int* spos, int64_t n, const uint64_t* kin, con
 }
 
 __global__ void k_gather(const double* pos, const double* mass, const int* idx, int64_t n, double* sx,
-                         double* sy, double* sz, double* sm, double4* pm) {
+                         double* sy, double* sz, double4* pm) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int o = idx[i];
@@ -623,7 +623,6 @@ __global__ void k_gather(const double* pos, const double* mass, const int* idx, 
   sx[i] = x;
   sy[i] = y;
   sz[i] = z;
-  sm[i] = m;
   pm[i] = make_double4(x, y, z, m);
 }
 
@@ -641,7 +640,7 @@ __global__ void __launch_bounds__(BS_T) k_tree_small(const double* __restrict__ 
                                                      int n, double* __restrict__ rootbox, uint64_t* __restrict__ key,
                                                      int* __restrict__ idx, double* __restrict__ sx,
                                                      double* __restrict__ sy, double* __restrict__ sz,
-                                                     double* __restrict__ sm, double4* __restrict__ pm) {
+                                                     double4* __restrict__ pm) {
   __shared__ BlockSort<uint64_t, TS_I, true> bs;
   __shared__ double ext[6][(BS_T / 64)];
   __shared__ double box[5];
@@ -705,7 +704,6 @@ __global__ void __launch_bounds__(BS_T) k_tree_small(const double* __restrict__ 
       sx[i] = x;
       sy[i] = y;
       sz[i] = z;
-      sm[i] = m;
       pm[i] = make_double4(x, y, z, m);
     }
   }
@@ -1099,7 +1097,7 @@ void cell_moments(Ctx& c, bool with_radius) {
 // sequence needs no host round trip.
 void refresh_frozen(Ctx& c, const double* pos, const double* mass) {
   hipLaunchKernelGGL(k_gather, grid1(c.n), dim3(256), 0, c.stream, pos, mass, c.idx[0].p, c.n, c.sx.p,
-                     c.sy.p, c.sz.p, c.sm.p, c.pm.p);
+                     c.sy.p, c.sz.p, c.pm.p);
   HIPCHK(hipGetLastError());
   cell_moments(c, false);
 }
@@ -1115,7 +1113,6 @@ void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
   ensure(c.ws, c.sx, n);
   ensure(c.ws, c.sy, n);
   ensure(c.ws, c.sz, n);
-  ensure(c.ws, c.sm, n);
   ensure(c.ws, c.leaf_of, n);
   ensure(c.ws, c.rootbox, (size_t)8 * nsys);
   {
@@ -1140,7 +1137,7 @@ void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
   if (nsys == 1 && n <= TS_MAX) {
     if (c.have_events) HIPCHK(hipEventRecord(c.ev[15], s));
     hipLaunchKernelGGL(k_tree_small, dim3(1), dim3(BS_T), 0, s, pos, mass, (int)n, c.rootbox.p, c.key[0].p,
-                       c.idx[0].p, c.sx.p, c.sy.p, c.sz.p, c.sm.p, c.pm.p);
+                       c.idx[0].p, c.sx.p, c.sy.p, c.sz.p, c.pm.p);
     HIPCHK(hipGetLastError());
     if (c.have_events) {
       HIPCHK(hipEventRecord(c.ev[16], s));
@@ -1179,7 +1176,7 @@ void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
     }
     if (c.have_events) HIPCHK(hipEventRecord(c.ev[16], s));
     hipLaunchKernelGGL(k_gather, grid1(n), dim3(256), 0, s, pos, mass, c.idx[0].p, n, c.sx.p, c.sy.p,
-                       c.sz.p, c.sm.p, c.pm.p);
+                       c.sz.p, c.pm.p);
     HIPCHK(hipGetLastError());
     if (c.have_events) HIPCHK(hipEventRecord(c.ev[17], s));
   }

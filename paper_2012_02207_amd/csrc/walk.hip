@@ -258,6 +258,22 @@ __global__ void k_extract_src(const uint64_t* keys, int64_t cnt, uint64_t mask, 
   if (i < cnt) src[i] = (int)(keys[i] & mask);
 }
 
+// off[from .. to] = at of each valid lane, whole wavefronts: the sinks without
+// entries between two of a list.  Long runs (a batch of many small systems has
+// lists of few entries for 65536 sinks, and a lane alone takes 1.7 ms for
+// those) are written by all lanes.
+__device__ __forceinline__ void fill_offsets(bool valid, int from, int to, int at, int* __restrict__ off, int lane) {
+  bool apart = valid && to - from >= WAVE;
+  if (valid && !apart)
+    for (int t = from; t <= to; t++) off[t] = at;
+  for (uint64_t todo = ballot(apart); todo; todo &= todo - 1) {
+    int l = __builtin_ctzll(todo);
+    int f = __builtin_amdgcn_readlane(from, l), e = __builtin_amdgcn_readlane(to, l);
+    int v = __builtin_amdgcn_readlane(at, l);
+    for (int t = f + lane; t <= e; t += WAVE) off[t] = v;
+  }
+}
+
 // A list of up to GS_MAX entries of 32-bit keys by one workgroup: sort, sources
 // and offsets in one launch instead of three per pass and two (a launch costs
 // some 5 us whatever its size).
@@ -280,15 +296,16 @@ __global__ void __launch_bounds__(BS_T) k_group_small(const uint64_t* __restrict
   // (bs.sk holds the sorted keys) entry i starts the lists of the sinks after
   // the one before it, up to its own; the sinks after the last start at the end
   uint32_t mask = (1u << bits) - 1u;
-  for (int i = tid; i <= cnt; i += BS_T) {
-    int from = i > 0 ? (int)(bs.sk[i - 1] >> bits) + 1 : 0;
+  for (int base = 0; base <= cnt; base += BS_T) {
+    int i = base + tid;
+    int from = i > 0 && i <= cnt ? (int)(bs.sk[i - 1] >> bits) + 1 : 0;
     int to = nseg;
     if (i < cnt) {
       uint32_t q = bs.sk[i];
       src[i] = (int)(q & mask);
       to = (int)(q >> bits);
     }
-    for (int t = from; t <= to; t++) off[t] = i;
+    fill_offsets(i <= cnt, from, to, i, off, lane);
   }
 }
 
@@ -328,15 +345,16 @@ __global__ void __launch_bounds__(T) k_group_parts(uint32_t* x, uint32_t* y, con
   // entry i starts the lists of the sinks after the one before it, up to its
   // own; the sinks after the last start at the end
   auto emit = [&](const uint32_t* keys) {
-    for (int i = tid; i <= n; i += T) {
-      int from = i > 0 ? (int)(keys[i - 1] >> bits) + 1 : 0;
+    for (int base = 0; base <= n; base += T) {
+      int i = base + tid;
+      int from = i > 0 && i <= n ? (int)(keys[i - 1] >> bits) + 1 : 0;
       int to = hi - lo - 1;
       if (i < n) {
         uint32_t q = keys[i];
         src[s0 + i] = (int)(q & mask);
         to = (int)(q >> bits);
       }
-      for (int t = from; t <= to; t++) off[lo + t] = s0 + i;
+      fill_offsets(i <= n, from, to, s0 + i, off + lo, lane);
     }
   };
   uint32_t low = nbits < 32 ? (1u << nbits) - 1u : ~0u;
@@ -431,7 +449,9 @@ static void group_by_sink(Ctx& c, CellList& L) {
   int bits = list_bits(c.ncell);
   ensure(c.ws, L.off, (size_t)nc + 1);
   ensure(c.ws, L.src, (size_t)std::max<int64_t>(L.count, 1));
-  if (L.count == 0 || (2 * bits <= 32 && L.count <= GS_MAX)) {
+  if (L.count == 0) {  // (a batch of systems of one cell each, say)
+    zero_fill(c, L.off.p, ((size_t)nc + 1) * sizeof(int));
+  } else if (2 * bits <= 32 && L.count <= GS_MAX) {
     hipLaunchKernelGGL(k_group_small, dim3(1), dim3(BS_T), 0, s, L.raw.p, (int)L.count, nc, bits, L.src.p, L.off.p);
   } else if (bits <= 20) {
     int fb = std::min(8, bits);

@@ -413,3 +413,31 @@ def test_cell_sums_of_clumped_trees(fmm, kind):
     for k in ("cell_mass", "cell_com"):
         assert np.array_equal(f.export(k), o.get(k).reshape(f.export(k).shape)), k
     f.close()
+
+
+@pytest.mark.parametrize("count,big", [(200, ()), (3000, ()), (3000, (0, 1499, 2999)), (70000 // 16, (7,))])
+def test_lists_of_few_sinks(fmm, count, big):
+    """Batches whose interaction lists are empty, or have entries for a few of
+    thousands of sinks: every list's offsets are the running counts of its
+    entries, and the large systems' sums are those of their own calls."""
+    rng = np.random.default_rng(count)
+    size = np.ones(count, dtype=np.int64)
+    size[list(big)] = 300
+    off = np.concatenate([[0], np.cumsum(size)])
+    pos, mass = rng.uniform(-1, 1, (off[-1], 3)), rng.uniform(0.5, 1.5, off[-1])
+    print(f"[gpu] lists of few sinks: {count} systems, {len(big)} large", flush=True)
+    f = fmm.FMM(p=4, err_tol=1e-3, n_leaf=16)
+    acc, pot = f.forces_batch(_dev(pos), _dev(mass), off)
+    st, nc = f.stats(), len(f.export("cell_level"))
+    assert (st["n_m2l"] > 0) == bool(big) and (st["n_est_far"] > 0) == bool(big)
+    for k in ("est_far", "est_near", "m2l", "p2p"):
+        pairs = f.export(k)  # rebuilt from the offsets
+        assert (np.diff(pairs[:, 0]) >= 0).all() and pairs.min(initial=0) >= 0 and pairs.max(initial=0) < nc, k
+    p2p = f.export("p2p")
+    assert set(map(tuple, p2p[p2p[:, 0] == p2p[:, 1]])) >= {(s, s) for s in np.flatnonzero(size == 1)}
+    single = np.repeat(size == 1, size)
+    assert not acc.cpu().numpy()[single].any() and not pot.cpu().numpy()[single].any()
+    for s in big:
+        a, q = f.forces(_dev(pos[off[s]:off[s + 1]]), _dev(mass[off[s]:off[s + 1]]))
+        assert torch.equal(acc[off[s]:off[s + 1]], a) and torch.equal(pot[off[s]:off[s + 1]], q)
+    f.close()

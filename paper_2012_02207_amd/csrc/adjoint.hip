@@ -265,30 +265,29 @@ __device__ __forceinline__ void adj_pair(const double4& me, const double4& g, co
   a[6] = fma(w3, g.z, fma(w5, uz, a[6]));
 }
 
-// the sinks i0 .. i0 + TS over the list srcl[qb .. qe); the TS sinks' 7 sums
-// to out (8 values per sink, the last one 0)
+// the sinks i0 .. i0 + TS over the list srcl[qb .. qe); the TS sinks' 7 sums to
+// out or (add) onto what is there (8 values per sink, the last one 0)
 template <int TS>
 __device__ __forceinline__ void adj_tile(int i0, int qb, int qe, int lane, const int* __restrict__ srcl,
                                          const int* __restrict__ cb, const int* __restrict__ ce,
                                          const double4* __restrict__ pm, const double4* __restrict__ tv,
-                                         const double4* __restrict__ src, double eps2, double* __restrict__ out) {
+                                         const double4* __restrict__ src, double eps2, double* __restrict__ out,
+                                         bool add) {
   double acc[7 * TS];
 #pragma unroll
   for (int k = 0; k < 7 * TS; k++) acc[k] = 0.0;
   const double4 *me = pm + i0, *g = tv + i0;
   BodyStream st;
   st.start(srcl, cb, ce, qb, qe, lane);
-  int j, na = st.next(lane, -1, j);
-  int jj = j >= 0 ? j : i0;  // (past the end of the list a body of the item's own, not used)
-  double4 cpm = pm[jj], csrc = src[jj];
+  int j, na = st.next(lane, i0, j);
+  double4 cpm = pm[j], csrc = src[j];
   while (na > 0) {
     double4 s = cpm, gj = csrc;
-    bool live = j >= 0;  // (past the end of the list: nothing)
-    int self = j - i0;   // the sink that this lane's body is, if any
-    na = st.next(lane, -1, j);
-    jj = j >= 0 ? j : i0;
-    cpm = pm[jj];
-    csrc = src[jj];
+    bool live = lane < na;  // (past the end of the list a body of the item's own, not used)
+    int self = j - i0;      // the sink that this lane's body is, if any
+    na = st.next(lane, i0, j);
+    cpm = pm[j];
+    csrc = src[j];
 #pragma unroll
     for (int k = 0; k < TS; k++) adj_pair(me[k], g[k], s, gj, live && self != k, eps2, acc + 7 * k);
   }
@@ -297,7 +296,8 @@ __device__ __forceinline__ void adj_tile(int i0, int qb, int qe, int lane, const
   int c, real;
   reduce_slot<7 * TS>(lane, c, real);
   if (real) {
-    out[8 * (c / 7) + c % 7] = tot;
+    double* o = out + 8 * (c / 7) + c % 7;
+    *o = add ? *o + tot : tot;
     if (c % 7 == 6) out[8 * (c / 7) + 7] = 0.0;
   }
 }
@@ -309,34 +309,31 @@ __global__ void __launch_bounds__(64 * ADJ_WAVES) __attribute__((amdgpu_waves_pe
     const double4* __restrict__ tv, const double4* __restrict__ src, double eps2, double4* __restrict__ out,
     double4* __restrict__ part) {
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  int nblk = (plan.max_items + ADJ_WAVES - 1) / ADJ_WAVES;
-  int blk = xcd_block();
-  int it = blk * ADJ_WAVES + wv;
-  if (blk >= nblk || it >= plan.max_items) return;
-  int li = it, seg = 0, tile = 0;
-  if (it >= plan.nleaf) {  // a later tile or segment
-    int x = it - plan.nleaf;
-    if (x >= *plan.nextra) return;
-    int2 v = plan.extra[x];
-    li = v.x;
-    nf_decode(v.y, seg, tile);
-  }
+  int li, seg, tile;
+  if (!nf_item(plan, xcd_block() * ADJ_WAVES + wv, li, seg, tile)) return;
   int B = leaves[li];
-  int nseg = plan.cell_nseg[B];
+  int nseg = plan.cell_nseg[B], send = seg + 1;
   int b = cb[B], e = ce[B];
-  int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
-  double4* dst = seg > 0 ? part + 2 * ((int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b)) : out + 2 * (int64_t)b;
+  double4* dst = out + 2 * (int64_t)b;
+  if (nseg > 1) {
+    int pbase = plan.cell_pbase[B];
+    if (pbase < 0) send = nseg;
+    if (seg > 0) dst = part + 2 * ((int64_t)pbase + (int64_t)(seg - 1) * (e - b));
+  }
   int s0, ts;
   nf_tile(e - b, tile, s0, ts);
-  for (int h = 0; h < ts; h += 4) {
-    double* o = (double*)(dst + 2 * (s0 + h));
-    int i0 = b + s0 + h;
-    switch (min(4, ts - h)) {
-      case 1: adj_tile<1>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
-      case 2: adj_tile<2>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
-      case 3: adj_tile<3>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
-      case 4: adj_tile<4>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o); break;
+  for (bool add = false; seg < send; seg++, add = true) {
+    int qb = off[B], qe = off[B + 1];
+    if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
+    for (int h = 0; h < ts; h += 4) {
+      double* o = (double*)(dst + 2 * (s0 + h));
+      int i0 = b + s0 + h;
+      switch (min(4, ts - h)) {
+        case 1: adj_tile<1>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o, add); break;
+        case 2: adj_tile<2>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o, add); break;
+        case 3: adj_tile<3>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o, add); break;
+        case 4: adj_tile<4>(i0, qb, qe, lane, srcl, cb, ce, pm, tv, src, eps2, o, add); break;
+      }
     }
   }
 }
@@ -351,7 +348,7 @@ __global__ void k_adj_combine(int64_t n, const int* __restrict__ leaf_of, const 
   if (i >= n) return;
   int B = leaf_of[i];
   int ns = cell_nseg[B];
-  if (ns <= 1) return;
+  if (ns <= 1 || cell_pbase[B] < 0) return;
   int nB = ce[B] - cb[B];
   const double4* pp = part + 2 * ((int64_t)cell_pbase[B] + (i - cb[B]));
   double4 a = out[2 * i], b = out[2 * i + 1];

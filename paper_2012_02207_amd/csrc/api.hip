@@ -491,12 +491,12 @@ fmm_status fmm_stats(fmm_ctx* ctx, fmm_stats_t* out) {
       }
       // body-pair count of the near field
       if (c.evaluated) {  // counted by the leaf kernel of the last evaluation
-        unsigned long long* d = (unsigned long long*)(c.counters.p + 40);
+        unsigned long long* d = (unsigned long long*)(c.counters.p + NF_COUNTERS);
         HIPCHK(hipMemcpyAsync(c.hbuf, d, 8, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));
         out->n_p2p_pairs = c.hbuf[0];
         // the near field's work items: the leaves and the later segments
-        HIPCHK(hipMemcpyAsync(c.hbuf, c.counters.p + 42, 4, hipMemcpyDeviceToHost, c.stream));
+        HIPCHK(hipMemcpyAsync(c.hbuf, c.counters.p + NF_COUNTERS + 2, 4, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));
         out->n_p2p_items = (int64_t)c.nleaf + *(const int*)c.hbuf;
       }

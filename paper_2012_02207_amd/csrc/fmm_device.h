@@ -99,12 +99,26 @@ __device__ __forceinline__ bool div_safe(double x) {
   return e - 523u < 1000u;
 }
 
-// Segment and tile of an extra near-field item (NfPlan) in one int: a split leaf
-// has at most 64 bodies, so 8 tiles (code >= 0); a larger one has one segment.
+// Segment and tile of an extra near-field item (NfPlan) in one int: a leaf of
+// segments has at most 64 bodies, so 8 tiles (code >= 0); a larger one has none.
 __device__ __forceinline__ int nf_code(int seg, int tile) { return tile < 8 ? seg * 8 + tile : -tile; }
 __device__ __forceinline__ void nf_decode(int code, int& seg, int& tile) {
   seg = code < 0 ? 0 : code >> 3;
   tile = code < 0 ? -code : code & 7;
+}
+
+// work item `it` of the plan: leaf index, segment and tile; false if there is none
+__device__ __forceinline__ bool nf_item(const NfPlan& plan, int it, int& li, int& seg, int& tile) {
+  li = it;
+  seg = tile = 0;
+  if (it >= plan.nleaf) {
+    int x = it - plan.nleaf;
+    if (it >= plan.max_items || x >= *plan.nextra) return false;
+    int2 v = plan.extra[x];
+    li = v.x;
+    nf_decode(v.y, seg, tile);
+  }
+  return true;
 }
 
 // sinks [s0, s0 + count) of tile `tile` of a leaf of nB bodies

@@ -103,26 +103,29 @@ struct CellList {
 
 // ------------------------------------------------------------------ near field
 // Work items of the near-field kernels: item li < nleaf is leaf li of the leaf
-// list (its whole source list, or the first segment of a long one); a leaf
-// whose list is longer than its system's K entries (and whose bodies fit one
-// wavefront) is cut into ns = ceil(len / K) contiguous segments, segment k the
-// entries [len k / ns, len (k + 1) / ns), and segments 1.. are the extra items
-// (leaf, segment) after the leaves, in any order.  The first segment
-// writes the near field itself, segment k > 0 its partial sums to slots
-// cell_pbase[B] + (k - 1) n_B + body; these are added in segment order
-// afterwards, so the result does not depend on the order of the items.
+// list.  The source list of a leaf of up to 64 bodies is ns = ceil(len / K)
+// contiguous segments, segment k the entries [len k / ns, len (k + 1) / ns),
+// whose sums are formed one by one and added in segment order.  K depends on
+// the leaf's own system alone, and so does the result: a system of a batch sums
+// as it does alone, and as with any amount of scratch.  Who forms the sums is
+// another matter.  A list that is long beside the others and finds room for its
+// partial sums is split: item li takes segment 0 and writes the near field, each
+// later segment is an extra item (leaf, segment) after the leaves, in any order,
+// which writes its sums to slots cell_pbase[B] + (k - 1) n_B + body, and these are
+// added afterwards.  Otherwise (cell_pbase[B] < 0) item li takes every segment.
 // In FP64 the sinks of a leaf are moreover taken in even tiles of up to NF_TILE,
 // an item each (leaf, segment, tile): otherwise a large leaf with a long list
 // is one wavefront's work long after the others have ended.
 constexpr int NF_TILE = 8;
+constexpr int NF_COUNTERS = 72;  // offset in Ctx::counters
 struct NfPlan {
   const int* cell_nseg;   // segments of each leaf, by cell id
-  const int* cell_pbase;  // first partial slot of each split leaf, by cell id
+  const int* cell_pbase;  // first partial slot of each split leaf, -1 of the others, by cell id
   const int2* extra;      // (leaf index, nf_code) of the extra items
   const int* nextra;      // extra item count (device)
   int nleaf;
   int max_items;          // host bound on the item count (grid size)
-  int max_slots;          // host bound on the partial slots
+  int max_slots;          // partial slots
 };
 
 // Work items of the FP64 M2L over whole lists: item B < ncell is sink B (its
@@ -217,9 +220,12 @@ struct Ctx {
   // walks
   dbuf<int2> front[2];
   // device counters (ints), by offset: [4..5] number of body chunks of the
-  // cells (long long, read by the radius and cell-minimum kernels); [32] input check; [40..41] near-field body pairs; [48..49]
-  // FP32 M2L pairs (stats); [64] sinks with root-level pairs; [256..] walk
-  // (64-bit counters at even int offsets)
+  // cells (long long, read by the radius and cell-minimum kernels); [32] input
+  // check; [46] extra items of the M2L; [48..49] FP32 M2L pairs (stats); [64] sinks
+  // with root-level pairs; near field, from NF_COUNTERS on: +0, +1 body pairs (long
+  // long), +2 later segments (stats), +3 extra items, +4, +5 partial slots and +6, +7
+  // later segments' items asked for (long long); [256..] walk (64-bit counters at
+  // even int offsets)
   dbuf<int> counters;
   CellList est_far, est_near, m2l, p2p;
   int64_t n_p2p_pairs = 0;

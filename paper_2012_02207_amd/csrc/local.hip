@@ -181,31 +181,30 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
 // of 16384 37.7 (36.6).
 constexpr int LG_WAVES = 1;
 
-// the sinks i0 .. i0 + TS over the list src[qb .. qe); returns the body pairs
-// (a body with itself is none)
+// the sinks i0 .. i0 + TS over the list src[qb .. qe), their sums to out or (add)
+// onto what is there; returns the body pairs (a body with itself is none)
 template <int TS>
 __device__ __forceinline__ long long near_tile64(int i0, int qb, int qe, int lane, const int* __restrict__ src,
                                                  const int* __restrict__ cb, const int* __restrict__ ce,
                                                  const double4* __restrict__ pm, double eps2,
-                                                 double* __restrict__ out) {
+                                                 double* __restrict__ out, bool add) {
   double acc[4 * TS];
 #pragma unroll
   for (int k = 0; k < 4 * TS; k++) acc[k] = 0.0;
   const double4* sink = pm + i0;
   BodyStream st;
   st.start(src, cb, ce, qb, qe, lane);
-  int j, na = st.next(lane, -1, j);
-  double4 cur = pm[j >= 0 ? j : i0];
+  int j, na = st.next(lane, i0, j);
+  double4 cur = pm[j];
   long long pairs = 0;
   while (na > 0) {
     double4 v = cur;
-    int jv = j;
-    if (jv < 0) v.w = 0.0;  // past the end of the list: no mass
-    pairs += (long long)na * TS;
-    int nn = st.next(lane, -1, j);
-    cur = pm[j >= 0 ? j : i0];
-    int self = jv - i0;  // the sink that this lane's body is, if any
-    pairs -= __popcll(ballot((unsigned)self < (unsigned)TS));
+    bool live = lane < na;
+    if (!live) v.w = 0.0;  // past the end of the list: no mass
+    int self = j - i0;     // the sink that this lane's body is, if any
+    pairs += (long long)na * TS - __popcll(ballot(live && (unsigned)self < (unsigned)TS));
+    int nn = st.next(lane, i0, j);
+    cur = pm[j];
 #pragma unroll
     for (int k = 0; k < TS; k++) {
       double dx = v.x - sink[k].x, dy = v.y - sink[k].y, dz = v.z - sink[k].z;
@@ -224,7 +223,7 @@ __device__ __forceinline__ long long near_tile64(int i0, int qb, int qe, int lan
   reduce_lanes<4 * TS>(acc, &tot, lane);
   int c, real;
   reduce_slot<4 * TS>(lane, c, real);
-  if (real) out[c] = tot;
+  if (real) out[c] = add ? out[c] + tot : tot;
   return pairs;
 }
 
@@ -233,40 +232,37 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     const int* __restrict__ off, const int* __restrict__ srcl, const double4* __restrict__ pm, double eps2,
     double4* __restrict__ nearbuf, double4* __restrict__ part, unsigned long long* npairs) {
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  int nblk = (plan.max_items + LG_WAVES - 1) / LG_WAVES;
-  int blk = xcd_block();
-  int it = blk * LG_WAVES + wv;
-  if (blk >= nblk || it >= plan.max_items) return;
-  int li = it, seg = 0, tile = 0;
-  if (it >= plan.nleaf) {  // a later tile or segment
-    int x = it - plan.nleaf;
-    if (x >= *plan.nextra) return;
-    int2 v = plan.extra[x];
-    li = v.x;
-    nf_decode(v.y, seg, tile);
-  }
+  int li, seg, tile;
+  if (!nf_item(plan, xcd_block() * LG_WAVES + wv, li, seg, tile)) return;
   int B = leaves[li];
-  int nseg = plan.cell_nseg[B];
+  int nseg = plan.cell_nseg[B], send = seg + 1;
   int b = cb[B], e = ce[B];
-  int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
-  double4* out = seg > 0 ? part + (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) : nearbuf + b;
+  double4* out = nearbuf + b;
+  if (nseg > 1) {
+    int pbase = plan.cell_pbase[B];
+    if (pbase < 0) send = nseg;
+    if (seg > 0) out = part + (int64_t)pbase + (int64_t)(seg - 1) * (e - b);
+  }
   int s0, ts;
   nf_tile(e - b, tile, s0, ts);
   double* o = (double*)(out + s0);
   long long pairs = 0;
-  switch (ts) {
+  for (bool add = false; seg < send; seg++, add = true) {
+    int qb = off[B], qe = off[B + 1];
+    if (nseg > 1) segment_bounds(nseg, seg, qb, qe);
+    switch (ts) {
 #define FMM_NEAR_TILE(T) \
-  case T: pairs = near_tile64<T>(b + s0, qb, qe, lane, srcl, cb, ce, pm, eps2, o); break;
-    FMM_NEAR_TILE(1)
-    FMM_NEAR_TILE(2)
-    FMM_NEAR_TILE(3)
-    FMM_NEAR_TILE(4)
-    FMM_NEAR_TILE(5)
-    FMM_NEAR_TILE(6)
-    FMM_NEAR_TILE(7)
-    FMM_NEAR_TILE(8)
+  case T: pairs += near_tile64<T>(b + s0, qb, qe, lane, srcl, cb, ce, pm, eps2, o, add); break;
+      FMM_NEAR_TILE(1)
+      FMM_NEAR_TILE(2)
+      FMM_NEAR_TILE(3)
+      FMM_NEAR_TILE(4)
+      FMM_NEAR_TILE(5)
+      FMM_NEAR_TILE(6)
+      FMM_NEAR_TILE(7)
+      FMM_NEAR_TILE(8)
 #undef FMM_NEAR_TILE
+    }
   }
   if (lane == 0 && pairs > 0) atomicAdd(npairs, (unsigned long long)pairs);
 }
@@ -350,36 +346,35 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
                                                               double eps2, double4* nearbuf,
                                                               double4* __restrict__ part,
                                                               unsigned long long* npairs, int gmax) {
-  // the staged chunk; at the end the groups' sums (4 x 64 doubles)
+  // the staged chunk; at the end of a segment the groups' sums (4 x 64 doubles)
   __shared__ double4 sbuf[LG_WAVES][LG_SLOTS];
+  // totals of an unsplit list's segments, one body per lane (in LDS: the registers
+  // would cost all lists a wavefront per SIMD)
+  __shared__ double2 tbuf[LG_WAVES][2][64];
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  int nblk = (plan.max_items + LG_WAVES - 1) / LG_WAVES;
-  int blk = xcd_block();
-  int it = blk * LG_WAVES + wv;
-  if (blk >= nblk || it >= plan.max_items) return;
-  int li = it, seg = 0;
-  if (it >= plan.nleaf) {  // a later segment of a long list
-    int x = it - plan.nleaf;
-    if (x >= *plan.nextra) return;
-    int2 v = plan.extra[x];
-    li = v.x;
-    int tile;  // (one tile in mixed precision)
-    nf_decode(v.y, seg, tile);
-  }
-  int B = leaves[li];
-  int nseg = plan.cell_nseg[B];
-  int b = cb[B], e = ce[B];
-  int qb = off[B], qe = off[B + 1];
-  if (nseg > 1) segment_bounds(nseg, seg, qb, qe);  // (the leaf's bodies fit one wavefront)
-  // output: the near field itself (a whole list, or the first segment of a
-  // long one), or the partial sums of a later segment
-  bool to_part = seg > 0;
-  int64_t pslot = to_part ? (int64_t)plan.cell_pbase[B] + (int64_t)(seg - 1) * (e - b) - b : 0;
+  int li, seg, tile;  // (one tile in mixed precision)
+  if (!nf_item(plan, xcd_block() * LG_WAVES + wv, li, seg, tile)) return;
   float eps2f = (float)eps2;
   long long pairs = 0;  // body pairs of this leaf (self pairs excluded), wave-uniform
   const double4* sb = sbuf[wv];
   unsigned lane32 = 32u * (unsigned)lane;
-  double(*rb)[64] = (double(*)[64])sbuf[wv];
+  double2(*rb)[64] = (double2(*)[64])sbuf[wv];  // the groups' sums, (x, y) and (z, potential)
+  double2(*tb)[64] = tbuf[wv];
+  int B = leaves[li];
+  int nseg = plan.cell_nseg[B];
+  int b = cb[B], e = ce[B];
+  int qb = off[B], qe = off[B + 1];
+  // output: the near field itself, or the partial sums of a later segment
+  double4* out = nearbuf;
+  int folds = 1;  // segments taken, one after the other
+  if (nseg > 1) {  // (the leaf's bodies fit one wavefront)
+    int pbase = plan.cell_pbase[B];
+    if (pbase < 0)
+      folds = nseg;
+    else
+      segment_bounds(nseg, seg, qb, qe);
+    if (seg > 0) out = part + ((int64_t)pbase + (int64_t)(seg - 1) * (e - b) - b);
+  }
   for (int i0 = b; i0 < e; i0 += 64) {
     int nB = min(64, e - i0);
     int G = 64 / nB;
@@ -394,6 +389,20 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     double4 me = pm[i];
     double nx = 0.0, ny = 0.0, nz = 0.0, np = 0.0;
     float fx = 0.f, fy = 0.f, fz = 0.f, fp = 0.f;
+    // the groups' sums in LDS, to be combined in order
+    auto put_groups = [&]() {
+      __builtin_amdgcn_wave_barrier();
+      rb[0][lane] = make_double2(nx, ny);
+      rb[1][lane] = make_double2(nz, np);
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+    };
+    int fold = 0, qfold = qe;  // segments added up so far, end of the present one
+    if (folds > 1) {
+      int q0 = qb;
+      qfold = qe;
+      segment_bounds(folds, 0, q0, qfold);
+    }
     // source chunks (<= 64 bodies of one source leaf) in list order; the
     // next chunk is fetched into registers while the current one is summed
     int q = qb, j0 = 0, je = 0;
@@ -476,32 +485,53 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
         nz += (double)fz;
         np += (double)fp;
         fx = fy = fz = fp = 0.f;
+        if (nq == qfold && nq < qe) {  // end of a segment
+          put_groups();
+          if (lane < nB)
+#pragma unroll 1
+            for (int k = 0; k < 2; k++) {  // (one after the other: registers)
+              double2 t = make_double2(0.0, 0.0);
+              for (int gg = 0; gg < G; gg++) {
+                double2 v = rb[k][gg * nB + s];
+                t.x += v.x;
+                t.y += v.y;
+              }
+              if (fold > 0) {
+                double2 v = tb[k][lane];
+                t.x = v.x + t.x;
+                t.y = v.y + t.y;
+              }
+              tb[k][lane] = t;
+            }
+          nx = ny = nz = np = 0.0;
+          fold++;
+          int q0 = qb;
+          qfold = qe;
+          segment_bounds(folds, fold, q0, qfold);
+        }
       }
       q = nq;
       j0 = nj0;
       je = nje;
     }
-    // combine the groups in order
-    __builtin_amdgcn_wave_barrier();
-    rb[0][lane] = nx;
-    rb[1][lane] = ny;
-    rb[2][lane] = nz;
-    rb[3][lane] = np;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
+    put_groups();
     if (lane < nB) {
       double tx = 0.0, ty = 0.0, tz = 0.0, tp = 0.0;
       for (int gg = 0; gg < G; gg++) {
-        int l = gg * nB + s;
-        tx += rb[0][l];
-        ty += rb[1][l];
-        tz += rb[2][l];
-        tp += rb[3][l];
+        double2 u = rb[0][gg * nB + s], v = rb[1][gg * nB + s];
+        tx += u.x;
+        ty += u.y;
+        tz += v.x;
+        tp += v.y;
       }
-      if (to_part)
-        part[pslot + i] = make_double4(tx, ty, tz, tp);
-      else
-        nearbuf[i] = make_double4(tx, ty, tz, tp);
+      if (fold > 0) {
+        double2 u = tb[0][lane], v = tb[1][lane];
+        tx = u.x + tx;
+        ty = u.y + ty;
+        tz = v.x + tz;
+        tp = v.y + tp;
+      }
+      out[i] = make_double4(tx, ty, tz, tp);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -513,58 +543,70 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 // plan has tiles.
 static bool nf_tiled(const Ctx& c) { return c.prm.precision != FMM_MIXED; }
 
-// Near-field work items (the plan above), one thread per leaf; ctr[0] counts
-// the extra items, ctr[1] the partial slots and ctr[-2] the later segments (all
-// zero on entry).
-// List entries per segment, at least: a 1024th of the system's bodies, from
-// NF_SEG_MIN on (NF_SEG_TILED times that in FP64, whose items hold at most 8
-// sinks), up to NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
-// more of smaller leaves.  A small system has few leaves with long lists (4096
-// bodies: 303 leaves of 226 entries), and only short segments spread them over
-// the chip; a large one has enough leaves, and only the outliers are cut (at
-// N = 2^18 one leaf holds 2776 entries, 42 times the mean work).  The bound is
-// the system's own, so a system of a batch sums in the same order as alone;
-// only a list total over K NF_ITEMS raises it, to bound the partial sums'
-// memory.  Mixed: with 256 entries or more whatever the size the near field of
-// 30011 bodies took 678 us (319 now), with a 512th and a 2048th of the bodies
-// the evaluation 1.96 and 2.09 ms (1.94), frozen 16384 0.68 and 0.86 (0.71).
-// FP64: twice, four, eight and 16 times the entries give 1.57, 1.43, 1.39 and
-// 1.39 ms at 16000 bodies, 1.28, 1.24, 1.20 and 1.22 at 4096, and the jerk of
-// 50021 bodies 3.62, 3.68, 3.76 and 3.88 ms.
-constexpr int NF_SEG_MIN = 8, NF_SEG_MAX = 512;
-constexpr int NF_SEG_DIV = 1024;
-constexpr int NF_SEG_TILED = 4;
-constexpr int64_t NF_ITEMS = 65536;
+// Near-field work items (NfPlan), one thread per leaf; ctr: counters[NF_COUNTERS ..].
+// List entries per segment, at least: a 1024th of the system's bodies (four times
+// that in FP64, whose items hold at most 8 sinks), from NF_SEG_MIN or
+// NF_SEG_MIN_TILED to NF_SEG_MAX, for leaves of up to 64 bodies, and in proportion
+// more of smaller leaves; and a 32nd of the list (NF_SEG_PER).  A small system has
+// few leaves with long lists (4096 bodies: 303 leaves of 226 entries), and only
+// short segments spread them over the chip; a large one has enough leaves, and
+// only the outliers are cut (at N = 2^18 one leaf holds 2776 entries, 42 times the
+// mean work).  The bound is the system's and the list's own, so that a system of a
+// batch sums in the same order as alone.
+// Mixed: with 256 entries or more whatever the size the near field of 30011 bodies
+// took 678 us (319 now).  At least 8, 16, 24 and 32: 8192 bodies 1.08, 0.98, 0.93 and
+// 0.93 ms, frozen 16384 524, 509, 458 and 455 us, near field of 1000 43, 45, 49 and 52 us.
+// FP64, at least 32, 64 and 96: 4096 bodies 0.90, 0.86 and 0.84 ms, jerk of 2000
+// 1.02, 1.02 and 1.05.  No bound on the segments of a list: 30000 bodies at p = 4,
+// err_tol = 1e-9 (lists of 1600) 3.8 ms, 2.2 with 32: the slots run out otherwise.
+constexpr int NF_SEG_MIN = 24, NF_SEG_MIN_TILED = 64, NF_SEG_MAX = 512;
+constexpr int NF_SEG_DIV = 1024, NF_SEG_TILED = 4;
+constexpr int NF_SEG_PER = 32;
+// What is split (whatever is, the sums are the same): lists longer than a 65536th
+// of all entries (NF_ITEMS), or where the leaves alone fill the chip some times over
+// (NF_FULL wavefronts) lists of more than twice the mean length.  NF_SLOTS, NF_SPLIT:
+// slots for partial sums (32 B each) and later segments' items, at the most; the
+// grid covers that many items, and a wavefront that finds none costs 0.8 ns.
+constexpr int64_t NF_ITEMS = 65536, NF_FULL = 24576, NF_SLOTS = 1 << 20, NF_SPLIT = 65536;
 
-__host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int tiled, int floor_k) {
-  int64_t k = bodies / NF_SEG_DIV;
-  k = k < NF_SEG_MIN ? NF_SEG_MIN : k;
-  if (tiled) k *= NF_SEG_TILED;
+// len: entries of the list (0: the least of any list)
+__host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int tiled, int len) {
+  int64_t k = bodies / NF_SEG_DIV * (tiled ? NF_SEG_TILED : 1), least = tiled ? NF_SEG_MIN_TILED : NF_SEG_MIN;
+  k = k < least ? least : k;
   k = k > NF_SEG_MAX ? NF_SEG_MAX : k;
   k = k * 64 / max_nb;
-  return k < floor_k ? floor_k : (int)k;
+  int part = (len + NF_SEG_PER - 1) / NF_SEG_PER;
+  return k < part ? part : (int)k;
 }
 
 __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* __restrict__ cb,
                           const int* __restrict__ ce, const int* __restrict__ off, const int* __restrict__ sys_off,
-                          int nsys, int floor_k, int max_nb, int tiled, int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
+                          int nsys, int max_nb, int tiled, int long_len, int max_slots, int max_split,
+                          int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
   int li = blockIdx.x * blockDim.x + threadIdx.x;
   if (li >= nleaf) return;
   int B = leaves[li];
   int len = off[B + 1] - off[B], nB = ce[B] - cb[B];
   int sys = nsys > 1 ? system_of(sys_off, nsys, cb[B]) : 0;
-  int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, tiled, floor_k);
-  int ns = (nB <= max_nb && len > K) ? (len + K - 1) / K : 1;
-  cell_nseg[B] = ns;
+  int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, tiled, len);
+  int ns = (nB <= 64 && len > K) ? (len + K - 1) / K : 1;
   int nt = tiled ? nf_tile_count(nB) : 1;
-  if (ns * nt > 1) {
-    int x = atomicAdd(ctr, ns * nt - 1);
-    for (int k = 0; k < ns; k++)
+  int pbase = -1;
+  if (ns > 1 && len > long_len) {  // split, if there are slots and items left
+    unsigned long long need = (unsigned long long)(ns - 1) * nB, more = (unsigned long long)(ns - 1) * nt;
+    unsigned long long at = atomicAdd((unsigned long long*)(ctr + 4), need);
+    if (at + need <= (unsigned long long)max_slots &&
+        atomicAdd((unsigned long long*)(ctr + 6), more) + more <= (unsigned long long)max_split)
+      pbase = (int)at;
+  }
+  cell_nseg[B] = ns;
+  cell_pbase[B] = pbase;
+  int nx = pbase >= 0 ? ns : 1;
+  if (nx * nt > 1) {
+    int x = atomicAdd(ctr + 3, nx * nt - 1);
+    for (int k = 0; k < nx; k++)
       for (int t = k == 0 ? 1 : 0; t < nt; t++) extra[x++] = make_int2(li, nf_code(k, t));
-    if (ns > 1) {
-      cell_pbase[B] = atomicAdd(ctr + 1, (ns - 1) * nB);
-      atomicAdd(ctr - 2, ns - 1);
-    }
+    if (nx > 1) atomicAdd(ctr + 2, nx - 1);
   }
 }
 
@@ -578,7 +620,7 @@ __global__ void k_nf_combine(int64_t n, const int* __restrict__ leaf_of, const i
   if (i >= n) return;
   int B = leaf_of[i];
   int ns = cell_nseg[B];
-  if (ns <= 1) return;
+  if (ns <= 1 || cell_pbase[B] < 0) return;
   int nB = ce[B] - cb[B];
   const double4* pp = part + cell_pbase[B] + (i - cb[B]);
   double4 t = nearbuf[i];
@@ -598,53 +640,49 @@ __global__ void k_nf_combine(int64_t n, const int* __restrict__ leaf_of, const i
 void plan_near_field(Ctx& c) {
   int nleaf = (int)c.nleaf;
   int64_t cnt = c.p2p.count;
-  int floor_k = (int)ceil_div(cnt, NF_ITEMS);
-  // a split leaf holds len > K entries in ceil(len / K) segments, so the extra
-  // items number fewer than cnt / K, with the smallest K of any system
   int max_nb = std::min(64, c.prm.n_leaf);
   int tiled = nf_tiled(c);
-  int kmin = nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, tiled, floor_k);
-  int64_t extra_max = cnt / kmin;
-  int64_t slot_max = extra_max * max_nb;
-  // with tiles: a leaf of n_B bodies has n_B / 8 more of them than one, and
-  // every segment of a split leaf up to ceil(max_nb / 8)
-  if (tiled) extra_max = extra_max * ceil_div(max_nb, NF_TILE) + c.n / NF_TILE;
   ensure(c.ws, c.nf_cell_nseg, (size_t)c.ncell);
   ensure(c.ws, c.nf_cell_pbase, (size_t)c.ncell);
-  ensure(c.ws, c.nf_extra, (size_t)extra_max + 1);
-  int* ctr = c.counters.p + 44;
-  hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
-                     c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, floor_k, max_nb, tiled, c.nf_cell_nseg.p,
-                     c.nf_cell_pbase.p, c.nf_extra.p, ctr);
-  HIPCHK(hipGetLastError());
-  // where memory is limited the partial sums get the slots that the plan
-  // counted (read back), not the bound, which is some four times that
-  if (c.ws.arena || c.ws.limit) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    HIPCHK(hipStreamIsCapturing(c.stream, &cs));
-    if (cs == hipStreamCaptureStatusNone) {
-      int* h = (int*)(c.hbuf + 120);
-      HIPCHK(hipMemcpyAsync(h, ctr + 1, sizeof(int), hipMemcpyDeviceToHost, c.stream));
-      HIPCHK(hipStreamSynchronize(c.stream));
-      slot_max = *h;
-    } else {
-      slot_max = c.nf.max_slots;  // the evaluation run before the capture had the same lists
+  // a list of len > K entries has ceil(len / K) segments, so the later segments
+  // number fewer than cnt / K, with the smallest K of any system
+  int64_t segs = cnt / nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, tiled, 0);
+  int64_t slots = std::min(NF_SLOTS, segs * 64);
+  if (c.ws.limit || c.ws.arena) {
+    // Where memory is limited: a slot per four entries, or in the fixed scratch
+    // what is left of it (with 8 bytes per slot for the extra items) after the
+    // buffers of the M2L, the only ones still to come.
+    int64_t few = ceil_div(cnt, 4);
+    if (c.ws.arena) {
+      int64_t m2l = 12 * c.ncell + 24 * 8192 + (std::min<int64_t>(8192, c.m2l.count / 512) + 1) * ncoef(c.p) * 16;
+      int64_t left = (int64_t)(c.ws.arena_cap - c.ws.arena_used) - m2l - c.n - 8192;
+      few = std::max(few, left / 40);
     }
+    slots = std::min(slots, few);
   }
-  ensure(c.ws, c.nf_part, (size_t)slot_max + 1);
-  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr, nleaf, (int)(nleaf + extra_max),
-                (int)slot_max};
+  // (a split list has no more extra items than slots)
+  int64_t split = std::min({NF_SPLIT, slots, segs * (tiled ? 64 / NF_TILE : 1)});
+  int64_t extra_max = split + (tiled ? c.n / NF_TILE : 0);  // with tiles n_B / 8 of every leaf besides
+  ensure(c.ws, c.nf_extra, (size_t)extra_max + 1);
+  ensure(c.ws, c.nf_part, (size_t)slots + 1);
+  int64_t waves = nleaf + (tiled ? c.n / NF_TILE : 0);
+  int long_len = (int)(waves < NF_FULL ? cnt / NF_ITEMS : 2 * cnt / nleaf);
+  int* ctr = c.counters.p + NF_COUNTERS;
+  hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
+                     c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, max_nb, tiled, long_len,
+                     (int)slots, (int)split, c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr);
+  HIPCHK(hipGetLastError());
+  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr + 3, nleaf,
+                (int)(nleaf + extra_max), (int)slots};
 }
 
-// Near field of every body into c.nearbuf (sorted order), on c.stream.
 void launch_near_field(Ctx& c) {
   if (c.nleaf <= 0) return;
   ensure(c.ws, c.nearbuf, (size_t)c.n);
   const int* leaves = c.leaves.p;
   // body-pair count of the near field, read by fmm_stats
-  // counters[40..41]: the body-pair count; [42], [44], [45]: the plan's counts
-  unsigned long long* npairs = (unsigned long long*)(c.counters.p + 40);
-  zero_fill(c, npairs, 6 * sizeof(int));
+  unsigned long long* npairs = (unsigned long long*)(c.counters.p + NF_COUNTERS);
+  zero_fill(c, npairs, 8 * sizeof(int));
   plan_near_field(c);
   int nblk = (c.nf.max_items + LG_WAVES - 1) / LG_WAVES;
   unsigned grid = xcd_grid(nblk);

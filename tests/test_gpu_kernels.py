@@ -441,3 +441,49 @@ def test_lists_of_few_sinks(fmm, count, big):
         a, q = f.forces(_dev(pos[off[s]:off[s + 1]]), _dev(mass[off[s]:off[s + 1]]))
         assert torch.equal(acc[off[s]:off[s + 1]], a) and torch.equal(pot[off[s]:off[s + 1]], q)
     f.close()
+
+
+# lists of 8 entries or more (32 in FP64) are cut in these systems: a batch has more
+# segments than the partial sums have room for, so most lists are summed by one
+# wavefront in the batch and by several in a call of their own
+@pytest.mark.parametrize("precision,count,n", [("mixed", 16, 4096), ("mixed", 60, 2000), ("fp64", 48, 4096)])
+def test_large_batch_equals_single_calls(fmm, precision, count, n):
+    """Every system of a batch of half a million list entries and more sums as
+    it does alone, bit for bit."""
+    kinds = [W.plummer(n, 200)[::2], W.kroupa_with_central(n, 201)[::2], W.uniform_cube(n, 202)]
+    pos = np.concatenate([kinds[s % 3][0] for s in range(count)])
+    mass = np.concatenate([kinds[s % 3][1] for s in range(count)])
+    print(f"[gpu] batch of {count} x {n} {precision}", flush=True)
+    f = fmm.FMM(p=5, err_tol=1e-6, precision=precision)
+    acc, pot = f.forces_batch(_dev(pos), _dev(mass), np.arange(count + 1) * n)
+    st = f.stats()
+    assert st["n_p2p_cells"] > 65536 * 8
+    alone = [f.forces(_dev(q), _dev(m)) for q, m in kinds]
+    for s in range(count):
+        a, q = alone[s % 3]
+        assert torch.equal(acc[s * n:(s + 1) * n], a) and torch.equal(pot[s * n:(s + 1) * n], q), s
+    f.close()
+
+
+@pytest.mark.parametrize("n,n_leaf", [(1500, 64), (4096, 64), (5000, 5), (20000, 30)])
+def test_near_field_under_a_limit(fmm, n, n_leaf):
+    """With less room for partial sums more lists are summed unsplit: the
+    same bits, for forces in both precisions, jerk and gradient, and the same
+    again in frozen steps."""
+    pos, vel, mass = (_dev(a) for a in W.plummer(n, 300))
+    out = []
+    for limit in (0, 1 << 34):
+        print(f"[gpu] near field n={n} n_leaf={n_leaf} limit={limit}", flush=True)
+        f = fmm.FMM(p=6, err_tol=1e-6, n_leaf=n_leaf)
+        f.set_workspace_limit(limit)
+        r = [*f.jerk(pos, vel, mass, eps_soft=1e-4), *f.adjoint(pos, mass, vel, eps_soft=1e-4)]
+        r += f.forces(pos, mass)
+        r += f.adjoint_last(r[-2], vel)
+        r += f.forces_frozen(pos + 1e-3 * vel, mass, graph=True)
+        f.set_params(precision="mixed")
+        r += f.forces(pos, mass)
+        r += f.forces_frozen(pos + 1e-3 * vel, mass)
+        out.append(r)
+        f.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)

@@ -107,6 +107,27 @@ __device__ __forceinline__ void nf_decode(int code, int& seg, int& tile) {
   tile = code < 0 ? -code : code & 7;
 }
 
+// segment seg of the nseg of sink B's list [b, e) (M2lSeg)
+__device__ __forceinline__ void m2l_segment(const M2lSeg& sg, int B, int nseg, int seg, int& b, int& e) {
+  if (nseg <= 1) return;
+  int K = sg.seglen ? sg.seglen[B] : sg.K;
+  b += seg * K;
+  e = min(e, b + K);
+}
+// first source of [b, e) whose id is >= first_lo (ids are breadth first, so the
+// sources above the root levels form a prefix of the ascending list)
+__device__ __forceinline__ int split_point(const int* src, int b, int e, int first_lo) {
+  int lo = b, hi = e;
+  while (lo < hi) {
+    int mid = (lo + hi) >> 1;
+    if (src[mid] < first_lo)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
 // work item `it` of the plan: leaf index, segment and tile; false if there is none
 __device__ __forceinline__ bool nf_item(const NfPlan& plan, int it, int& li, int& seg, int& tile) {
   li = it;

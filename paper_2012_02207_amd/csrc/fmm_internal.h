@@ -128,17 +128,21 @@ struct NfPlan {
   int max_slots;          // partial slots
 };
 
-// Work items of the FP64 M2L over whole lists: item B < ncell is sink B (its
-// whole list, or the first K pairs of a long one), and a sink with more than
-// K pairs appends its later segments (sink, segment) as extra items, which
-// write partial expansions to slots pbase[B] + segment - 1; these are added
-// to the sink's expansion in segment order afterwards.
+// Work items of the M2L.  A sink's list of more than K pairs is cut into segments of
+// K (the last one shorter), whose expansions are formed one by one and added in
+// segment order; K depends on the sink's own system alone, and so does the result.
+// Item B < ncell is sink B (its whole list, or the first segment), the later
+// segments are extra items (sink, segment), which write to slots
+// pbase[B] + segment - 1, added afterwards.  The kernel of orders above 16, whose
+// expansions are large, also takes a plan without extra items (pbase[B] < 0 for
+// every list of segments): item B then adds up the segments itself.
 struct M2lSeg {
   const int* nseg;    // segments of each sink (null: one item per sink)
-  const int* pbase;   // first partial slot of each split sink
+  const int* pbase;   // first partial slot of each split sink, -1 of the others of segments
   const int2* extra;  // (sink, segment) of the extra items
   const int* nextra;  // extra item count (device)
   double* part;       // partial expansions, one slot each
+  const int* seglen;  // K of each sink (null: the K below, of one system)
   int K;              // pairs per segment
   int max_items;      // host bound on the item count (grid size)
 };
@@ -258,7 +262,7 @@ struct Ctx {
   dbuf<int2> nf_extra;
   dbuf<double4> nf_part;
   NfPlan nf{};
-  dbuf<int> m2l_nseg, m2l_pbase;
+  dbuf<int> m2l_nseg, m2l_pbase, m2l_seglen;
   dbuf<int2> m2l_extra;
   dbuf<double> m2l_part;
 
@@ -329,9 +333,8 @@ void direct_sum(int64_t n, const double* pos, const double* mass, double eps2, i
 bool check_inputs_dev(Ctx& c, const double* pos, const double* mass, int64_t n);
 
 // the M2L's segment plan, and the sums of the split sinks' partial expansions
-constexpr int M2L_SEG = 512, M2L_HI_SEG = 512;  // pairs per segment, at least
-M2lSeg plan_m2l(Ctx& c, int seg_min);
-void combine_m2l(Ctx& c, const M2lSeg& sg, double* loc);
+M2lSeg plan_m2l(Ctx& c, int first, bool split);
+void combine_m2l(Ctx& c, const M2lSeg& sg, int first, double* loc);
 // M2L launchers (one per compiled order)
 void launch_m2l_fp64(Ctx& c);
 // constant tables of the kernels, uploaded once per device at context creation

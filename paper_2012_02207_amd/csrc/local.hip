@@ -654,7 +654,8 @@ void plan_near_field(Ctx& c) {
     // buffers of the M2L, the only ones still to come.
     int64_t few = ceil_div(cnt, 4);
     if (c.ws.arena) {
-      int64_t m2l = 12 * c.ncell + 24 * 8192 + (std::min<int64_t>(8192, c.m2l.count / 512) + 1) * ncoef(c.p) * 16;
+      int64_t pairs = c.m2l.count / 512 + 1;  // segments of M2L lists, at most
+      int64_t m2l = 12 * c.ncell + pairs * (8 + (c.p <= FMM_GPU_PMAX ? ncoef(c.p) * 16 : 0)) + 65536;
       int64_t left = (int64_t)(c.ws.arena_cap - c.ws.arena_used) - m2l - c.n - 8192;
       few = std::max(few, left / 40);
     }

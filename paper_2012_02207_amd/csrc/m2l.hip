@@ -374,30 +374,43 @@ __global__ void __launch_bounds__(64 * m2l_waves(P)) __attribute__((amdgpu_waves
     }
     int b = off[B], e = off[B + 1];
     double* out = loc + (size_t)B * NC * 2;
-    if (sg.nseg[B] > 1) {
-      b += seg * sg.K;
-      e = min(e, b + sg.K);
-      if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
-    }
+    m2l_segment(sg, B, sg.nseg[B], seg, b, e);
+    if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
     m2l_range_fp64<P>(B, b, e, lane, src, cx, cy, cz, mult, out, acc);
   }
 }
 
-// The segment plan of the M2L over whole lists (one thread per sink); ctr[0]
-// counts the extra items (zero on entry), and a split sink's partial slots
-// follow its extra items.
-__global__ void k_m2l_plan(int ncell, const int* __restrict__ off, int K, int* nseg, int* pbase, int2* extra,
-                           int* ctr) {
-  int B = blockIdx.x * blockDim.x + threadIdx.x;
+// Pairs per segment, at least M2L_SEG and a M2L_SEG_DIV-th of the system's bodies:
+// the longest lists of a system (2^18 bodies, p = 10: one of 8668 pairs, 19.5 times
+// the mean) are otherwise a wavefront's work long after the others have ended.
+constexpr int M2L_SEG = 512, M2L_SEG_DIV = 384;
+__host__ __device__ inline int m2l_seg_pairs(int64_t bodies) {
+  return (int)(bodies / M2L_SEG_DIV > M2L_SEG ? bodies / M2L_SEG_DIV : M2L_SEG);
+}
+
+// The segment plan, one thread per sink from `first` on, over its sources from
+// `first` on; with split, the lists' later segments become extra items.  ctr[0]
+// counts them (zero on entry); a split sink's partial slots follow its extra items.
+__global__ void k_m2l_plan(int ncell, int first, const int* __restrict__ off, const int* __restrict__ src,
+                           const int* __restrict__ cb, const int* __restrict__ sys_off, int nsys, int K, bool split,
+                           int* nseg, int* pbase, int* seglen, int2* extra, int* ctr) {
+  int B = first + blockIdx.x * blockDim.x + threadIdx.x;
   if (B >= ncell) return;
-  int len = off[B + 1] - off[B];
-  int ns = len > K ? (len + K - 1) / K : 1;
-  nseg[B] = ns;
-  if (ns > 1) {
-    int x = atomicAdd(ctr, ns - 1);
-    for (int k = 1; k < ns; k++) extra[x + k - 1] = make_int2(B, k);
-    pbase[B] = x;
+  if (nsys > 1) {
+    int s = system_of(sys_off, nsys, cb[B]);
+    K = m2l_seg_pairs(sys_off[s + 1] - sys_off[s]);
+    seglen[B] = K;
   }
+  int b = off[B], e = off[B + 1];
+  int len = e - (first > 0 ? split_point(src, b, e, first) : b);
+  int ns = len > K ? (len - 1) / K + 1 : 1;
+  int at = -1;
+  if (ns > 1 && split) {
+    at = atomicAdd(ctr, ns - 1);
+    for (int k = 1; k < ns; k++) extra[at + k - 1] = make_int2(B, k);
+  }
+  nseg[B] = ns;
+  pbase[B] = at;
 }
 
 // the partial expansions of split sinks added in segment order (threads of
@@ -416,34 +429,36 @@ __global__ void k_m2l_combine(int ncd, int max_extra, const int* __restrict__ ns
   loc[(size_t)B * ncd + k] = s;
 }
 
-constexpr int M2L_SEG_DIV = 8192;  // pairs per segment: at least the list total / M2L_SEG_DIV
-
-// the plan for the M2L over whole lists (on c.stream), at least seg_min pairs
-// per segment
-M2lSeg plan_m2l(Ctx& c, int seg_min) {
+// the plan for the sinks from `first` on and their sources from there on (on
+// c.stream)
+M2lSeg plan_m2l(Ctx& c, int first, bool split) {
   int nc = (int)c.ncell;
   int64_t cnt = c.m2l.count;
-  int K = (int)std::max<int64_t>(seg_min, ceil_div(cnt, M2L_SEG_DIV));
-  // a split sink holds len > K pairs in ceil(len / K) < 2 len / K segments, so
-  // the extra items number fewer than cnt / K <= M2L_SEG_DIV
-  int64_t extra_max = std::min<int64_t>(M2L_SEG_DIV, ceil_div(cnt, K));
+  int K = m2l_seg_pairs(c.nsys > 1 ? 1 : c.n);
+  // a list of len > K pairs has ceil(len / K) segments, so the later ones number
+  // fewer than cnt / K (their partial expansions take 2 bytes per pair at p = 10,
+  // 5 at p = 16, where the lists take 16 and more)
+  int64_t extra_max = split ? ceil_div(cnt, K) : 0;
   size_t ncd = (size_t)ncoef(c.p) * 2;
   ensure(c.ws, c.m2l_nseg, (size_t)nc + 1);
   ensure(c.ws, c.m2l_pbase, (size_t)nc + 1);
+  if (c.nsys > 1) ensure(c.ws, c.m2l_seglen, (size_t)nc);
   ensure(c.ws, c.m2l_extra, (size_t)extra_max + 1);
   ensure(c.ws, c.m2l_part, (size_t)(extra_max + 1) * ncd);
   ensure(c.ws, c.counters, 512);
   int* ctr = c.counters.p + 46;
   zero_fill(c, ctr, sizeof(int));
-  hipLaunchKernelGGL(k_m2l_plan, dim3((unsigned)ceil_div(nc, 256)), dim3(256), 0, c.stream, nc, c.m2l.off.p, K,
-                     c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr);
+  hipLaunchKernelGGL(k_m2l_plan, dim3((unsigned)ceil_div(nc - first, 256)), dim3(256), 0, c.stream, nc, first,
+                     c.m2l.off.p, c.m2l.src.p, c.c_begin.p, c.sys_off.p, c.nsys, K, split, c.m2l_nseg.p,
+                     c.m2l_pbase.p, c.m2l_seglen.p, c.m2l_extra.p, ctr);
   HIPCHK(hipGetLastError());
-  return M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p, K, (int)(nc + extra_max)};
+  return M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p,
+                c.nsys > 1 ? c.m2l_seglen.p : nullptr, K, (int)(nc - first + extra_max)};
 }
 
-// adds the partial expansions of the plan's split sinks
-void combine_m2l(Ctx& c, const M2lSeg& sg, double* loc) {
-  int ncd = ncoef(c.p) * 2, max_extra = sg.max_items - (int)c.ncell;
+// adds the partial expansions of the split sinks of a plan from `first` on
+void combine_m2l(Ctx& c, const M2lSeg& sg, int first, double* loc) {
+  int ncd = ncoef(c.p) * 2, max_extra = sg.max_items - ((int)c.ncell - first);
   if (max_extra > 0)
     hipLaunchKernelGGL(k_m2l_combine, dim3((unsigned)ceil_div((int64_t)max_extra * ncd, 256)), dim3(256), 0,
                        c.stream, ncd, max_extra, sg.nseg, sg.pbase, sg.extra, sg.nextra, sg.part, loc);
@@ -462,14 +477,14 @@ static void launch_p(Ctx& c, int first_lo, const double* mult, double* loc, cons
     return;
   }
   M2lSeg sg{};
-  if (first_lo >= nc) sg = plan_m2l(c, M2L_SEG);  // whole lists: long ones in segments
+  if (first_lo >= nc) sg = plan_m2l(c, 0, true);  // whole lists: long ones in segments
   int nitems = sg.nseg ? sg.max_items : nc;
   int nblk = (nitems + m2l_waves(P) - 1) / m2l_waves(P);
   unsigned grid = xcd_grid(nblk);
   hipLaunchKernelGGL((k_m2l_fp64<P, false>), dim3(grid), dim3(64 * m2l_waves(P)), 0, c.stream, nc, first_lo,
                      (const int*)nullptr, (const int*)nullptr, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p,
                      c.c_cz.p, mult, loc, sg);
-  if (sg.nseg) combine_m2l(c, sg, loc);
+  if (sg.nseg) combine_m2l(c, sg, 0, loc);
 }
 
 template <int P>

@@ -253,127 +253,121 @@ __global__ void __launch_bounds__(64 * hi::WAVES) k_m2l_hi(int p, int ncell, int
       B = x.x;
       seg = x.y;
     }
-    int b = off[B], e = off[B + 1];
-    if (B >= first_lo) {
-      int lo = b, hi = e;
-      while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (src[mid] < first_lo)
-          lo = mid + 1;
-        else
-          hi = mid;
-      }
-      e = lo;
-    }
+    int b0 = off[B], e0 = off[B + 1];
+    if (B >= first_lo) e0 = split_point(src, b0, e0, first_lo);
     double* out = loc + (size_t)B * NC * 2;
-    if (sg.nseg && sg.nseg[B] > 1) {
-      b += seg * sg.K;
-      e = min(e, b + sg.K);
-      if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
-    }
-    if (b == e) {
+    if (b0 == e0) {
       for (int k = tid; k < NC * 2; k += 64 * hi::WAVES) out[k] = 0.0;
       continue;
     }
-    __syncthreads();  // the previous item's sums have been read
-    for (int k = tid; k < S; k += 64 * hi::WAVES) acc[k] = 0.0;
     double bx = cx[B], by = cy[B], bz = cz[B];
-    for (int base = b; base < e; base += PT) {
-      __syncthreads();  // the previous pairs' tables have been read
-      if (tid < 2 * PT) {  // angle multiples by the angle-addition recurrence, alpha and -theta
-        int pr = tid % PT, k = base + pr;
-        bool act = k < e;
-        int A = src[act ? k : b];
-        double Rx = bx - cx[A], Ry = by - cy[A], Rz = bz - cz[A];
-        double rho2 = fma(Rx, Rx, Ry * Ry);
-        double r2 = fma(Rz, Rz, rho2);
-        double rinv = 1.0 / sqrt(r2), rho = sqrt(rho2);
-        double c1, s1;
-        double2* t;
-        if (tid < PT) {
-          c1 = rho > 0.0 ? Ry / rho : 0.0;
-          s1 = rho > 0.0 ? Rx / rho : 1.0;
-          t = ta;
-          ids[pr] = A;
-          rin[pr] = act ? rinv : 0.0;
-        } else {
-          c1 = Rz * rinv;
-          s1 = -rho * rinv;
-          t = tb;
-        }
-        double cm = 1.0, sm = 0.0;
-        for (int m = 0; m <= p; m++) {
-          t[m * PT + pr] = make_double2(cm, sm);
-          double c2 = fma(cm, c1, -sm * s1);
-          sm = fma(sm, c1, cm * s1);
-          cm = c2;
-        }
-      }
-      __syncthreads();
-      {
-        const double2* M[NT];
-#pragma unroll
-        for (int t = 0; t < NT; t++) M[t] = (const double2*)mult + (size_t)ids[16 * t + (lane & 15)] * NC;
-        if (n0 <= p) o0.forward(n0, p, M, ta, tb, V, RS, lane);
-        if (n1 <= p) o1.forward(n1, p, M, ta, tb, V, RS, lane);
-        if (n2 <= p) o2.forward(n2, p, M, ta, tb, V, RS, lane);
-        if (PM >= 24 && n3 <= p) o3.forward(n3, p, M, ta, tb, V, RS, lane);
-      }
-      __syncthreads();
-      // Translation along z, Lhat_n^m = (-1)^{n+m} / ((n-m)!(n+m)!)
-      // sum_{k=m}^{p-n} M'_k^m j!/r^{j+1}, j = n + k: a wavefront per order m, a
-      // lane per pair and part, in place (the lane reads its column, then writes)
-      for (int h = 0; h < 2; h++) {
-        int m = h ? 15 - wv : wv, part = lane / PT, col = lane % PT, K = p - 2 * m;
-        if (K < 0) continue;
-        double g[T_MAX], s[T_MAX];
-        double ri = rin[col], rp = ri;
-        for (int j = 0; j < 2 * m; j++) rp *= ri;
-#pragma unroll
-        for (int j = 0; j < T_MAX; j++) {
-          s[j] = 0.0;
-          if (j <= K) {
-            g[j] = c_fact_hi[2 * m + j] * rp;
-            rp *= ri;
+    int nseg = sg.nseg ? sg.nseg[B] : 1, send = seg + 1;
+    if (nseg > 1 && sg.pbase[B] < 0) send = nseg;
+    if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
+    for (bool add = false; seg < send; seg++, add = true) {
+      int b = b0, e = e0;
+      m2l_segment(sg, B, nseg, seg, b, e);
+      __syncthreads();  // the previous sums have been read
+      for (int k = tid; k < S; k += 64 * hi::WAVES) acc[k] = 0.0;
+      for (int base = b; base < e; base += PT) {
+        __syncthreads();  // the previous pairs' tables have been read
+        if (tid < 2 * PT) {  // angle multiples by the angle-addition recurrence, alpha and -theta
+          int pr = tid % PT, k = base + pr;
+          bool act = k < e;
+          int A = src[act ? k : b];
+          double Rx = bx - cx[A], Ry = by - cy[A], Rz = bz - cz[A];
+          double rho2 = fma(Rx, Rx, Ry * Ry);
+          double r2 = fma(Rz, Rz, rho2);
+          double rinv = 1.0 / sqrt(r2), rho = sqrt(rho2);
+          double c1, s1;
+          double2* t;
+          if (tid < PT) {
+            c1 = rho > 0.0 ? Ry / rho : 0.0;
+            s1 = rho > 0.0 ? Rx / rho : 1.0;
+            t = ta;
+            ids[pr] = A;
+            rin[pr] = act ? rinv : 0.0;
           } else {
-            g[j] = 0.0;
+            c1 = Rz * rinv;
+            s1 = -rho * rinv;
+            t = tb;
+          }
+          double cm = 1.0, sm = 0.0;
+          for (int m = 0; m <= p; m++) {
+            t[m * PT + pr] = make_double2(cm, sm);
+            double c2 = fma(cm, c1, -sm * s1);
+            sm = fma(sm, c1, cm * s1);
+            cm = c2;
           }
         }
-        if (part < 2 && !(m == 0 && part == 1)) {
-          int row = part ? 2 * m : m > 0 ? 2 * m - 1 : 0;
+        __syncthreads();
+        {
+          const double2* M[NT];
 #pragma unroll
-          for (int kk = 0; kk < T_MAX; kk++) {
-            if (kk <= K) {
-              int k = m + kk;
-              double x = V[(k * k + row) * RS + col];
+          for (int t = 0; t < NT; t++) M[t] = (const double2*)mult + (size_t)ids[16 * t + (lane & 15)] * NC;
+          if (n0 <= p) o0.forward(n0, p, M, ta, tb, V, RS, lane);
+          if (n1 <= p) o1.forward(n1, p, M, ta, tb, V, RS, lane);
+          if (n2 <= p) o2.forward(n2, p, M, ta, tb, V, RS, lane);
+          if (PM >= 24 && n3 <= p) o3.forward(n3, p, M, ta, tb, V, RS, lane);
+        }
+        __syncthreads();
+        // Translation along z, Lhat_n^m = (-1)^{n+m} / ((n-m)!(n+m)!)
+        // sum_{k=m}^{p-n} M'_k^m j!/r^{j+1}, j = n + k: a wavefront per order m, a
+        // lane per pair and part, in place (the lane reads its column, then writes)
+        for (int h = 0; h < 2; h++) {
+          int m = h ? 15 - wv : wv, part = lane / PT, col = lane % PT, K = p - 2 * m;
+          if (K < 0) continue;
+          double g[T_MAX], s[T_MAX];
+          double ri = rin[col], rp = ri;
+          for (int j = 0; j < 2 * m; j++) rp *= ri;
 #pragma unroll
-              for (int nn = 0; nn < T_MAX - kk; nn++)
-                if (nn + kk <= K) s[nn] = fma(x, g[nn + kk], s[nn]);
+          for (int j = 0; j < T_MAX; j++) {
+            s[j] = 0.0;
+            if (j <= K) {
+              g[j] = c_fact_hi[2 * m + j] * rp;
+              rp *= ri;
+            } else {
+              g[j] = 0.0;
             }
           }
+          if (part < 2 && !(m == 0 && part == 1)) {
+            int row = part ? 2 * m : m > 0 ? 2 * m - 1 : 0;
 #pragma unroll
-          for (int nn = 0; nn < T_MAX; nn++) {
-            if (nn <= K) {
-              int n = m + nn;
-              double f = ((nn & 1) ? -1.0 : 1.0) / (c_fact_hi[nn] * c_fact_hi[n + m]);
-              V[(n * n + row) * RS + col] = s[nn] * f;
+            for (int kk = 0; kk < T_MAX; kk++) {
+              if (kk <= K) {
+                int k = m + kk;
+                double x = V[(k * k + row) * RS + col];
+#pragma unroll
+                for (int nn = 0; nn < T_MAX - kk; nn++)
+                  if (nn + kk <= K) s[nn] = fma(x, g[nn + kk], s[nn]);
+              }
+            }
+#pragma unroll
+            for (int nn = 0; nn < T_MAX; nn++) {
+              if (nn <= K) {
+                int n = m + nn;
+                double f = ((nn & 1) ? -1.0 : 1.0) / (c_fact_hi[nn] * c_fact_hi[n + m]);
+                V[(n * n + row) * RS + col] = s[nn] * f;
+              }
             }
           }
         }
+        __syncthreads();
+        if (n0 <= p) o0.back(n0, p, ta, tb, V, RS, acc, lane);
+        if (n1 <= p) o1.back(n1, p, ta, tb, V, RS, acc, lane);
+        if (n2 <= p) o2.back(n2, p, ta, tb, V, RS, acc, lane);
+        if (PM >= 24 && n3 <= p) o3.back(n3, p, ta, tb, V, RS, acc, lane);
       }
       __syncthreads();
-      if (n0 <= p) o0.back(n0, p, ta, tb, V, RS, acc, lane);
-      if (n1 <= p) o1.back(n1, p, ta, tb, V, RS, acc, lane);
-      if (n2 <= p) o2.back(n2, p, ta, tb, V, RS, acc, lane);
-      if (PM >= 24 && n3 <= p) o3.back(n3, p, ta, tb, V, RS, acc, lane);
-    }
-    __syncthreads();
-    // back to the unscaled basis: L_n^m = (n-m)!(n+m)! Lhat_n^m
-    for (int u = tid; u < S; u += 64 * hi::WAVES) {
-      int n = both_sign_n(u), j = u - n * n, m = (j + 1) >> 1;
-      bool im = j > 0 && !(j & 1);
-      out[2 * cidx(n, m) + (im ? 1 : 0)] = acc[u] * (c_fact_hi[n - m] * c_fact_hi[n + m]);
-      if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
+      // back to the unscaled basis: L_n^m = (n-m)!(n+m)! Lhat_n^m
+      for (int u = tid; u < S; u += 64 * hi::WAVES) {
+        int n = both_sign_n(u), j = u - n * n, m = (j + 1) >> 1;
+        bool im = j > 0 && !(j & 1);
+        double* o = out + 2 * cidx(n, m) + (im ? 1 : 0);
+        double v = acc[u] * (c_fact_hi[n - m] * c_fact_hi[n + m]);
+        *o = add ? *o + v : v;
+        if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
+      }
     }
   }
 }
@@ -413,7 +407,8 @@ void launch_m2l_hi(Ctx& c, int first_lo, const double* mult, double* loc, const 
   upload_hi_tables();
   int nc = (int)c.ncell;
   M2lSeg sg{};
-  if (!sinks && first_lo >= nc) sg = plan_m2l(c, M2L_HI_SEG);
+  // (where memory is limited no list is split: its partial expansions take up to 8 KB each)
+  if (!sinks && first_lo >= nc) sg = plan_m2l(c, 0, !c.ws.arena && !c.ws.limit);
   unsigned grid = sinks ? 2048u : (unsigned)std::max(sg.nseg ? sg.max_items : nc, 1);
   // 32 pairs at a time where their coefficients fit the 160 KB of LDS (p <= 20)
   constexpr int P_TWO = 20;
@@ -422,7 +417,7 @@ void launch_m2l_hi(Ctx& c, int first_lo, const double* mult, double* loc, const 
                      c.p, nc, first_lo, sinks, nsinks, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult,
                      loc, sg);
   HIPCHK(hipGetLastError());
-  if (sg.nseg) combine_m2l(c, sg, loc);
+  if (sg.nseg) combine_m2l(c, sg, 0, loc);
 }
 
 }  // namespace fmm

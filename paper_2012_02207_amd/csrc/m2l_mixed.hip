@@ -143,20 +143,6 @@ __device__ __forceinline__ void angle_table(float c1, float s1, float* cm, float
 
 constexpr int MX_WAVES = 4;  // wavefronts of a workgroup, at most
 
-// first source of [b, e) whose id is >= first_lo (ids are breadth first, so the
-// sources above the root levels form a prefix of the ascending list)
-__device__ __forceinline__ int split_point(const int* src, int b, int e, int first_lo) {
-  int lo = b, hi = e;
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    if (src[mid] < first_lo)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
 // One wavefront per sink (or wps of them, each with a contiguous part of the
 // list), a source per lane.  Up to p = 10, four waves per
 // SIMD (at most 128 VGPRs: a few bytes spill at p = 10, measured faster than
@@ -208,11 +194,8 @@ __global__ void __launch_bounds__(64 * MX_WAVES) __attribute__((amdgpu_waves_per
   if (live) {
     e = off[B + 1];
     b = split_point(src, off[B], e, first_lo);
-    if (sg.nseg && sg.nseg[B] > 1) {
-      b += seg * sg.K;
-      e = min(e, b + sg.K);
-      if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
-    }
+    if (sg.nseg) m2l_segment(sg, B, sg.nseg[B], seg, b, e);
+    if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
   }
   int lane = threadIdx.x & 63;
   if (wps == 1 && b == e) {  // no FP32 pair: the sink's expansion starts at zero
@@ -405,43 +388,6 @@ __global__ void k_scale(int ncell, const double* rad, double* scale) {
   if (c < ncell) scale[c] = rad[c] > 0.0 ? rad[c] : 1.0;
 }
 
-// The segment plan of the FP32 M2L (one thread per sink below the root
-// levels; its FP32 pairs are the list's suffix from split_point); ctr[0]
-// counts the extra items (zero on entry).
-__global__ void k_m2l32_plan(int ncell, int first_lo, const int* __restrict__ off, const int* __restrict__ src,
-                             int K, int* nseg, int* pbase, int2* extra, int* ctr) {
-  int B = first_lo + blockIdx.x * blockDim.x + threadIdx.x;
-  if (B >= ncell) return;
-  int e = off[B + 1];
-  int len = e - split_point(src, off[B], e, first_lo);
-  int ns = len > K ? (len + K - 1) / K : 1;
-  nseg[B] = ns;
-  if (ns > 1) {
-    int x = atomicAdd(ctr, ns - 1);
-    for (int k = 1; k < ns; k++) extra[x + k - 1] = make_int2(B, k);
-    pbase[B] = x;
-  }
-}
-
-// partial expansions of split sinks added in segment order (threads of each
-// sink's first extra item, one per coefficient)
-__global__ void k_m2l32_combine(int ncd, int max_extra, const int* __restrict__ nseg, const int* __restrict__ pbase,
-                                const int2* __restrict__ extra, const int* __restrict__ nextra,
-                                const double* __restrict__ part, double* loc) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int x = (int)(t / ncd), k = (int)(t % ncd);
-  if (x >= max_extra || x >= *nextra) return;
-  int2 v = extra[x];
-  if (v.y != 1) return;
-  int B = v.x, ns = nseg[B];
-  double s = loc[(size_t)B * ncd + k];
-  for (int g = 1; g < ns; g++) s += part[(size_t)(pbase[B] + g - 1) * ncd + k];
-  loc[(size_t)B * ncd + k] = s;
-}
-
-constexpr int M2L32_SEG_MIN = 512;   // FP32 pairs per segment, at least
-constexpr int M2L32_SEG_DIV = 8192;  // and at least the list total / M2L32_SEG_DIV
-
 template <int P>
 static void launch_p32(Ctx& c, int first_lo) {
   int nc = (int)c.ncell;
@@ -449,36 +395,13 @@ static void launch_p32(Ctx& c, int first_lo) {
   if (nlo <= 0) return;
   int wps = c.prm.m2l_waves;
   M2lSeg sg{};
-  int64_t extra_max = 0;
-  if (wps == 1) {  // long lists in segments (see M2lSeg)
-    int64_t cnt = c.m2l.count;
-    int K = (int)std::max<int64_t>(M2L32_SEG_MIN, ceil_div(cnt, M2L32_SEG_DIV));
-    // split sinks hold len > K pairs in ceil(len / K) < 2 len / K segments:
-    // fewer than cnt / K <= M2L32_SEG_DIV extra items
-    extra_max = std::min<int64_t>(M2L32_SEG_DIV, ceil_div(cnt, K));
-    size_t ncd = (size_t)ncoef(P) * 2;
-    ensure(c.ws, c.m2l_nseg, (size_t)nc + 1);
-    ensure(c.ws, c.m2l_pbase, (size_t)nc + 1);
-    ensure(c.ws, c.m2l_extra, (size_t)extra_max + 1);
-    ensure(c.ws, c.m2l_part, (size_t)(extra_max + 1) * ncd);
-    ensure(c.ws, c.counters, 512);
-    int* ctr = c.counters.p + 46;
-    zero_fill(c, ctr, sizeof(int));
-    hipLaunchKernelGGL(k_m2l32_plan, dim3((unsigned)ceil_div(nlo, 256)), dim3(256), 0, c.stream, nc, first_lo,
-                       c.m2l.off.p, c.m2l.src.p, K, c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr);
-    HIPCHK(hipGetLastError());
-    sg = M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p, K, (int)(nlo + extra_max)};
-  }
+  if (wps == 1) sg = plan_m2l(c, first_lo, true);  // long lists in segments
   int nitems = sg.nseg ? sg.max_items : nlo;
   unsigned grid = xcd_grid(nitems);
   hipLaunchKernelGGL(k_m2l_fp32<P>, dim3(grid), dim3(64 * wps), sizeof(double) * wps * (P + 1) * 64, c.stream, nc, first_lo,
                      c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.scale.p, c.nmult.p, c.loc.p,
                      wps, sg);
-  if (sg.nseg && extra_max > 0) {
-    int ncd = ncoef(P) * 2;
-    hipLaunchKernelGGL(k_m2l32_combine, dim3((unsigned)ceil_div(extra_max * ncd, 256)), dim3(256), 0, c.stream,
-                       ncd, (int)extra_max, sg.nseg, sg.pbase, sg.extra, sg.nextra, sg.part, c.loc.p);
-  }
+  if (sg.nseg) combine_m2l(c, sg, first_lo, c.loc.p);
 }
 
 template <int P>

@@ -487,3 +487,47 @@ def test_near_field_under_a_limit(fmm, n, n_leaf):
         f.close()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# M2L lists of more than 512 pairs (a 384th of the bodies, if that is more) are cut,
+# also in batches of over four million pairs
+@pytest.mark.parametrize("precision,p,count,n,n_leaf", [("fp64", 5, 12, 30000, 64), ("mixed", 5, 12, 30000, 64),
+                                                        ("fp64", 4, 40, 8000, 6), ("mixed", 11, 40, 8000, 6),
+                                                        ("fp64", 18, 12, 5000, 6), ("fp64", 16, 4, 6000, 6)])
+def test_batch_m2l_segments(fmm, precision, p, count, n, n_leaf):
+    """Every system of a batch sums as it does alone, bit for bit."""
+    kinds = [W.plummer(n, 200)[::2], W.kroupa_with_central(n, 201)[::2], W.uniform_cube(n, 202)]
+    pos = np.concatenate([kinds[s % 3][0] for s in range(count)])
+    mass = np.concatenate([kinds[s % 3][1] for s in range(count)])
+    print(f"[gpu] batch of {count} x {n} {precision} p={p} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=p, err_tol=1e-6, precision=precision, n_leaf=n_leaf)
+    acc, pot = f.forces_batch(_dev(pos), _dev(mass), np.arange(count + 1) * n)
+    assert count < 40 or f.stats()["n_m2l"] > 2 * 512 * 8192
+    alone, longest = [], 0
+    for q, m in kinds:
+        alone.append(f.forces(_dev(q), _dev(m)))
+        longest = max(longest, np.bincount(f.export("m2l")[:, 0]).max())
+    assert longest > 512
+    for s in range(count):
+        a, q = alone[s % 3]
+        assert torch.equal(acc[s * n:(s + 1) * n], a) and torch.equal(pot[s * n:(s + 1) * n], q), s
+    f.close()
+
+
+@pytest.mark.parametrize("p,n,n_leaf", [(17, 9000, 6), (22, 12000, 8)])
+def test_high_order_m2l_under_a_limit(fmm, p, n, n_leaf):
+    """Without slots for partial expansions (a workspace limit, the fixed
+    scratch) long lists are summed by one workgroup: the same bits."""
+    pos, vel, mass = (_dev(a) for a in W.kroupa_with_central(n, 400))
+    out = []
+    for limit in (0, 1 << 34):
+        print(f"[gpu] high-order M2L p={p} n={n} limit={limit}", flush=True)
+        f = fmm.FMM(p=p, err_tol=1e-6, n_leaf=n_leaf)
+        f.set_workspace_limit(limit)
+        out.append([*f.forces(pos, mass), *f.adjoint(pos, mass, vel)])
+        assert np.bincount(f.export("m2l")[:, 0]).max() > 512
+    out.append([*f.forces(pos, mass, noalloc=True), *out[0][2:]])
+    f.close()
+    for r in out[1:]:
+        for a, b in zip(out[0], r):
+            assert torch.equal(a, b)

@@ -491,10 +491,10 @@ fmm_status fmm_stats(fmm_ctx* ctx, fmm_stats_t* out) {
       }
       // body-pair count of the near field
       if (c.evaluated) {  // counted by the leaf kernel of the last evaluation
-        unsigned long long* d = (unsigned long long*)(c.counters.p + NF_COUNTERS);
-        HIPCHK(hipMemcpyAsync(c.hbuf, d, 8, hipMemcpyDeviceToHost, c.stream));
+        std::vector<unsigned long long> d(NF_PAIR_SLOTS * NF_PAIR_STRIDE / 2);
+        HIPCHK(hipMemcpyAsync(d.data(), c.counters.p + NF_PAIRS, d.size() * 8, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));
-        out->n_p2p_pairs = c.hbuf[0];
+        for (size_t k = 0; k < d.size(); k += NF_PAIR_STRIDE / 2) out->n_p2p_pairs += (int64_t)d[k];
         // the near field's work items: the leaves and the later segments
         HIPCHK(hipMemcpyAsync(c.hbuf, c.counters.p + NF_COUNTERS + 2, 4, hipMemcpyDeviceToHost, c.stream));
         HIPCHK(hipStreamSynchronize(c.stream));

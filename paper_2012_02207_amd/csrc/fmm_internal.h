@@ -117,7 +117,11 @@ struct CellList {
 // an item each (leaf, segment, tile): otherwise a large leaf with a long list
 // is one wavefront's work long after the others have ended.
 constexpr int NF_TILE = 8;
-constexpr int NF_COUNTERS = 72;  // offset in Ctx::counters
+// Counters in Ctx::counters: those of the plan, then the body pairs, a sum per
+// NF_PAIR_SLOT on a cache line of its own (atomics on one address take 12.5 ns each:
+// with a single sum they bound the near field of 30000 systems of 100 bodies at 6.9 ms)
+constexpr int NF_COUNTERS = 512, NF_PAIRS = NF_COUNTERS + 32, NF_PAIR_SLOTS = 64, NF_PAIR_STRIDE = 32;
+constexpr int COUNTERS = NF_PAIRS + NF_PAIR_SLOTS * NF_PAIR_STRIDE;
 struct NfPlan {
   const int* cell_nseg;   // segments of each leaf, by cell id
   const int* cell_pbase;  // first partial slot of each split leaf, -1 of the others, by cell id
@@ -226,10 +230,10 @@ struct Ctx {
   // device counters (ints), by offset: [4..5] number of body chunks of the
   // cells (long long, read by the radius and cell-minimum kernels); [32] input
   // check; [46] extra items of the M2L; [48..49] FP32 M2L pairs (stats); [64] sinks
-  // with root-level pairs; near field, from NF_COUNTERS on: +0, +1 body pairs (long
-  // long), +2 later segments (stats), +3 extra items, +4, +5 partial slots and +6, +7
-  // later segments' items asked for (long long); [256..] walk (64-bit counters at
-  // even int offsets)
+  // with root-level pairs; [256..] walk (64-bit counters at even int offsets); near
+  // field: from NF_COUNTERS on +2 later segments (stats), +3 extra items, +4, +5
+  // partial slots and +6, +7 later segments' items asked for (long long), from
+  // NF_PAIRS on body pairs (long long, stats)
   dbuf<int> counters;
   CellList est_far, est_near, m2l, p2p;
   int64_t n_p2p_pairs = 0;

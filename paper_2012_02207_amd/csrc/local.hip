@@ -181,6 +181,11 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
 // of 16384 37.7 (36.6).
 constexpr int LG_WAVES = 1;
 
+// the pairs of an item added to the sum of its workgroup's slot (NF_PAIRS)
+__device__ __forceinline__ void count_pairs(unsigned long long* npairs, long long pairs) {
+  atomicAdd(npairs + (blockIdx.x & (NF_PAIR_SLOTS - 1)) * (NF_PAIR_STRIDE / 2), (unsigned long long)pairs);
+}
+
 // the sinks i0 .. i0 + TS over the list src[qb .. qe), their sums to out or (add)
 // onto what is there; returns the body pairs (a body with itself is none)
 template <int TS>
@@ -264,7 +269,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
 #undef FMM_NEAR_TILE
     }
   }
-  if (lane == 0 && pairs > 0) atomicAdd(npairs, (unsigned long long)pairs);
+  if (lane == 0 && pairs > 0) count_pairs(npairs, pairs);
 }
 
 // Mixed precision: the n_B sink bodies are replicated over
@@ -535,7 +540,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) __attribute__((amdgpu_waves_per
     }
     __builtin_amdgcn_wave_barrier();
   }
-  if (lane == 0 && pairs > 0) atomicAdd(npairs, (unsigned long long)pairs);
+  if (lane == 0 && pairs > 0) count_pairs(npairs, pairs);
 }
 
 // Which of the two kernels the near field of a context takes: in every precision
@@ -681,9 +686,9 @@ void launch_near_field(Ctx& c) {
   if (c.nleaf <= 0) return;
   ensure(c.ws, c.nearbuf, (size_t)c.n);
   const int* leaves = c.leaves.p;
-  // body-pair count of the near field, read by fmm_stats
-  unsigned long long* npairs = (unsigned long long*)(c.counters.p + NF_COUNTERS);
-  zero_fill(c, npairs, 8 * sizeof(int));
+  // the plan's counters and the body-pair counts, read by fmm_stats
+  unsigned long long* npairs = (unsigned long long*)(c.counters.p + NF_PAIRS);
+  zero_fill(c, c.counters.p + NF_COUNTERS, (COUNTERS - NF_COUNTERS) * sizeof(int));
   plan_near_field(c);
   int nblk = (c.nf.max_items + LG_WAVES - 1) / LG_WAVES;
   unsigned grid = xcd_grid(nblk);

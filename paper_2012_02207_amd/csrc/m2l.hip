@@ -445,7 +445,7 @@ M2lSeg plan_m2l(Ctx& c, int first, bool split) {
   if (c.nsys > 1) ensure(c.ws, c.m2l_seglen, (size_t)nc);
   ensure(c.ws, c.m2l_extra, (size_t)extra_max + 1);
   ensure(c.ws, c.m2l_part, (size_t)(extra_max + 1) * ncd);
-  ensure(c.ws, c.counters, 512);
+  ensure(c.ws, c.counters, COUNTERS);
   int* ctr = c.counters.p + 46;
   zero_fill(c, ctr, sizeof(int));
   hipLaunchKernelGGL(k_m2l_plan, dim3((unsigned)ceil_div(nc - first, 256)), dim3(256), 0, c.stream, nc, first,

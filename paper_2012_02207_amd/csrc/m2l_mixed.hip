@@ -487,7 +487,7 @@ __global__ void k_add_sinks(const int* __restrict__ sinks, const int* __restrict
 void launch_m2l_mixed_root(Ctx& c, double* loc64) {
   int nc = (int)c.ncell;
   ensure(c.ws, c.root_sinks, (size_t)nc);
-  ensure(c.ws, c.counters, 512);
+  ensure(c.ws, c.counters, COUNTERS);
   int* count = c.counters.p + 64;
   zero_fill(c, count, sizeof(int));
   int first_lo = mixed_first_lo(c);

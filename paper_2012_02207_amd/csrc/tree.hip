@@ -1185,7 +1185,7 @@ void build_tree(Ctx& c, int64_t n, const double* pos, const double* mass) {
   // arrays, and the cells written again
   size_t cap = (size_t)std::max<int64_t>(1024, 4 * n / std::max(1, c.prm.n_leaf) + 64 + 2 * nsys);
   if (c.c_level.epoch == c.ws.epoch) cap = std::max(cap, c.c_level.cap);
-  ensure(c.ws, c.counters, 512);  // the full size at once: counters[4..5] must outlive this call
+  ensure(c.ws, c.counters, COUNTERS);  // the full size at once: counters[4..5] must outlive this call
   int nb = (int)ceil_div(n, CT_TILE);
   ensure(c.ws, c.sort_hist, (size_t)CT_ROWS * nb * 2 + CT_ROWS + 64);
   int* cnt = c.sort_hist.p;

@@ -513,7 +513,7 @@ static void run_walk(Ctx& c, CellList& acc, CellList& nearl, bool group,
   ensure(c.ws, c.front[1], fcap0);
   ensure(c.ws, acc.raw, (size_t)c.ncell * 8 + 64);  // (kept as large as earlier calls left it)
   ensure(c.ws, nearl.raw, (size_t)c.ncell * 8 + 64);
-  ensure(c.ws, c.counters, 512);
+  ensure(c.ws, c.counters, COUNTERS);
   int* ctr = c.counters.p + 256;
   int bits = list_bits(c.ncell);
   long long* h = c.hbuf;  // the counters, read back as 64-bit values

@@ -531,3 +531,18 @@ def test_high_order_m2l_under_a_limit(fmm, p, n, n_leaf):
     for r in out[1:]:
         for a, b in zip(out[0], r):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("count,n,n_leaf", [(1, 3000, 64), (1, 9000, 100), (700, 50, 8), (3, 20000, 64)])
+def test_body_pair_count(fmm, precision, count, n, n_leaf):
+    """The near field's body pairs are those of its list."""
+    pos, _, mass = W.plummer(count * n, 21)
+    print(f"[gpu] body pairs {count} x {n} n_leaf={n_leaf} {precision}", flush=True)
+    f = fmm.FMM(p=4, err_tol=1e-5, n_leaf=n_leaf, precision=precision)
+    for _ in range(2):
+        f.forces_batch(_dev(pos), _dev(mass), np.arange(count + 1) * n)
+    size = f.export("cell_end").astype(np.int64) - f.export("cell_begin")
+    p2p = f.export("p2p")
+    assert f.stats()["n_p2p_pairs"] == (size[p2p[:, 0]] * size[p2p[:, 1]]).sum() - count * n
+    f.close()

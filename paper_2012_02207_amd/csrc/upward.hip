@@ -12,6 +12,8 @@
 // different coefficients accumulate over the bodies in order.
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #include "fmm_device.h"
 #include "fmm_tables.h"
 
@@ -99,8 +101,9 @@ __device__ inline void regular_column_lockstep(int p, int m, double x, double y,
   }
 }
 
+// (leaves of up to `most` bodies)
 template <int V>
-__global__ void __launch_bounds__(64 * P2M_WAVES) k_p2m(int p, const int* __restrict__ leaves, int nleaves,
+__global__ void __launch_bounds__(64 * P2M_WAVES) k_p2m(int p, const int* __restrict__ leaves, int nleaves, int most,
                                                         const int* __restrict__ cb, const int* __restrict__ ce,
                                                         const double4* __restrict__ pm, const double* __restrict__ cx,
                                                         const double* __restrict__ cy, const double* __restrict__ cz,
@@ -114,6 +117,7 @@ __global__ void __launch_bounds__(64 * P2M_WAVES) k_p2m(int p, const int* __rest
   double* val = lds + (size_t)wv * S * batch;  // [body][value]
   double x0 = cx[c], y0 = cy[c], z0 = cz[c];
   int b = cb[c], e = ce[c];
+  if (e - b > most) return;
   int hb = lane / (p + 1), hm = lane - hb * (p + 1);  // harmonic lane: body hb, column hm
   double sum[V];
 #pragma unroll
@@ -149,6 +153,74 @@ __global__ void __launch_bounds__(64 * P2M_WAVES) k_p2m(int p, const int* __rest
 #pragma unroll
   for (int v = 0; v < V; v++) {
     int k = lane + 64 * v;
+    if (k < S) {
+      int n = both_sign_n(k), j = k - n * n, m = (j + 1) >> 1;
+      out[2 * cidx(n, m) + (j > 0 && !(j & 1) ? 1 : 0)] = sum[v];
+      if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
+    }
+  }
+}
+
+// P2M of the leaves of more than `most` bodies, a workgroup per leaf: the wavefronts
+// share the harmonics of a batch and then the values, each summed over the batch in
+// sorted body order as above.  One wavefront takes 4 ms for a leaf of 1000 bodies
+// at p = 30, long after all others have ended.
+constexpr int P2M_WIDE = 8;
+constexpr int64_t P2M_FULL = 2048;  // leaves that fill the chip with a wavefront each
+
+__global__ void __launch_bounds__(64 * P2M_WIDE) k_p2m_wide(int p, const int* __restrict__ leaves, int most,
+                                                            const int* __restrict__ cb, const int* __restrict__ ce,
+                                                            const double4* __restrict__ pm,
+                                                            const double* __restrict__ cx,
+                                                            const double* __restrict__ cy,
+                                                            const double* __restrict__ cz, double* __restrict__ mult) {
+  extern __shared__ double lds[];
+  int c = leaves[blockIdx.x];
+  int b = cb[c], e = ce[c];
+  if (e - b <= most) return;
+  constexpr int T = 64 * P2M_WIDE;
+  int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  int S = (p + 1) * (p + 1), per = p2m_batch(p), batch = per * P2M_WIDE;
+  double* val = lds;                   // [body][value]
+  double* mass = lds + (size_t)S * batch;
+  double x0 = cx[c], y0 = cy[c], z0 = cz[c];
+  int hl = lane / (p + 1), hm = lane - hl * (p + 1), hb = wv * per + hl;  // body hb of the batch, column hm
+  constexpr int V = ((FMM_TABLE_PMAX + 1) * (FMM_TABLE_PMAX + 1) + T - 1) / T;
+  double sum[V];
+#pragma unroll
+  for (int v = 0; v < V; v++) sum[v] = 0.0;
+  for (int i0 = b; i0 < e; i0 += batch) {
+    int cnt = min(batch, e - i0);
+    if (hl < per && hb < cnt) {
+      double4 q = pm[i0 + hb];
+      if (hm == 0) mass[hb] = q.w;
+      regular_column_lockstep(p, hm, q.x - x0, q.y - y0, q.z - z0, [&](int n, double vr, double vi) {
+        double* w = val + hb * S + n * n + 2 * hm;
+        if (hm > 0) {
+          w[-1] = vr;
+          w[0] = vi;
+        } else {
+          w[0] = vr;
+        }
+      });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      int k = tid + T * v;
+      if (k < S)
+#pragma unroll 4
+        for (int j = 0; j < cnt; j++) {
+          double t = mass[j] * val[j * S + k];
+          sum[v] = sum[v] + t;
+        }
+    }
+    __syncthreads();
+  }
+  double* out = mult + (size_t)c * ncoef(p) * 2;
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    int k = tid + T * v;
     if (k < S) {
       int n = both_sign_n(k), j = k - n * n, m = (j + 1) >> 1;
       out[2 * cidx(n, m) + (j > 0 && !(j & 1) ? 1 : 0)] = sum[v];
@@ -416,10 +488,19 @@ void expansions_up(Ctx& c) {
   hipStream_t s = c.stream;
   int p = c.p, nc = (int)c.ncell;
   int S = (p + 1) * (p + 1);
+  // Leaves of more than 64 bodies where the leaves are few, of more than 512 where
+  // they fill the chip, take a workgroup each; there are none unless n_leaf is
+  // larger, or bodies coincide to the last level.
+  int most = c.nleaf < P2M_FULL ? 64 : 512;
+  bool wide = c.prm.n_leaf > most || c.depth == FMM_MAX_LEVEL;
   auto p2m = S <= 2 * 64 ? k_p2m<2> : S <= 4 * 64 ? k_p2m<4> : S <= 9 * 64 ? k_p2m<9> : k_p2m<16>;
   hipLaunchKernelGGL(p2m, dim3((unsigned)ceil_div(c.nleaf, P2M_WAVES)), dim3(64 * P2M_WAVES),
-                     sizeof(double) * S * p2m_batch(p) * P2M_WAVES, s, p, c.leaves.p, (int)c.nleaf, c.c_begin.p,
-                     c.c_end.p, c.pm.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.mult.p);
+                     sizeof(double) * S * p2m_batch(p) * P2M_WAVES, s, p, c.leaves.p, (int)c.nleaf,
+                     wide ? most : INT_MAX, c.c_begin.p, c.c_end.p, c.pm.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.mult.p);
+  if (wide)
+    hipLaunchKernelGGL(k_p2m_wide, dim3((unsigned)c.nleaf), dim3(64 * P2M_WIDE),
+                       sizeof(double) * (S + 1) * p2m_batch(p) * P2M_WIDE, s, p, c.leaves.p, most, c.c_begin.p,
+                       c.c_end.p, c.pm.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, c.mult.p);
   HIPCHK(hipGetLastError());
   m2m_levels(c, c.mult.p);
   int64_t npk = (int64_t)nc * (p + 1);

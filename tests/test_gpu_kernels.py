@@ -546,3 +546,25 @@ def test_body_pair_count(fmm, precision, count, n, n_leaf):
     p2p = f.export("p2p")
     assert f.stats()["n_p2p_pairs"] == (size[p2p[:, 0]] * size[p2p[:, 1]]).sum() - count * n
     f.close()
+
+
+# leaves of more than 64 bodies (512 from 2048 leaves on) take a workgroup of eight
+# wavefronts each, others one wavefront
+@pytest.mark.parametrize("p", [1, 3, 10, 15, 16, 21, 30])
+@pytest.mark.parametrize("n,n_leaf,copies", [(1000, 1024, 0), (1500, 200, 65), (30000, 8, 600)])
+def test_upward_large_leaves(fmm, p, n, n_leaf, copies):
+    """Multipoles and norms of the oracle, bit for bit: leaves about the bounds,
+    by n_leaf and by coincident bodies, beside small ones."""
+    pos, mass = W.uniform_cube(n, 50 + n)
+    pos[100:100 + copies] = pos[100]
+    pos[200 + copies:264 + copies] = pos[99]
+    mass[::9] = 0.0
+    print(f"[gpu] upward p={p} n={n} n_leaf={n_leaf} copies={copies}", flush=True)
+    f = fmm.FMM(p=p, n_leaf=n_leaf)
+    f.build(_dev(pos), _dev(mass))
+    assert copies < 600 or f.stats()["nleaf"] > 2048
+    o = oracle.Oracle()
+    o.run(pos, mass, p=p, err_tol=1e-7, n_leaf=n_leaf, stage="upward")
+    assert np.array_equal(f.export("mult"), o.get("mult"))
+    assert np.array_equal(f.export("pk"), o.get("pk"))
+    f.close()

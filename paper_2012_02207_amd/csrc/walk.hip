@@ -686,8 +686,14 @@ __global__ void __launch_bounds__(64 * NF_WAVES) k_near_f(int nleaves, const int
 // wavefront per leaf and take 181 this way, at 1000 bodies 170 and 39, at 2737
 // leaves (50021 bodies) 243 and 91; at 5358 leaves the two are equal (240), and
 // where the leaves fill the chip the chains of adds lose (320 against 243 us at
-// 14391 leaves).
+// 14391 leaves).  So they do with large leaves (n_leaf = 400 and more at 2^20
+// bodies of a cube, 4096 leaves: 10.1 against 7.1 ms): where the leaves have more
+// than NF_LANES blocks of 64 bodies in all, a leaf of 64 and more takes a wavefront
+// per block, a lane per body, as in k_near_f, unless its list is more than twice the
+// mean (an outskirts leaf of a 2^20-body model has all bodies as partners, and is
+// the kernel's length).
 constexpr int NF_FEW = 4096;
+constexpr int64_t NF_LANES = 8192;
 
 // The terms of the lane's body (v; no body: mass 0) for sinks k .. k+3 of pm,
 // written to t[0], t[65], t[130], t[195].  masses_safe: every mass of the chunk
@@ -739,8 +745,9 @@ __device__ __forceinline__ double add_terms(double near, const double* t, int cn
 __global__ void __launch_bounds__(1024) k_near_f_few(int nleaves, const int* __restrict__ leaves,
                                                      const int* __restrict__ cb, const int* __restrict__ ce,
                                                      const int* __restrict__ off, const int* __restrict__ src,
-                                                     const double4* __restrict__ pm, double* __restrict__ f) {
-  __shared__ double tbuf[16][4 * 65];
+                                                     const double4* __restrict__ pm, int lane_entries,
+                                                     double* __restrict__ f) {
+  __shared__ __align__(32) double tbuf[16][4 * 65 + 4];
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int li = xcd_block();
   if (li >= nleaves) return;
@@ -748,6 +755,30 @@ __global__ void __launch_bounds__(1024) k_near_f_few(int nleaves, const int* __r
   int b = cb[B], e = ce[B];
   int qb = off[B], qe = off[B + 1];
   double* tw = tbuf[wv];
+  if (e - b >= 64 && qe - qb <= lane_entries) {
+    double4* sb = (double4*)tw;  // the staged chunk
+    for (int i0 = b + wv * 64; i0 < e; i0 += 1024) {
+      double4 me = pm[min(i0 + lane, e - 1)];
+      double near = 0.0;
+      BodyStream st;
+      st.start(src, cb, ce, qb, qe, lane);
+      int j, na = st.next(lane, b, j);
+      double4 cur = pm[j];
+      while (na > 0) {
+        __builtin_amdgcn_wave_barrier();
+        sb[lane] = cur;
+        __builtin_amdgcn_wave_barrier();
+        int nn = st.next(lane, b, j);
+        cur = pm[j];
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged chunk is visible to the wave
+        for (int t = 0; t < na; t++) near = near + near_term(sb[t], me, true);
+        na = nn;
+      }
+      if (i0 + lane < e) f[i0 + lane] = near;
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
   int mine = min(lane, 3) * 65;
   for (int i0 = b + wv * 4; i0 < e; i0 += 64) {
     int nB = min(4, e - i0);
@@ -846,7 +877,8 @@ void estimate_walk(Ctx& c, const std::function<void()>& beside) {
   group_by_sink(c, c.est_near);
   if (c.nleaf <= NF_FEW)
     hipLaunchKernelGGL(k_near_f_few, dim3(xcd_grid(c.nleaf)), dim3(1024), 0, s, (int)c.nleaf, c.leaves.p,
-                       c.c_begin.p, c.c_end.p, c.est_near.off.p, c.est_near.src.p, c.pm.p, c.fpart.p);
+                       c.c_begin.p, c.c_end.p, c.est_near.off.p, c.est_near.src.p, c.pm.p,
+                       c.n > 64 * NF_LANES ? (int)(2 * c.est_near.count / c.nleaf) : 0, c.fpart.p);
   else
     hipLaunchKernelGGL(k_near_f, dim3(xcd_grid(ceil_div(c.nleaf, NF_WAVES))), dim3(64 * NF_WAVES), 0, s,
                        (int)c.nleaf, c.leaves.p, c.c_begin.p, c.c_end.p, c.est_near.off.p, c.est_near.src.p,

@@ -568,3 +568,44 @@ def test_upward_large_leaves(fmm, p, n, n_leaf, copies):
     assert np.array_equal(f.export("mult"), o.get("mult"))
     assert np.array_equal(f.export("pk"), o.get("pk"))
     f.close()
+
+
+@pytest.mark.parametrize("n,n_leaf,kind", [(530000, 1024, "cube"), (600001, 1000, "mixed")])
+def test_estimate_of_large_leaves(fmm, n, n_leaf, kind):
+    """Up to 4096 leaves that hold more than 8192 blocks of 64 bodies: the sums of
+    leaves of 64 and more (a lane per body) and of the others, each body's in the
+    defining order, so bit for bit the running sums of its list in numpy."""
+    pos, mass = W.uniform_cube(n, 7)
+    if kind == "mixed":  # leaves of all sizes, coincident bodies, no mass
+        pos[:n // 2] *= 0.2
+        pos[5:25] = pos[5]
+        mass[::3] = 0.0
+    print(f"[gpu] estimate of large leaves n={n} n_leaf={n_leaf}", flush=True)
+    f = fmm.FMM(p=1, err_tol=1.0, n_leaf=n_leaf)
+    f.forces(_dev(pos), _dev(mass))
+    assert f.stats()["nleaf"] <= 4096
+    perm = f.export("perm").astype(np.int64)
+    x, m = pos[perm], mass[perm]
+    cb, ce, parent = f.export("cell_begin"), f.export("cell_end"), f.export("cell_parent")
+    far, fpart, near = f.export("fcell_est"), f.export("f_part"), f.export("est_near").astype(np.int64)
+    size = ce - cb
+    leaves = np.unique(near[:, 0])
+    picked = [leaves[size[leaves] == k][0] for k in np.unique(size[leaves])[::max(1, n_leaf // 12)]]
+    picked += [leaves[np.argmax(size[leaves])], leaves[np.argmin(size[leaves])]]
+    assert max(size[c] for c in picked) > 64
+    for c in picked:
+        sources = near[near[:, 0] == c, 1]
+        j = np.concatenate([np.arange(cb[a], ce[a]) for a in sources])
+        top, path = 0.0, []
+        q = c
+        while q >= 0:
+            path.append(q)
+            q = parent[q]
+        for q in path[::-1]:
+            top = top + far[q]
+        for i in {int(cb[c]), int(ce[c]) - 1, int(cb[c]) + int(size[c]) // 2}:
+            d = x[j] - x[i]
+            d2 = (d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]) + d[:, 2] * d[:, 2]
+            term = np.where(d2 > 0.0, m[j] / np.where(d2 > 0.0, d2, 1.0), 0.0)
+            assert fpart[i] == top + np.cumsum(term)[-1], (c, i)
+    f.close()

@@ -214,8 +214,9 @@ struct HiOrder {
 // M2L of the list of each sink (a workgroup per sink, or per segment of a long
 // list, see M2lSeg), or of the listed sinks; with B >= first_lo only the sources
 // below first_lo are taken (the FP64 part of mixed precision).
-// NT tiles of 16 pairs at a time, orders up to PM.
-template <int NT, int PM>
+// NT tiles of 16 pairs at a time, orders up to PM.  WHOLE: the plan has no extra
+// items, and a workgroup adds up the segments of a long list itself.
+template <int NT, int PM, bool WHOLE>
 __global__ void __launch_bounds__(64 * hi::WAVES) k_m2l_hi(int p, int ncell, int first_lo,
                                                            const int* __restrict__ sinks,
                                                            const int* __restrict__ nsinks,
@@ -261,12 +262,14 @@ __global__ void __launch_bounds__(64 * hi::WAVES) k_m2l_hi(int p, int ncell, int
       continue;
     }
     double bx = cx[B], by = cy[B], bz = cz[B];
-    int nseg = sg.nseg ? sg.nseg[B] : 1, send = seg + 1;
-    if (nseg > 1 && sg.pbase[B] < 0) send = nseg;
-    if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
-    for (bool add = false; seg < send; seg++, add = true) {
-      int b = b0, e = e0;
-      m2l_segment(sg, B, nseg, seg, b, e);
+    int b = b0, e = e0, K = 0;
+    if (sg.nseg && sg.nseg[B] > 1) {
+      K = sg.seglen ? sg.seglen[B] : sg.K;
+      b += seg * K;
+      e = min(e0, b + K);
+      if (seg > 0) out = sg.part + (size_t)(sg.pbase[B] + seg - 1) * NC * 2;
+    }
+    while (true) {
       __syncthreads();  // the previous sums have been read
       for (int k = tid; k < S; k += 64 * hi::WAVES) acc[k] = 0.0;
       for (int base = b; base < e; base += PT) {
@@ -365,9 +368,12 @@ __global__ void __launch_bounds__(64 * hi::WAVES) k_m2l_hi(int p, int ncell, int
         bool im = j > 0 && !(j & 1);
         double* o = out + 2 * cidx(n, m) + (im ? 1 : 0);
         double v = acc[u] * (c_fact_hi[n - m] * c_fact_hi[n + m]);
-        *o = add ? *o + v : v;
+        *o = WHOLE && b > b0 ? *o + v : v;
         if (j == 0) out[2 * cidx(n, 0) + 1] = 0.0;
       }
+      if (!WHOLE || e == e0) break;
+      b = e;
+      e = min(e0, b + K);
     }
   }
 }
@@ -408,11 +414,13 @@ void launch_m2l_hi(Ctx& c, int first_lo, const double* mult, double* loc, const 
   int nc = (int)c.ncell;
   M2lSeg sg{};
   // (where memory is limited no list is split: its partial expansions take up to 8 KB each)
-  if (!sinks && first_lo >= nc) sg = plan_m2l(c, 0, !c.ws.arena && !c.ws.limit);
+  bool whole = c.ws.arena || c.ws.limit;
+  if (!sinks && first_lo >= nc) sg = plan_m2l(c, 0, !whole);
   unsigned grid = sinks ? 2048u : (unsigned)std::max(sg.nseg ? sg.max_items : nc, 1);
   // 32 pairs at a time where their coefficients fit the 160 KB of LDS (p <= 20)
   constexpr int P_TWO = 20;
-  auto kern = c.p <= P_TWO ? k_m2l_hi<2, P_TWO> : k_m2l_hi<1, hi::PMAX>;
+  auto kern = c.p <= P_TWO ? (whole ? k_m2l_hi<2, P_TWO, true> : k_m2l_hi<2, P_TWO, false>)
+                           : (whole ? k_m2l_hi<1, hi::PMAX, true> : k_m2l_hi<1, hi::PMAX, false>);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * hi::WAVES), m2l_hi_lds_bytes(c.p, c.p <= P_TWO ? 2 : 1), c.stream,
                      c.p, nc, first_lo, sinks, nsinks, c.m2l.off.p, c.m2l.src.p, c.c_cx.p, c.c_cy.p, c.c_cz.p, mult,
                      loc, sg);

@@ -654,17 +654,20 @@ void plan_near_field(Ctx& c) {
   int64_t segs = cnt / nf_segment(c.nsys > 1 ? 1 : c.n, max_nb, tiled, 0);
   int64_t slots = std::min(NF_SLOTS, segs * 64);
   if (c.ws.limit || c.ws.arena) {
-    // Where memory is limited: a slot per four entries, or in the fixed scratch
-    // what is left of it (with 8 bytes per slot for the extra items) after the
-    // buffers of the M2L, the only ones still to come.
-    int64_t few = ceil_div(cnt, 4);
+    // Where memory is limited: as many slots as fit beside the buffers still to come,
+    // those of the M2L (up to a segment per 512 pairs) and, in a context's own
+    // workspace, of the gradient; none, if need be.
+    int64_t expansion = ncoef(c.p) * 16, segments = c.m2l.count / 512 + 1;
+    int64_t later = 12 * c.ncell + segments * (8 + (c.p <= FMM_GPU_PMAX ? expansion : 0)) + c.n + 65536;
+    int64_t fit;
     if (c.ws.arena) {
-      int64_t pairs = c.m2l.count / 512 + 1;  // segments of M2L lists, at most
-      int64_t m2l = 12 * c.ncell + pairs * (8 + (c.p <= FMM_GPU_PMAX ? ncoef(c.p) * 16 : 0)) + 65536;
-      int64_t left = (int64_t)(c.ws.arena_cap - c.ws.arena_used) - m2l - c.n - 8192;
-      few = std::max(few, left / 40);
+      fit = ((int64_t)(c.ws.arena_cap - c.ws.arena_used) - later) / 40;  // (8 bytes of extra items per slot)
+    } else {
+      later += 2 * c.ncell * expansion + 128 * c.n;
+      fit = std::min(ceil_div(cnt, 4), ((int64_t)c.ws.limit - (int64_t)c.ws.bytes - later - later / 4) / 130);
+      if ((int64_t)c.nf_part.cap > c.nf.max_slots) fit = std::max<int64_t>(fit, c.nf.max_slots);  // (held already)
     }
-    slots = std::min(slots, few);
+    slots = std::min(slots, std::max<int64_t>(fit, 0));
   }
   // (a split list has no more extra items than slots)
   int64_t split = std::min({NF_SPLIT, slots, segs * (tiled ? 64 / NF_TILE : 1)});

@@ -407,8 +407,7 @@ __global__ void k_m2l_plan(int ncell, int first, const int* __restrict__ off, co
   int at = -1;
   if (ns > 1 && split) {
     at = atomicAdd(ctr, ns - 1);
-    if (extra)  // (null: counted only)
-      for (int k = 1; k < ns; k++) extra[at + k - 1] = make_int2(B, k);
+    for (int k = 1; k < ns; k++) extra[at + k - 1] = make_int2(B, k);
   }
   nseg[B] = ns;
   pbase[B] = at;
@@ -430,10 +429,6 @@ __global__ void k_m2l_combine(int ncd, int max_extra, const int* __restrict__ ns
   loc[(size_t)B * ncd + k] = s;
 }
 
-// later segments up to which the fixed scratch holds slots for the bound of their
-// number
-constexpr int64_t M2L_ARENA_EXTRA = 8192;
-
 // the plan for the sinks from `first` on and their sources from there on (on
 // c.stream)
 M2lSeg plan_m2l(Ctx& c, int first, bool split) {
@@ -450,23 +445,13 @@ M2lSeg plan_m2l(Ctx& c, int first, bool split) {
   if (c.nsys > 1) ensure(c.ws, c.m2l_seglen, (size_t)nc);
   ensure(c.ws, c.counters, COUNTERS);
   int* ctr = c.counters.p + 46;
-  auto plan = [&](int2* extra) {
-    zero_fill(c, ctr, sizeof(int));
-    hipLaunchKernelGGL(k_m2l_plan, dim3((unsigned)ceil_div(nc - first, 256)), dim3(256), 0, c.stream, nc, first,
-                       c.m2l.off.p, c.m2l.src.p, c.c_begin.p, c.sys_off.p, c.nsys, K, split, c.m2l_nseg.p,
-                       c.m2l_pbase.p, c.m2l_seglen.p, extra, ctr);
-    HIPCHK(hipGetLastError());
-  };
-  if (c.ws.arena && extra_max > M2L_ARENA_EXTRA) {  // the fixed scratch: their exact number
-    plan(nullptr);
-    int* h = (int*)(c.hbuf + 120);
-    HIPCHK(hipMemcpyAsync(h, ctr, sizeof(int), hipMemcpyDeviceToHost, c.stream));
-    HIPCHK(hipStreamSynchronize(c.stream));
-    extra_max = *h;
-  }
   ensure(c.ws, c.m2l_extra, (size_t)extra_max + 1);
   ensure(c.ws, c.m2l_part, (size_t)(extra_max + 1) * ncd);
-  plan(c.m2l_extra.p);
+  zero_fill(c, ctr, sizeof(int));
+  hipLaunchKernelGGL(k_m2l_plan, dim3((unsigned)ceil_div(nc - first, 256)), dim3(256), 0, c.stream, nc, first,
+                     c.m2l.off.p, c.m2l.src.p, c.c_begin.p, c.sys_off.p, c.nsys, K, split, c.m2l_nseg.p,
+                     c.m2l_pbase.p, c.m2l_seglen.p, c.m2l_extra.p, ctr);
+  HIPCHK(hipGetLastError());
   return M2lSeg{c.m2l_nseg.p, c.m2l_pbase.p, c.m2l_extra.p, ctr, c.m2l_part.p,
                 c.nsys > 1 ? c.m2l_seglen.p : nullptr, K, (int)(nc - first + extra_max)};
 }

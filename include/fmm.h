@@ -20,7 +20,9 @@
  * scratch (tree, expansions, lists), grows it on demand and frees it in
  * fmm_destroy.  Work is enqueued on the given stream; functions that return
  * host-visible values synchronise that stream.  No function throws; every
- * status other than FMM_OK leaves outputs unspecified and the context usable.
+ * status other than FMM_OK leaves outputs unspecified and the context usable
+ * (a call that fails after it has enqueued work waits for that work, except
+ * while its stream is being captured).
  * A context must not be used from two host threads at once.
  */
 #ifndef FMM_H
@@ -221,8 +223,8 @@ fmm_status fmm_adjoint(fmm_ctx* ctx, int64_t n, const double* pos, const double*
  * order) is the acceleration that evaluation returned.  gacc, gpot, gpos and
  * gmass as in fmm_adjoint; the result equals fmm_adjoint's at the same inputs
  * bit for bit.  Errors: a null pointer or n < 1 -> FMM_EINVAL; no such
- * evaluation (none yet, another n, a batch, mixed or direct precision, or a
- * tree built since) -> FMM_ENOTBUILT. */
+ * evaluation (none yet, another n, a batch, mixed or direct precision, a
+ * tree built or an evaluation failed since) -> FMM_ENOTBUILT. */
 fmm_status fmm_adjoint_last(fmm_ctx* ctx, int64_t n, const double* acc, const double* gacc,
                             const double* gpot, double* gpos, double* gmass, void* stream);
 

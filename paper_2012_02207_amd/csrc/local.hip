@@ -178,7 +178,7 @@ __device__ __forceinline__ void l2p_eval(int p, const double* __restrict__ L, do
 // its place until its longest item ends, so with four, 2.6 of the 4 wavefronts
 // per SIMD that fit were in flight in FP64, 3.7 of 6 in mixed precision: 2^18
 // bodies in FP64 4.40 ms (4.34 with one), 2^20 mixed 8.24 (8.04), 256 systems
-// of 16384 37.7 (36.6).
+// of 1032 to 65006 bodies (mean 15512) 37.7 (36.6).
 constexpr int LG_WAVES = 1;
 
 // the pairs of an item added to the sum of its workgroup's slot (NF_PAIRS)
@@ -326,9 +326,10 @@ __device__ __forceinline__ float mass32(const double4& v) {
 }
 
 // Bound by VALU issue: 18 instructions of 4 cycles per pair (rsq 8), 20 of all
-// the kernel's, and 77% of the lanes used.  So what is not a pair's own
-// arithmetic is kept off the vector unit (N = 2^20, 3.16e9 pairs: 25.5 to 20
-// instructions per round of the groups, 2.85 to 2.34 ms):
+// the kernel's, and 77% of the lanes used (counted from the lists: 21% are left
+// over by leaves that do not divide 64, the rest by last rounds).  So what is not
+// a pair's own arithmetic is kept off the vector unit (N = 2^20, 3.16e9 pairs: 25.5
+// to 20 instructions per round of the groups, 2.85 to 2.34 ms):
 //  - The records of a group's bodies are adjacent in LDS (slot g S + t / G for
 //    body t of group t mod G), so a round of four pairs takes one address.
 //  - The trip count na / G is the same for every lane and stays in SGPRs; only the

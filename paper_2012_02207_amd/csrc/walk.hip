@@ -438,8 +438,8 @@ static int list_bits(int64_t ncell) {
 // where the 256 parts hold up to GP_ONCE entries on average; else up to 256 times 256
 // parts of up to GP_TWICE.
 // More than 2^20 cells (keys over 40 bits): the LSD sort.  Against it everywhere:
-// 256 systems of 16384 bodies 41.4 -> 38.3 ms (the sorts 7.0 -> 3.9), 2^22 bodies
-// 31.4 -> 29.4, 30011 1.37 -> 1.27.  GP_ONCE 4096 and 16384 time alike; GP_TWICE 640
+// 256 systems of 1032 to 65006 bodies (mean 15512) 41.4 -> 38.3 ms (the sorts
+// 7.0 -> 3.9), 2^22 bodies 31.4 -> 29.4, 30011 1.37 -> 1.27.  GP_ONCE 4096 and 16384 time alike; GP_TWICE 640
 // costs 2^20 bodies 0.1 ms, 3000 2^18 in FP64 0.05.
 constexpr int64_t GP_ONCE = 8192, GP_TWICE = 1536;
 

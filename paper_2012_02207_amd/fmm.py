@@ -264,10 +264,11 @@ class FMM:
         return acc, pot
 
     def autotune(self, pos, mass, offsets=None, eps_soft=0.0, p=None, err_tol=None):
-        """Picks n_leaf, then (mixed precision) the FP32 M2L's wavefronts per
-        sink, then the near field's lane groups for this workload (timed on the
-        GPU, cached per workload class in the process); returns n_leaf.  All
-        choices are set in the context and read back into self.params."""
+        """Picks the near field's start and n_leaf, then (mixed precision only) the
+        FP32 M2L's wavefronts per sink and the near field's lane groups for this
+        workload (timed on the GPU, cached per workload class in the process);
+        returns n_leaf.  All choices are set in the context and read back into
+        self.params."""
         torch = _torch()
         n = mass.shape[0]
         off = np.ascontiguousarray(np.asarray([0, n] if offsets is None else offsets, dtype=np.int64))

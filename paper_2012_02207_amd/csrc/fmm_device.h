@@ -133,9 +133,9 @@ __device__ __forceinline__ bool nf_item(const NfPlan& plan, int it, int& li, int
   li = it;
   seg = tile = 0;
   if (it >= plan.nleaf) {
-    int x = it - plan.nleaf;
-    if (it >= plan.max_items || x >= *plan.nextra) return false;
-    int2 v = plan.extra[x];
+    int x = it - plan.nleaf, front = plan.nextra[0];
+    if (it >= plan.max_items || x >= front + plan.nextra[1]) return false;
+    int2 v = plan.extra[x < front ? x : plan.max_items - 1 - (it - front)];
     li = v.x;
     nf_decode(v.y, seg, tile);
   }

@@ -125,8 +125,9 @@ constexpr int COUNTERS = NF_PAIRS + NF_PAIR_SLOTS * NF_PAIR_STRIDE;
 struct NfPlan {
   const int* cell_nseg;   // segments of each leaf, by cell id
   const int* cell_pbase;  // first partial slot of each split leaf, -1 of the others, by cell id
-  const int2* extra;      // (leaf index, nf_code) of the extra items
-  const int* nextra;      // extra item count (device)
+  const int2* extra;      // (leaf index, nf_code) of the extra items, [max_items - nleaf]:
+                          // later segments' from the front on, the first segments' later tiles from the back
+  const int* nextra;      // their two counts (device)
   int nleaf;
   int max_items;          // host bound on the item count (grid size)
   int max_slots;          // partial slots
@@ -231,9 +232,9 @@ struct Ctx {
   // cells (long long, read by the radius and cell-minimum kernels); [32] input
   // check; [46] extra items of the M2L; [48..49] FP32 M2L pairs (stats); [64] sinks
   // with root-level pairs; [256..] walk (64-bit counters at even int offsets); near
-  // field: from NF_COUNTERS on +2 later segments (stats), +3 extra items, +4, +5
-  // partial slots and +6, +7 later segments' items asked for (long long), from
-  // NF_PAIRS on body pairs (long long, stats)
+  // field: from NF_COUNTERS on +2 later segments (stats), +4, +5 partial slots and
+  // +6, +7 later segments' items asked for (long long), +8, +9 extra items of later
+  // segments and of first ones, from NF_PAIRS on body pairs (long long, stats)
   dbuf<int> counters;
   CellList est_far, est_near, m2l, p2p;
   int64_t n_p2p_pairs = 0;

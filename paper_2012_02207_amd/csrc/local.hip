@@ -572,7 +572,13 @@ constexpr int NF_SEG_PER = 32;
 // of all entries (NF_ITEMS), or where the leaves alone fill the chip some times over
 // (NF_FULL wavefronts) lists of more than twice the mean length.  NF_SLOTS, NF_SPLIT:
 // slots for partial sums (32 B each) and later segments' items, at the most; the
-// grid covers that many items, and a wavefront that finds none costs 0.8 ns.
+// grid covers that many items, and a wavefront that finds none costs 0.8 ns.  Later
+// segments come first among the extra items, then the later tiles in the order of
+// the leaves, whose lists are the longer the shallower the leaf: the longest items
+// have to start early.  (The atomics for slots delay the wavefronts that have long
+// lists, so the tiles are claimed before them; after them all items of those
+// wavefronts came last: the near field of 2^18 bodies alone 1.18 -> 1.14 ms in FP64,
+// the gradient's 2.47 -> 2.36.)
 constexpr int64_t NF_ITEMS = 65536, NF_FULL = 24576, NF_SLOTS = 1 << 20, NF_SPLIT = 65536;
 
 // len: entries of the list (0: the least of any list)
@@ -587,7 +593,7 @@ __host__ __device__ inline int nf_segment(int64_t bodies, int max_nb, int tiled,
 
 __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* __restrict__ cb,
                           const int* __restrict__ ce, const int* __restrict__ off, const int* __restrict__ sys_off,
-                          int nsys, int max_nb, int tiled, int long_len, int max_slots, int max_split,
+                          int nsys, int max_nb, int tiled, int long_len, int max_slots, int max_split, int extra_max,
                           int* cell_nseg, int* cell_pbase, int2* extra, int* ctr) {
   int li = blockIdx.x * blockDim.x + threadIdx.x;
   if (li >= nleaf) return;
@@ -597,6 +603,10 @@ __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* 
   int K = nf_segment(sys_off[sys + 1] - sys_off[sys], max_nb, tiled, len);
   int ns = (nB <= 64 && len > K) ? (len + K - 1) / K : 1;
   int nt = tiled ? nf_tile_count(nB) : 1;
+  if (nt > 1) {  // (claimed before any slots: see above)
+    int x = extra_max - 1 - atomicAdd(ctr + 9, nt - 1);
+    for (int t = 1; t < nt; t++) extra[x--] = make_int2(li, nf_code(0, t));
+  }
   int pbase = -1;
   if (ns > 1 && len > long_len) {  // split, if there are slots and items left
     unsigned long long need = (unsigned long long)(ns - 1) * nB, more = (unsigned long long)(ns - 1) * nt;
@@ -607,12 +617,11 @@ __global__ void k_nf_plan(const int* __restrict__ leaves, int nleaf, const int* 
   }
   cell_nseg[B] = ns;
   cell_pbase[B] = pbase;
-  int nx = pbase >= 0 ? ns : 1;
-  if (nx * nt > 1) {
-    int x = atomicAdd(ctr + 3, nx * nt - 1);
-    for (int k = 0; k < nx; k++)
-      for (int t = k == 0 ? 1 : 0; t < nt; t++) extra[x++] = make_int2(li, nf_code(k, t));
-    if (nx > 1) atomicAdd(ctr + 2, nx - 1);
+  if (pbase >= 0) {
+    int x = atomicAdd(ctr + 8, (ns - 1) * nt);
+    for (int k = 1; k < ns; k++)
+      for (int t = 0; t < nt; t++) extra[x++] = make_int2(li, nf_code(k, t));
+    atomicAdd(ctr + 2, ns - 1);
   }
 }
 
@@ -680,9 +689,9 @@ void plan_near_field(Ctx& c) {
   int* ctr = c.counters.p + NF_COUNTERS;
   hipLaunchKernelGGL(k_nf_plan, dim3((unsigned)ceil_div(nleaf, 256)), dim3(256), 0, c.stream, c.leaves.p, nleaf,
                      c.c_begin.p, c.c_end.p, c.p2p.off.p, c.sys_off.p, c.nsys, max_nb, tiled, long_len,
-                     (int)slots, (int)split, c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr);
+                     (int)slots, (int)split, (int)extra_max, c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr);
   HIPCHK(hipGetLastError());
-  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr + 3, nleaf,
+  c.nf = NfPlan{c.nf_cell_nseg.p, c.nf_cell_pbase.p, c.nf_extra.p, ctr + 8, nleaf,
                 (int)(nleaf + extra_max), (int)slots};
 }
 

@@ -62,10 +62,10 @@ P2P_FLOPS = 20   # per directed body pair: acc + pot, softened, rsqrt counted on
 # (fetch x2.0, write x1.0).  Keyed by (kernel, workload, precision); valid only
 # while the kernel's source file has the recorded SHA-1 (else reported as null).
 MEASURED_TRAFFIC = {
-    ("k_m2l_fp32", "plummer_1m", "mixed"): (2472.0e6, "paper_2012_02207_amd/csrc/m2l_mixed.hip",
+    ("k_m2l_fp32", "plummer_1m", "mixed"): (2475.0e6, "paper_2012_02207_amd/csrc/m2l_mixed.hip",
                                              "f3358e736b66a1a230d68f8cbf2d488acac11124"),
-    ("k_leaf_group (mixed P2P)", "plummer_1m", "mixed"): (1277.0e6, "paper_2012_02207_amd/csrc/local.hip",
-                                                           "c071b26545e9e9a8fd1fbe3f7b2d1fe16a8adbf7"),
+    ("k_leaf_group (mixed P2P)", "plummer_1m", "mixed"): (1261.0e6, "paper_2012_02207_amd/csrc/local.hip",
+                                                           "007e0f284ae8c85dfabf18d78804e57f6321a090"),
 }
 
 
